@@ -241,8 +241,9 @@ aq_status aq_layer_set_path(aq_layer* layer, aq_path path);
  *                           bit-identical to its in-loop decode), 2 the
  *                           dense product with both operands staged in LDS,
  *                           3 the wave-split convolution kernel (3x3 and
- *                           1x1) where it applies (image planes a multiple
- *                           of 4 pixels): 128-token tiles, or, with a
+ *                           1x1) where it applies (even image widths,
+ *                           planes a multiple of 4 pixels, output rows that
+ *                           tile 128 tokens): 128-token tiles, or, with a
  *                           64-token AQ_OPT_FUSED_TILE, 64-token tiles with
  *                           two waves per reduction
  *   AQ_OPT_FUSED_TILE       fused kernel tile BM * 1000 + BN (0 = planner);
@@ -255,9 +256,9 @@ aq_status aq_layer_set_path(aq_layer* layer, aq_path path);
  *                           (bit-identical outputs)
  *   AQ_OPT_TILE_ORDER       workgroup order: 0 auto, 1 token tiles slowest,
  *                           2 channel tiles slowest (bit-identical outputs)
- *   AQ_OPT_STAGE_ROWS       convolution staging: 0 each input row once per
- *                           block of output rows, 1 kh rows per output row
- *                           (bit-identical outputs)
+ *   AQ_OPT_STAGE_ROWS       kept for callers that set it (0 or 1); it has no
+ *                           effect: a convolution tile stages every input row
+ *                           it reads once
  *   AQ_OPT_SPLIT_K          fused kernel: workgroups sharing one output tile
  *                           along K (0 = planner, 1 = none, up to 8); partial
  *                           tiles are summed in a fixed order, so repeated

@@ -13,9 +13,11 @@ static hipError_t conv_tiles(const Geom& geo, const FusedPlan& p, const FusedLau
         AQ_TILE(128, 64, 3)
         AQ_TILE(128, 64, 6)
         AQ_TILE(64, 64, 6)
+        if constexpr (DEC == FUSED_DEC_REC) { AQ_TILE(64, 64, 9) }
     } else {
         AQ_TILE(64, 96, 4)
         AQ_TILE(64, 64, 4)
+        if constexpr (DEC == FUSED_DEC_REC) { AQ_TILE(64, 64, 8) }
     }
 #undef AQ_TILE
     return hipErrorInvalidConfiguration;

@@ -28,8 +28,11 @@
 //    token), so that one lane's 8 operand values are one 16-byte read and 16
 //    lanes read 256 contiguous bytes.
 //  * Linear layer: a chunk is 64 consecutive k (4 MFMA steps).
-//  * Convolution (implicit im2col): the staging area holds the input rows the
-//    token tile touches, with zero padding columns.  A 3x3 chunk is 16 input
+//  * Convolution (implicit im2col): a token tile is BM consecutive output
+//    pixels, whatever rows and images they start and end in; the staging area
+//    holds the run of input rows it touches, with zero padding columns.  (Rows
+//    that do not tile BM used to leave this kernel for the generic one: 3x3,
+//    4 images of 24 x 24, 576 -> 576 channels, M = 2: 379 -> 22.4 us.)  A 3x3 chunk is 16 input
 //    channels and one MFMA step is one kernel position (kh, kw) over them.
 //    The weight groups of a chunk run over (channel, kh, kw) with the channel
 //    outermost, so a lane decodes the 9 groups of its 8 channels and regroups
@@ -196,9 +199,9 @@ fused_fwd_kernel(Geom geo, FusedPlan plan, const void* __restrict__ cb, const ui
                  "s"(geo.cin), "s"(geo.OW), "s"(geo.OH), "s"(geo.stride), "s"(geo.pad));
     asm volatile("" ::"s"(plan.nchunk), "s"(plan.ps), "s"(plan.pw), "s"(plan.pr), "s"(plan.pbuf_bytes),
                  "s"(plan.nmajor), "s"(plan.units), "s"(plan.tile_div), "s"(plan.rec_bytes), "s"(plan.inv_pr),
-                 "s"(plan.inv_ow), "s"(plan.cb_bytes), "s"(plan.x_bytes), "s"(plan.total_rows), "s"(plan.inv_wp),
+                 "s"(plan.inv_ow), "s"(plan.cb_bytes), "s"(plan.x_bytes), "s"(plan.vrows), "s"(plan.inv_wp),
                  "s"(plan.inv_tile_div), "s"(plan.inv_oh), "s"(cb), "s"(crec), "s"(X), "s"(gridDim.x),
-                 "s"(plan.sr), "s"(plan.rpb), "s"(plan.inv_sr), "s"(plan.inv_rpb), "s"(plan.splitk),
+                 "s"(plan.vr), "s"(plan.rstep), "s"(plan.rmul), "s"(plan.inv_vr), "s"(plan.splitk),
                  "s"(plan.ntiles), "s"(plan.inv_ntiles));
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -269,28 +272,34 @@ fused_fwd_kernel(Geom geo, FusedPlan plan, const void* __restrict__ cb, const ui
     bool g_ok[UPL];                 // the unit loads data (false: zeros)
     bool l_ok[UPL];                 // the unit exists
     int k_first[UPL];               // linear: first k of the unit for chunk 0
-    const int gr0 = CONV ? fdiv(T0, geo.OW, plan.inv_ow) : 0;
+    int c_end[CONV ? UPL : 1];      // convolution: the unit loads data in chunks before c_end (0: none)
+    // convolution: the first staged row, kernel row 0 of the tile's first output row
+    int V0 = 0;
     if constexpr (CONV) {
-        const int wp = geo.W >> 1;  // pixel pairs per row
+        const int gr0 = __builtin_amdgcn_readfirstlane(fdiv(T0, geo.OW, plan.inv_ow));
+        const int b0 = __builtin_amdgcn_readfirstlane(fdiv(gr0, geo.OH, plan.inv_oh));
+        V0 = __umul24(b0, plan.vr) + __umul24(gr0 - (int)__umul24(b0, geo.OH), plan.rstep);
+    }
+    if constexpr (CONV) {
+        const int wp = (geo.W + 1) >> 1;  // pixel pairs per row (odd rows: the last pair repeats a pixel)
 #pragma unroll
         for (int j = 0; j < UPL; ++j) {
             const int u = lane + 64 * j;
             const int t = fdiv(u, wp, plan.inv_wp);
-            const int pp = u - __umul24(t, wp);
+            const int px = min(2 * (u - (int)__umul24(t, wp)), geo.W - 2);
             const int o = fdiv(t, plan.pr, plan.inv_pr);
             const int pr = t - __umul24(o, plan.pr);
-            // staged row pr: row jr of block blk, the input rows of plan.rpb
-            // consecutive output rows starting at output row gr (one image)
-            const int blk = fdiv(pr, plan.sr, plan.inv_sr), jr = pr - __umul24(blk, plan.sr);
-            const int gr = gr0 + __umul24(blk, plan.rpb);
-            const int b = fdiv(gr, geo.OH, plan.inv_oh), oh = gr - __umul24(b, geo.OH);
-            const int ih = __umul24(oh, geo.stride) - geo.pad + jr;
+            const int V = V0 + pr;
+            const int b = fdiv(V, plan.vr, plan.inv_vr);
+            const int ih = __umul24(V - (int)__umul24(b, plan.vr), plan.rmul) - geo.pad;
             l_ok[j] = u < plan.units;
-            g_ok[j] = l_ok[j] & (gr < plan.total_rows) & (ih >= 0) & (ih < geo.H);
-            const uint32_t ga = (uint32_t)(__umul24(__umul24(b, geo.cin) + 8 * o, geo.H) + ih) * (uint32_t)geo.W + 2u * pp;
+            g_ok[j] = l_ok[j] & (V < plan.vrows) & (ih >= 0) & (ih < geo.H);
+            const uint32_t ga = (uint32_t)(__umul24(__umul24(b, geo.cin) + 8 * o, geo.H) + ih) * (uint32_t)geo.W + (uint32_t)px;
             g_off[j] = g_ok[j] ? ga : 0u;
             k_first[j] = 0;
-            l_off[j] = l_ok[j] ? (uint32_t)(__umul24(o, plan.ps) + (__umul24(pr, plan.pw) + 2 * pp + geo.pad) * 16)
+            // the last chunk may hold fewer channels (8 o, ... exist in every chunk before c_end)
+            c_end[j] = g_ok[j] ? (geo.cin - 8 * o + 16 * CM - 1) / (16 * CM) : 0;
+            l_off[j] = l_ok[j] ? (uint32_t)(__umul24(o, plan.ps) + (__umul24(pr, plan.pw) + px + geo.pad) * 16)
                                : (uint32_t)(plan.pbuf_bytes - 32);
         }
     } else {
@@ -331,7 +340,7 @@ fused_fwd_kernel(Geom geo, FusedPlan plan, const void* __restrict__ cb, const ui
         for (int j = 0; j < UPL; ++j) {
             if constexpr (CONV) {
                 // 8 channels x 2 pixels
-                const uint32_t base = g_ok[j] & cv ? (g_off[j] + (uint32_t)(chunk * 16 * CM) * HW) * 2u : kOutOfRange;
+                const uint32_t base = chunk < c_end[j] ? (g_off[j] + (uint32_t)(chunk * 16 * CM) * HW) * 2u : kOutOfRange;
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
                     stage[j][e] = __builtin_amdgcn_raw_buffer_load_b32(xr, base + (uint32_t)(e * HW * 2), 0, 0);
@@ -414,13 +423,11 @@ fused_fwd_kernel(Geom geo, FusedPlan plan, const void* __restrict__ cb, const ui
     if constexpr (CONV) {
 #pragma unroll
         for (int a = 0; a < AM; ++a) {
-            const int T = T0 + 32 * a + l32;
+            const int T = min(T0 + 32 * a + l32, tokens - 1);   // rows past the last token are not staged
             const int gT = fdiv(T, geo.OW, plan.inv_ow);
-            const int r = gT - gr0;
             const int ow = T - __umul24(gT, geo.OW);
-            // output row r: block r / rpb, whose row (r % rpb) * stride is kernel row 0
-            const int blk = fdiv(r, plan.rpb, plan.inv_rpb), rr = r - __umul24(blk, plan.rpb);
-            const int R0 = __umul24(blk, plan.sr) + __umul24(rr, geo.stride);
+            const int b = fdiv(gT, geo.OH, plan.inv_oh), oh = gT - __umul24(b, geo.OH);
+            const int R0 = __umul24(b, plan.vr) + __umul24(oh, plan.rstep) - V0;
             a_base[a] = (uint32_t)(q * plan.ps + (__umul24(R0, plan.pw) + __umul24(ow, geo.stride)) * 16);
         }
         // zero the padding columns of both buffers once: (buffer, plane, row, pad column)

@@ -31,7 +31,7 @@ struct Options {
     int dense_bm, dense_bn;   // forced dense-product tile (0: planner)
     int rlin_tile;            // wave-split linear kernel tile variant (0, 1, 2)
     int tile_order;           // 0 auto, 1 token tiles slowest, 2 channel tiles slowest
-    int stage_rows;           // 1: kh staged rows per output row
+    int stage_rows;           // no effect (kept for callers that set it)
     int split_k;              // fused kernel K split over workgroups (0: planner)
     int grad_splits;          // codebook gradient token splits (0: planner)
     int grad_regs;            // 1: register-staged weight-gradient kernels
@@ -96,16 +96,17 @@ struct FusedPlan {
     int bm, bn, upl;      // tile and staging units per lane
     int units;            // staging units per chunk
     int pr, pw, ps;       // patch rows, patch width (pixels), pixel / token-row stride (bytes)
-    // convolution: the staged rows are blocks of sr rows, each holding every input
-    // row of rpb consecutive output rows of one image (output row i of a block
-    // reads block rows i * stride + kernel row)
-    int sr, rpb;
-    float inv_sr, inv_rpb;
+    // convolution: the input rows of all images in one numbering, vr rows per
+    // image: kernel row 0 of output row oh of image b is row b * vr + oh * rstep,
+    // and row v of an image is input row v * rmul - pad.  A tile stages the run
+    // of pr rows that starts at its first output row's.
+    int vr, rstep, rmul;
+    float inv_vr;
+    int vrows;            // images * vr
     int pbuf_bytes;       // one staging buffer
-    int total_rows;       // convolution: images * OH
     size_t lds_bytes;     // dynamic LDS per workgroup
-    // convolution: fp32 reciprocals of OW, OH, pr and W / 2 (correctly rounded)
-    // for the kernel's quotient-with-correction index arithmetic
+    // convolution: fp32 reciprocals of OW, OH, pr and (W + 1) / 2 (correctly
+    // rounded) for the kernel's quotient-with-correction index arithmetic
     float inv_ow, inv_oh, inv_pr, inv_wp;
     int64_t x_bytes;      // bytes of this forward's input X (the bound of the kernel's activation loads)
     int tile_div;         // tiles along the faster tile index (token tiles if nmajor, else channel tiles)

@@ -9,6 +9,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <numeric>
 #include <string>
 #include <utility>
 #include <vector>
@@ -295,28 +296,32 @@ bool fused_plan_create(const aq_layer_desc& d, int g, int M, int B, aq::FusedPla
     const bool conv = is_conv(d);
     if (g == 9 && !(conv && d.conv_kh == 3 && d.conv_kw == 3)) return false;   // g = 9: one 3x3 filter per group
     if (conv) {
-        if (d.x_dtype != AQ_F16 || d.in_w % 2 != 0) return false;
-        if (d.conv_kh == 3 && d.conv_kw == 3 && d.conv_cin % 16 == 0) {
+        if (d.x_dtype != AQ_F16 || d.in_w < 2 || d.conv_cin % 8 != 0) return false;
+        if (d.conv_kh == 3 && d.conv_kw == 3) {
             p->kind = 1;
             p->cm = 1;
-            p->nchunk = d.conv_cin / 16;
-        } else if (d.conv_kh == 1 && d.conv_kw == 1 && d.conv_pad == 0 && d.conv_cin % 64 == 0) {
+        } else if (d.conv_kh == 1 && d.conv_kw == 1 && d.conv_pad == 0) {
             p->kind = 2;
             p->cm = 4;
-            p->nchunk = d.conv_cin / 64;
         } else {
             return false;
         }
+        p->nchunk = (d.conv_cin + 16 * p->cm - 1) / (16 * p->cm);
+        // the g = 9 format is taken on even widths and whole 16-channel chunks only
+        if (g == 9 && (d.in_w % 2 != 0 || d.conv_cin % 16 != 0)) return false;
     } else {
         if (d.x_dtype != AQ_F16 && d.x_dtype != AQ_I8) return false;
         p->kind = 0;
         p->cm = 4;
         p->nchunk = (d.in_features + 63) / 64;
     }
-    if (g == 8 && (M == 2 || M == 4) && B <= 8 && d.codebook_dtype == AQ_F16) {
+    // a convolution whose last chunk is not whole: its codes past the end must
+    // decode to zeros, which the records do
+    const bool whole = !conv || d.conv_cin % (16 * p->cm) == 0;
+    if (whole && g == 8 && (M == 2 || M == 4) && B <= 8 && d.codebook_dtype == AQ_F16) {
         p->dec = aq::FUSED_DEC_PK16;
         p->cb_bytes = M * 256 * 16;             // LDS keeps 256 rows per codebook
-    } else if (g == 8 && M == 1 && B > 8 && d.codebook_dtype == AQ_F16) {
+    } else if (whole && g == 8 && M == 1 && B > 8 && d.codebook_dtype == AQ_F16) {
         p->dec = aq::FUSED_DEC_T16G;
         p->cb_bytes = 0;
     } else {
@@ -428,57 +433,66 @@ double cu_time(int64_t n, int occ, double loop, double fixed) {
     return (double)(n / occ) * together(occ) + together(n % occ);
 }
 
-// Staging geometry of a convolution tile of `bm` output pixels: the input
-// rows it reads (each input row once per block of output rows of one image: a
-// tile of whole images, or of consecutive rows of one image; kh rows per output
-// row when that stages fewer rows or AQ_OPT_STAGE_ROWS = 1), their padded width,
-// and the staging units (plane of 8 channels, staged row, pixel pair).  With
-// `widen`, a staged row is widened until consecutive output rows start OW
-// 16-byte slots apart (mod 64 banks), which makes A-fragment reads of rows
-// shorter than 16 tokens conflict free.  False when bm and OW do not tile
-// each other.
-bool conv_staging(const Geom& geo, const aq::Options& opt, int kind, int cm, int bm, bool widen, aq::FusedPlan* q) {
-    if (!(bm % geo.OW == 0 || geo.OW % bm == 0)) return false;
-    const int tr = bm >= geo.OW ? bm / geo.OW : 1;
+// Staging geometry of a convolution tile of `bm` consecutive output pixels:
+// the run of input rows it reads (FusedPlan::vr; every row once, whatever rows
+// and images the tile starts and ends in), their padded width, and the staging
+// units (plane of 8 channels, staged row, pixel pair).  With `widen`, a staged
+// row is widened until consecutive output rows start OW 16-byte slots apart
+// (mod 64 banks), which makes A-fragment reads of rows shorter than 16 tokens
+// conflict free.
+void conv_staging(const Geom& geo, int kind, int cm, int bm, bool widen, aq::FusedPlan* q) {
     const int kh = kind == 1 ? 3 : 1;
-    const int img = geo.OH * geo.OW;
-    int rpb = 1;
-    if (opt.stage_rows != 1) {
-        if (bm % img == 0) rpb = geo.OH;
-        else if (img % bm == 0 && tr > 1) rpb = tr;
-    }
-    int sr = (rpb - 1) * geo.stride + kh;
-    if (rpb > 1 && (tr / rpb) * sr >= tr * kh) {
-        rpb = 1;
-        sr = kh;
-    }
-    q->rpb = rpb;
-    q->sr = sr;
-    q->inv_rpb = 1.0f / (float)rpb;
-    q->inv_sr = 1.0f / (float)sr;
-    q->pr = (tr / rpb) * sr;
+    // 1x1: only the rows the outputs use are numbered
+    q->rstep = kh == 1 ? 1 : geo.stride;
+    q->rmul = kh == 1 ? geo.stride : 1;
+    q->vr = kh == 1 ? geo.OH : (geo.OH - 1) * geo.stride + kh;
+    q->inv_vr = 1.0f / (float)q->vr;
+    const int64_t img = (int64_t)geo.OH * geo.OW, nimg = geo.tokens / img;
+    q->vrows = (int)(nimg * q->vr);
+    // most output rows and image borders a tile spans (tiles start at multiples of bm)
+    const int gcd = std::gcd(bm, geo.OW);
+    const int64_t nr = std::min<int64_t>((geo.OW - gcd + bm - 1) / geo.OW + 1, nimg * geo.OH);
+    int64_t cross = img % bm == 0 ? 0 : bm % img == 0 ? bm / img - 1 : nr >= 2 ? (nr - 2) / geo.OH + 1 : 0;
+    cross = std::min<int64_t>(cross, nimg - 1);
+    q->pr = (int)((nr - 1) * q->rstep + kh + cross * std::max(0, q->vr - geo.OH * q->rstep));
     q->pw = geo.W + 2 * geo.pad;
-    // consecutive output rows of a block are `stride` staged rows apart (kh
-    // apart with one output row per block)
-    const int rstep = rpb > 1 ? geo.stride : kh;
     if (widen)
-        while ((rstep * q->pw - geo.OW) % 16 != 0) ++q->pw;
+        while ((q->rstep * q->pw - geo.OW) % 16 != 0) ++q->pw;
     q->ps = q->pr * q->pw * 16;                    // one plane of 8 channels
-    q->units = 2 * cm * q->pr * (geo.W / 2);       // (plane, row, pixel pair)
-    q->total_rows = (int)(geo.tokens / geo.OW);
+    q->units = 2 * cm * q->pr * ((geo.W + 1) / 2); // (plane, row, pixel pair)
     q->inv_ow = 1.0f / (float)geo.OW;
     q->inv_oh = 1.0f / (float)geo.OH;
     q->inv_pr = 1.0f / (float)q->pr;
-    q->inv_wp = 1.0f / (float)(geo.W / 2);
-    return true;
+    q->inv_wp = 1.0f / (float)((geo.W + 1) / 2);
+}
+
+// The geometry the convolution kernels run on: a 1x1 convolution with stride 1
+// reads its images as rows of the largest power of two up to 64 pixels that
+// divides them, whatever their own width (a token tile then stages no pixel it
+// does not use); any other layer keeps its own.
+Geom kernel_geom(const Geom& geo) {
+    Geom g = geo;
+    if (geo.conv && geo.kh == 1 && geo.kw == 1 && geo.stride == 1 && geo.pad == 0) {
+        const int img = geo.H * geo.W;
+        int w = 64;
+        while (img % w != 0) w /= 2;
+        if (w >= 2) {
+            g.W = g.OW = w;
+            g.H = g.OH = img / w;
+        }
+    }
+    return g;
 }
 
 bool fused_plan_tile(const Geom& geo, const aq::Options& opt, size_t part_cap, int x_dtype, aq::FusedPlan* p) {
-    static const TileCand conv3[] = {{64, 96, 3}, {64, 64, 3}, {128, 64, 3}, {128, 64, 6}, {64, 64, 6}};
-    static const TileCand conv1[] = {{64, 96, 4}, {64, 64, 4}};
+    // (the last convolution tiles, with more staged pixels per lane, are built for
+    // pre-decoded operands only)
+    static const TileCand conv3[] = {{64, 96, 3}, {64, 64, 3}, {128, 64, 3}, {128, 64, 6}, {64, 64, 6}, {64, 64, 9}};
+    static const TileCand conv1[] = {{64, 96, 4}, {64, 64, 4}, {64, 64, 8}};
     static const TileCand lin[] = {{64, 96, 8}, {64, 64, 8}, {32, 128, 4}, {32, 64, 4}};
     const TileCand* cands = p->kind == 1 ? conv3 : p->kind == 2 ? conv1 : lin;
-    const int ncand = p->kind == 1 ? 5 : p->kind == 2 ? 2 : 4;
+    const int rec_only = p->kind != 0 && p->dec != aq::FUSED_DEC_REC ? 1 : 0;
+    const int ncand = (p->kind == 1 ? 6 : p->kind == 2 ? 3 : 4) - rec_only;
     const int want_bm = opt.fused_bm, want_bn = opt.fused_bn;
     double best = 0;
     aq::FusedPlan bestp{};
@@ -499,14 +513,14 @@ bool fused_plan_tile(const Geom& geo, const aq::Options& opt, size_t part_cap, i
         q.bn = t.bn;
         q.upl = t.upl;
         if (p->kind != 0) {
-            if (!conv_staging(geo, opt, p->kind, p->cm, t.bm, widen, &q)) continue;
+            conv_staging(geo, p->kind, p->cm, t.bm, widen, &q);
         } else {
             q.pr = q.pw = 0;
-            q.sr = q.rpb = 1;
-            q.inv_ow = q.inv_oh = q.inv_pr = q.inv_wp = q.inv_sr = q.inv_rpb = 0.0f;
+            q.vr = q.rstep = q.rmul = 1;
+            q.inv_ow = q.inv_oh = q.inv_pr = q.inv_wp = q.inv_vr = 0.0f;
             q.ps = t.bm * 16 + 16;                      // one plane of 8 consecutive k
             q.units = t.bm * 2 * p->cm;                 // (token, plane)
-            q.total_rows = 0;
+            q.vrows = 0;
         }
         q.pbuf_bytes = 2 * p->cm * q.ps + 32;       // + a spare slot for padding units
         if ((q.units + 63) / 64 > t.upl) continue;
@@ -669,10 +683,10 @@ bool use_predecoded(const aq_layer* L, const Geom& geo) {
 // multiple of 4 tokens, more staging units than instantiated).
 bool wsplit_plan(const Geom& geo, const aq::Options& opt, int wk, aq::FusedPlan* p) {
     if (p->dec != aq::FUSED_DEC_REC || !(p->kind == 1 || (p->kind == 2 && p->cm == 4))) return false;
-    if ((geo.OH * geo.OW) % 4 != 0 || geo.W % 2 != 0) return false;
+    if ((geo.OH * geo.OW) % 4 != 0) return false;
     const int bm = wk == 1 ? 128 : 64;
     aq::FusedPlan q = *p;
-    if (!conv_staging(geo, opt, p->kind, p->cm, bm, false, &q)) return false;
+    conv_staging(geo, p->kind, p->cm, bm, false, &q);
     q.upl = (wk * q.units + 255) / 256;
     if (p->kind == 1 ? q.upl > 3 : q.upl != 2) return false;
     int bn = geo.C_out % 192 == 0 ? 192 : 128;
@@ -702,7 +716,18 @@ bool wsplit_plan(const Geom& geo, const aq::Options& opt, int wk, aq::FusedPlan*
 struct Route {
     enum Kind { LUT = 0, F32 = 1, GENERIC = 2, DENSE = 3, FUSED = 4, REC_LINEAR = 5, NONE = 6 } kind;
     aq::FusedPlan fp;
+    Geom geo;          // the geometry the kernels run on (kernel_geom)
+    bool uneven;       // a convolution outside even_tiles
 };
+
+// A convolution whose images tile evenly: even widths, whole channel chunks,
+// and 64- or 128-token tiles that are whole output rows or parts of one.  The
+// dense product and the g = 9 format run on these only, the wave-split kernel
+// is forced on these only, and the allocation-free forward gives any other
+// one the generic kernel where its records pass the static array.
+bool even_tiles(const Geom& geo, const aq::FusedPlan& p) {
+    return geo.W % 2 == 0 && geo.cin % (16 * p.cm) == 0 && (128 % geo.OW == 0 || geo.OW % 64 == 0);
+}
 
 Route plan_route(const aq_layer* L, const Geom& geo) {
     Route r{};
@@ -719,8 +744,19 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
     aq::FusedPlan fp = L->fplan;
     // the fused kernel uses 32-bit element and byte offsets
     const int64_t nimg = geo.conv ? geo.tokens / ((int64_t)geo.OH * geo.OW) : 0;
-    const bool fits31 = geo.tokens * (int64_t)std::max(geo.K, geo.C_out) * 4 < (int64_t(1) << 31) &&
-                        (!geo.conv || nimg * (int64_t)geo.cin * geo.H * geo.W * 2 < (int64_t(1) << 31));
+    bool fits31 = geo.tokens * (int64_t)std::max(geo.K, geo.C_out) * 4 < (int64_t(1) << 31) &&
+                  (!geo.conv || nimg * (int64_t)geo.cin * geo.H * geo.W * 2 < (int64_t(1) << 31));
+    r.geo = kernel_geom(geo);
+    r.uneven = geo.conv && L->fused_ok && !even_tiles(geo, L->fplan);
+    if (r.uneven) {
+        // small images of few channels can pass what the index arithmetic takes
+        // (24-bit factors) before the byte offsets do
+        const int64_t lim24 = int64_t(1) << 24;
+        fits31 = fits31 && geo.tokens < lim24 && nimg * ((geo.OH - 1) * (int64_t)geo.stride + geo.kh) < lim24 &&
+                 nimg * geo.cin < lim24 && (int64_t)geo.C_out * geo.K * 2 < (int64_t(1) << 31);
+        // other codebook types decode their records value by value and keep the generic kernel
+        if (geo.g != 8 || d.codebook_dtype != AQ_F16) fits31 = false;
+    }
     if (L->fused_ok && use_predecoded(L, geo)) {
         // pre-decoded mode: operands decoded once per forward, then read with plain loads
         fp.dec = aq::FUSED_DEC_REC;
@@ -736,10 +772,12 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
     aq::FusedPlan gp = fp;
     // dense product over the records: a comparator route (AQ_OPT_RECORD_PRODUCT = 2);
     // measured slower than the fused kernel's pre-decoded mode on most layer shapes here
-    if (L->fused_ok && fits31 && fp.dec == aq::FUSED_DEC_REC && opt.rec_product == 2 && gemm_plan_tile(geo, opt, &gp)) {
+    if (L->fused_ok && fits31 && !r.uneven && fp.dec == aq::FUSED_DEC_REC && opt.rec_product == 2 &&
+        gemm_plan_tile(geo, opt, &gp)) {
         order(gp);
         r.kind = Route::DENSE;
         r.fp = gp;
+        r.geo = geo;
         return r;
     }
     // Convolutions on the wave-split records kernel where its tiles fill the
@@ -770,11 +808,11 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
         rp.mc = 1;
         rp.cb_bytes = 0;
         aq::FusedPlan w1 = rp, w2 = rp;
-        const bool ok1 = wsplit_plan(geo, opt, 1, &w1), ok2 = wsplit_plan(geo, opt, 2, &w2);
+        const bool ok1 = wsplit_plan(r.geo, opt, 1, &w1), ok2 = wsplit_plan(r.geo, opt, 2, &w2);
         const aq::FusedPlan* pick = nullptr;
         if (opt.rec_product == 3 && !ws_switch) {
-            if (opt.fused_bm == 64 ? ok2 : ok1) pick = opt.fused_bm == 64 ? &w2 : &w1;
-        } else if (opt.rec_product == 0 && geo.OW >= 16) {
+            if (!r.uneven && (opt.fused_bm == 64 ? ok2 : ok1)) pick = opt.fused_bm == 64 ? &w2 : &w1;
+        } else if (opt.rec_product == 0 && r.geo.OW >= 16) {
             // (output rows under 16 tokens: this kernel does not widen its staged
             // rows, and its fragment reads conflict; 8 x 8 images measured slower)
             if (ok1 && w1.ntiles >= (fp.kind == 1 ? 192 : 256)) pick = &w1;
@@ -787,7 +825,14 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
         }
     }
     if (!planned && L->fused_ok && fits31 && opt.generic != 1)
-        planned = fused_plan_tile(geo, opt, L->part_bytes, d.x_dtype, &fp);
+        planned = fused_plan_tile(r.geo, opt, L->part_bytes, d.x_dtype, &fp);
+    if (!planned && r.uneven && fits31 && opt.generic != 1 && fp.dec != aq::FUSED_DEC_REC && opt.weights != 1) {
+        // long output rows stage more pixels than the in-loop tiles hold
+        fp.dec = aq::FUSED_DEC_REC;
+        fp.mc = 1;
+        fp.cb_bytes = 0;
+        planned = fused_plan_tile(r.geo, opt, L->part_bytes, d.x_dtype, &fp);
+    }
     if (planned) {
         order(fp);
         fp.tile_div = fp.nmajor ? (int)((geo.tokens + fp.bm - 1) / fp.bm) : (geo.C_out + fp.bn - 1) / fp.bn;
@@ -881,8 +926,8 @@ aq_status run_route(aq_layer* L, const Geom& geo, const Route& r, const void* X,
         const aq::FusedLaunch fl{cbsrc, recs, L->d_scales, X, xs, Y, d.y_dtype, d.x_dtype, st, wk.part, wk.arrivals};
         if (e == hipSuccess)
             e = r.kind == Route::REC_LINEAR ? aq::launch_rec_linear(geo, fp, fl)
-                : fp.wsplit                  ? aq::launch_rec_conv(geo, fp, fl)
-                                             : aq::launch_fused_forward(geo, fp, fl);
+                : fp.wsplit                  ? aq::launch_rec_conv(r.geo, fp, fl)
+                                             : aq::launch_fused_forward(r.geo, fp, fl);
         break;
     }
     }
@@ -1140,7 +1185,7 @@ aq_status aq_layer_create(const aq_layer_desc* desc, const void* codebooks, cons
                 }
                 // room for every split count the planner allows on its tile, so a
                 // forced split (AQ_OPT_SPLIT_K) fits too
-                if (fused_plan_tile(gmax, aq::Options{}, SIZE_MAX, desc->x_dtype, &q) && q.ntiles < 256) {
+                if (fused_plan_tile(kernel_geom(gmax), aq::Options{}, SIZE_MAX, desc->x_dtype, &q) && q.ntiles < 256) {
                     const int smax = std::min<int>({aq::kMaxSplitK, 512 / q.ntiles, q.nchunk / 4});
                     if (smax > 1) need = std::max(need, (size_t)smax * q.ntiles * q.bm * q.bn * 4);
                 }
@@ -1301,6 +1346,10 @@ aq_status aq_layer_forward_static(aq_layer* L, const void* X, const float* x_sca
     Workspace wk;
     // sizes first, so a refused call launches nothing
     s = static_workspace(L, geo, r, reinterpret_cast<uint8_t*>(uintptr_t(256)), &wk);
+    if (s != AQ_OK && r.kind == Route::FUSED && r.uneven) {
+        r.kind = Route::GENERIC;      // needs no scratch
+        s = static_workspace(L, geo, r, reinterpret_cast<uint8_t*>(uintptr_t(256)), &wk);
+    }
     if (s != AQ_OK) return s;
     const hipStream_t st = static_cast<hipStream_t>(stream);
     s = scratch_for_current_device(st, &base);
@@ -1330,7 +1379,7 @@ aq_status aq_layer_describe(const aq_layer* L, int64_t n, char* buf, int64_t siz
         if (r.kind == Route::FUSED)
             t += " upl=" + std::to_string(p.upl) + " split_k=" + std::to_string(p.splitk) +
                  " order=" + (p.nmajor ? "channel" : "token") +
-                 " wg_per_cu=" + std::to_string(fused_occupancy(geo, p, L->desc.x_dtype));
+                 " wg_per_cu=" + std::to_string(fused_occupancy(r.geo, p, L->desc.x_dtype));
         if (r.kind == Route::REC_LINEAR) t += " variant=" + std::to_string(p.rlin_var);
         if (p.dec == aq::FUSED_DEC_REC)
             t += " records_bytes=" + std::to_string(aq::operand_record_bytes(geo, p));

@@ -89,8 +89,8 @@ rec_conv_kernel(Geom geo, FusedPlan plan, const uint8_t* __restrict__ rec, const
                  "s"(geo.OH), "s"(geo.stride), "s"(geo.pad));
     asm volatile("" ::"s"(plan.nchunk), "s"(plan.ps), "s"(plan.pw), "s"(plan.pr), "s"(plan.pbuf_bytes),
                  "s"(plan.nmajor), "s"(plan.units), "s"(plan.tile_div), "s"(plan.inv_pr), "s"(plan.inv_ow),
-                 "s"(plan.x_bytes), "s"(plan.total_rows), "s"(plan.inv_wp), "s"(plan.inv_tile_div), "s"(plan.inv_oh),
-                 "s"(plan.sr), "s"(plan.rpb), "s"(plan.inv_sr), "s"(plan.inv_rpb), "s"(rec), "s"(X));
+                 "s"(plan.x_bytes), "s"(plan.vrows), "s"(plan.inv_wp), "s"(plan.inv_tile_div), "s"(plan.inv_oh),
+                 "s"(plan.vr), "s"(plan.rstep), "s"(plan.rmul), "s"(plan.inv_vr), "s"(rec), "s"(X));
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -119,37 +119,38 @@ rec_conv_kernel(Geom geo, FusedPlan plan, const uint8_t* __restrict__ rec, const
 
     // ---- staging units of this thread: unit tid + 256 j is (chunk g of the
     // iteration, plane o, staged row, pixel pair) ----
-    const int gr0 = qdiv_rc(T0, geo.OW, plan.inv_ow);   // first output row of the tile
+    int V0;   // the first staged row, kernel row 0 of the tile's first output row
+    {
+        const int gr0 = __builtin_amdgcn_readfirstlane(qdiv_rc(T0, geo.OW, plan.inv_ow));
+        const int b0 = __builtin_amdgcn_readfirstlane(qdiv_rc(gr0, geo.OH, plan.inv_oh));
+        V0 = __umul24(b0, plan.vr) + __umul24(gr0 - (int)__umul24(b0, geo.OH), plan.rstep);
+    }
     uint32_t g_off[UPL];   // element offset of the unit's first value for iteration 0
     uint32_t l_off[UPL];   // byte offset of the unit's destination from its parity's buffer of chunk 0
-    int u_chunk[UPL];      // the unit's chunk within an iteration
-    bool g_ok[UPL];
+    int i_end[UPL];        // the unit loads data in iterations before i_end (0: none)
     {
-        const int wp = geo.W >> 1;
+        const int wp = (geo.W + 1) >> 1;   // odd rows: the last pair repeats a pixel
 #pragma unroll
         for (int j = 0; j < UPL; ++j) {
             const int uu = tid + 256 * j;
             const int g = WK == 2 && uu >= plan.units ? 1 : 0;
             const int u = uu - g * plan.units;
-            u_chunk[j] = g;
             const int t = qdiv_rc(u, wp, plan.inv_wp);
-            const int pp = u - __umul24(t, wp);
+            const int px = min(2 * (u - (int)__umul24(t, wp)), geo.W - 2);
             const int o = qdiv_rc(t, plan.pr, plan.inv_pr);
             const int pr = t - __umul24(o, plan.pr);
-            // staged row pr: row jr of block blk, the input rows of plan.rpb
-            // consecutive output rows starting at output row gr (one image)
-            const int blk = qdiv_rc(pr, plan.sr, plan.inv_sr), jr = pr - __umul24(blk, plan.sr);
-            const int gr = gr0 + __umul24(blk, plan.rpb);
-            const int b = qdiv_rc(gr, geo.OH, plan.inv_oh), oh = gr - __umul24(b, geo.OH);
-            const int ih = __umul24(oh, geo.stride) - geo.pad + jr;
+            const int V = V0 + pr;
+            const int b = qdiv_rc(V, plan.vr, plan.inv_vr);
+            const int ih = __umul24(V - (int)__umul24(b, plan.vr), plan.rmul) - geo.pad;
             const bool l_ok = u < plan.units;
-            g_ok[j] = l_ok & (gr < plan.total_rows) & (ih >= 0) & (ih < geo.H);
-            g_off[j] = g_ok[j] ? (uint32_t)(__umul24(__umul24(b, geo.cin) + 8 * o + 16 * CM * g, geo.H) + ih) *
-                                         (uint32_t)geo.W +
-                                     2u * pp
-                               : 0u;
+            const bool g_ok = l_ok & (V < plan.vrows) & (ih >= 0) & (ih < geo.H);
+            const int chan = 8 * o + 16 * CM * g;   // the unit's first channel in iteration 0
+            i_end[j] = g_ok ? (geo.cin - chan + WK * 16 * CM - 1) / (WK * 16 * CM) : 0;
+            g_off[j] = g_ok ? (uint32_t)(__umul24(__umul24(b, geo.cin) + chan, geo.H) + ih) * (uint32_t)geo.W +
+                                  (uint32_t)px
+                            : 0u;
             l_off[j] = l_ok ? (uint32_t)(2 * g * plan.pbuf_bytes + __umul24(o, plan.ps) +
-                                         (__umul24(pr, plan.pw) + 2 * pp + geo.pad) * 16)
+                                         (__umul24(pr, plan.pw) + px + geo.pad) * 16)
                             : (uint32_t)(plan.pbuf_bytes - 32);   // a spare slot
         }
     }
@@ -159,9 +160,8 @@ rec_conv_kernel(Geom geo, FusedPlan plan, const uint8_t* __restrict__ rec, const
     auto stage_load = [&](int it) {
 #pragma unroll
         for (int j = 0; j < UPL; ++j) {
-            const bool cv = WK * it + u_chunk[j] < plan.nchunk;
             const uint32_t base =
-                g_ok[j] & cv ? (g_off[j] + (uint32_t)(WK * it * 16 * CM) * (uint32_t)HW) * 2u : kOutOfRange;
+                it < i_end[j] ? (g_off[j] + (uint32_t)(WK * it * 16 * CM) * (uint32_t)HW) * 2u : kOutOfRange;
 #pragma unroll
             for (int e = 0; e < 8; ++e)
                 stg[j][e] = __builtin_amdgcn_raw_buffer_load_b32(xr, base + (uint32_t)(e * HW * 2), 0, 0);
@@ -186,13 +186,11 @@ rec_conv_kernel(Geom geo, FusedPlan plan, const uint8_t* __restrict__ rec, const
     uint32_t a_base[TM];
 #pragma unroll
     for (int a = 0; a < TM; ++a) {
-        const int T = T0 + WT + 32 * a + l32;
+        const int T = min(T0 + WT + 32 * a + l32, tokens - 1);   // rows past the last token are not staged
         const int gT = qdiv_rc(T, geo.OW, plan.inv_ow);
-        const int r = gT - gr0;
         const int ow = T - __umul24(gT, geo.OW);
-        // output row r: block r / rpb, whose row (r % rpb) * stride is kernel row 0
-        const int blk = qdiv_rc(r, plan.rpb, plan.inv_rpb), rr = r - __umul24(blk, plan.rpb);
-        const int R0 = __umul24(blk, plan.sr) + __umul24(rr, geo.stride);
+        const int b = qdiv_rc(gT, geo.OH, plan.inv_oh), oh = gT - __umul24(b, geo.OH);
+        const int R0 = __umul24(b, plan.vr) + __umul24(oh, plan.rstep) - V0;
         a_base[a] = (uint32_t)(2 * wk * plan.pbuf_bytes + q * plan.ps +
                                (__umul24(R0, plan.pw) + __umul24(ow, geo.stride)) * 16);
     }

@@ -1,0 +1,93 @@
+"""GPU parity of the kernels on shapes where their index arithmetic can go wrong: image widths and heights that
+do not tile a token tile, odd widths, channel counts that leave a chunk partly empty, ragged token counts.
+
+Every element of Y is compared with the fp64 oracle, by infinity-norm relative error and by the per-element
+rounding bound of the path's arithmetic; a second forward must give the same bits.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from parity_checks import check_against_oracle, sampled_outputs
+from workloads import ConvGeom, LayerSpec, generate
+
+pytestmark = pytest.mark.gpu
+
+TOL = 2e-3
+
+
+def _conv(name, n, cin, C_out, k, H, W, stride=1, M=2, B=8, **kw):
+    geom = ConvGeom(cin, k, k, stride, (k - 1) // 2, H, W)
+    return LayerSpec(name=name, C_out=C_out, K=geom.K, g=8, M=M, B=B, n=n, conv=geom, **kw)
+
+
+def _forward(spec, inp, opts=None):
+    import paper_2506_05960_amd as P
+    layer = P.AQLayer(spec, inp)
+    for k, v in (opts or {}).items():
+        layer.set_option(k, v)
+    route = layer.describe(spec.n)
+    print(spec.name, opts or {}, route, flush=True)
+    x = torch.from_numpy(np.ascontiguousarray(inp["x"])).cuda()
+    y, y2 = layer.forward(x), layer.forward(x)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y2)
+    layer.close()
+    return y.float().cpu().numpy().astype(np.float64), route
+
+
+def _check(spec, inp, y):
+    tok, ch = np.arange(spec.tokens), np.arange(spec.C_out)
+    check_against_oracle(spec, inp, sampled_outputs(spec, y, tok, ch), tok, ch, "decode", TOL)
+
+
+UNEVEN = [
+    _conv("u24", 2, 32, 64, 3, 24, 24),                       # rows that start mid-tile, one image border per tile
+    _conv("u24_m4_long", 1, 256, 96, 3, 24, 24, M=4),         # a K split over a partial last tile
+    _conv("u72", 1, 16, 40, 3, 6, 72),                        # rows longer than a tile
+    _conv("u10", 5, 48, 72, 3, 10, 10),                       # two image borders in one tile, planes not a multiple of 8
+    _conv("u9_odd", 3, 16, 33, 3, 9, 9),                      # odd width, planes not a multiple of 4
+    _conv("u25x31_odd", 2, 24, 64, 3, 25, 31),                # odd width, a half-empty last chunk
+    _conv("u13x15_s2", 3, 64, 48, 3, 13, 15, stride=2),       # odd width, stride 2
+    _conv("u7x2", 4, 8, 16, 3, 7, 2),                         # the narrowest width, half a chunk in all
+    _conv("u40x132", 1, 16, 64, 3, 40, 132),                  # the most staged pixels per lane
+    _conv("u36_rec", 4, 64, 256, 3, 36, 36, M=1),             # records only
+    _conv("u28_b16", 2, 48, 64, 3, 28, 28, M=1, B=16),        # codewords from memory
+    _conv("u1x1_24", 3, 80, 96, 1, 24, 24),                   # 1x1, a partly empty chunk, planes of 64-pixel rows
+    _conv("u1x1_odd", 2, 64, 64, 1, 15, 17),                  # 1x1, odd planes
+    _conv("u1x1_10", 7, 40, 50, 1, 10, 10, M=4),              # 1x1, 4-pixel rows
+    _conv("u48_wide", 8, 48, 256, 3, 48, 48, y_dtype="f32"),  # enough tiles for the wave-split kernel
+    _conv("u1x1_wide", 12, 144, 192, 1, 54, 52),
+]
+
+
+@pytest.mark.parametrize("spec", UNEVEN, ids=lambda s: s.name)
+@pytest.mark.parametrize("weights", [0, 1, 2])
+def test_uneven_convolutions(spec, weights):
+    inp = generate(spec, 7001)
+    y, route = _forward(spec, inp, {"weights": weights})
+    # (forced to decode in its loop, the fused kernel stages fewer pixels than the longest and odd 1x1 rows need)
+    assert route["route"] in ("fused", "rec-conv") or weights == 1
+    _check(spec, inp, y)
+    if weights == 0:
+        y_gen, route = _forward(spec, inp, {"generic": 1})
+        assert route["route"] == "generic"
+        _check(spec, inp, y_gen)
+
+
+def test_uneven_convolution_static_and_limits():
+    """The allocation-free forward gives the forward's bits; g = 9 on an odd width stays refused."""
+    import paper_2506_05960_amd as P
+    spec = UNEVEN[0]
+    inp = generate(spec, 7002)
+    layer = P.AQLayer(spec, inp)
+    x = torch.from_numpy(inp["x"]).cuda()
+    assert torch.equal(layer.forward(x), layer.forward(x, static=True))
+    layer.close()
+    g9 = LayerSpec(name="g9_24", C_out=64, K=32 * 9, g=9, M=2, B=8, n=1, conv=ConvGeom(32, 3, 3, 1, 1, 24, 24))
+    layer = P.AQLayer(g9, generate(g9, 7003))
+    with pytest.raises(P.AQError) as e:
+        layer.forward(torch.zeros((1, 32, 24, 24), dtype=torch.float16, device="cuda"))
+    assert e.value.status == 2
+    layer.close()
