@@ -217,6 +217,89 @@ __device__ __forceinline__ void records_f16_body(const u32x4* __restrict__ cb, c
     }
 }
 
+// Records of a 64-wide chunk in bf16 (linear layers with bf16 tiles): the M
+// codewords of a group summed in fp32 in ascending m and rounded once.  MC > 0
+// fixes M, and every load of a thread is then issued before any sum; MC = 0
+// loops over M.  Bound by its two dependent memory levels (codes, then
+// codewords), like the fp16 kernel above.
+template <int CBT>
+__device__ __forceinline__ void codeword8(const void* cb, int64_t row, float (&v)[8]) {
+    if constexpr (CBT == AQ_F32) {
+        const floatx4* p = static_cast<const floatx4*>(cb) + 2 * row;
+        const floatx4 a = p[0], b = p[1];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[e] = a[e];
+            v[4 + e] = b[e];
+        }
+    } else {
+        const u32x4 w = static_cast<const u32x4*>(cb)[row];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const uint16_t h = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+            v[e] = CBT == AQ_F16 ? f16_to_f32(h) : bf16_to_f32(h);
+        }
+    }
+}
+
+template <int CBT, typename CodeT, int MC>
+__global__ void __launch_bounds__(256)
+operand_records_bf16_kernel(const void* __restrict__ cb, const CodeT* __restrict__ codes, u32x4* __restrict__ rec,
+                            int nchunk, int C_out, int Gn, int Mn, int B) {
+    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;   // (chunk, channel, half)
+    if (idx >= (int64_t)nchunk * C_out * 2) return;
+    const int c = (int)(idx / (2 * C_out));
+    const int rem = (int)(idx - (int64_t)c * 2 * C_out);
+    const int n = rem >> 1, q = rem & 1;
+    const int64_t rows = (int64_t)1 << B;
+    const int M = MC ? MC : Mn;
+    float v[4][8];
+    auto code = [&](int s, int m) -> int64_t {
+        const int j = min(8 * c + 2 * s + q, Gn - 1);   // groups past the end of K are zeroed below
+        return codes[((int64_t)n * Gn + j) * M + m];
+    };
+    if constexpr (MC > 0) {
+        int64_t k[4][MC];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int m = 0; m < MC; ++m) k[s][m] = code(s, m);
+        float w[4][MC][8];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int m = 0; m < MC; ++m) codeword8<CBT>(cb, m * rows + k[s][m], w[s][m]);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                v[s][e] = w[s][0][e];
+#pragma unroll
+                for (int m = 1; m < MC; ++m) v[s][e] = __fadd_rn(v[s][e], w[s][m][e]);
+            }
+    } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) codeword8<CBT>(cb, code(s, 0), v[s]);
+        for (int m = 1; m < M; ++m)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                float w[8];
+                codeword8<CBT>(cb, m * rows + code(s, m), w);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[s][e] = __fadd_rn(v[s][e], w[e]);
+            }
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        u32x4 o;
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+            o[d] = (uint32_t)f32_to_bf16(opaque_f32(v[s][2 * d])) | ((uint32_t)f32_to_bf16(opaque_f32(v[s][2 * d + 1])) << 16);
+        if (8 * c + 2 * s + q >= Gn) o = u32x4{0u, 0u, 0u, 0u};
+        rec[(((int64_t)c * 4 + s) * C_out + n) * 2 + q] = o;
+    }
+}
+
 template <typename CodeT, bool K3, int MC>
 __global__ void __launch_bounds__(256)
 operand_records_f16_kernel(const u32x4* __restrict__ cb, const CodeT* __restrict__ codes, u32x4* __restrict__ rec,
@@ -344,6 +427,25 @@ static hipError_t records_dispatch(const Geom& geo, const FusedPlan& plan, const
     u32x4* r = static_cast<u32x4*>(rec);
     if (plan.kind != 1 && plan.cm != 4) return hipErrorInvalidConfiguration;
     if (geo.g != 8 && !(geo.g == 9 && plan.kind == 1)) return hipErrorInvalidConfiguration;
+    if (plan.tile == AQ_BF16) {
+        if (plan.kind != 0 || geo.g != 8) return hipErrorInvalidConfiguration;
+#define AQ_RECB(CBT, MC)                                                                                      \
+    operand_records_bf16_kernel<CBT, CodeT, MC><<<grid, block, 0, st>>>(w.codebooks, codes, r, plan.nchunk,   \
+                                                                        geo.C_out, geo.G, geo.M, geo.B)
+#define AQ_RECB_M(CBT)                 \
+    if (geo.M == 1) AQ_RECB(CBT, 1);   \
+    else if (geo.M == 2) AQ_RECB(CBT, 2); \
+    else AQ_RECB(CBT, 0);
+        switch (w.cb_dtype) {
+        case AQ_F32: AQ_RECB_M(AQ_F32) break;
+        case AQ_F16: AQ_RECB_M(AQ_F16) break;
+        default: AQ_RECB_M(AQ_BF16) break;
+        }
+#undef AQ_RECB_M
+#undef AQ_RECB
+        note_launch(st, "operand_records_bf16_kernel", {w.cb_dtype, 8 * (int)sizeof(CodeT), geo.M <= 2 ? geo.M : 0});
+        return hipGetLastError();
+    }
     if (w.cb_dtype == AQ_F16 && geo.g == 8 && (geo.M == 1 || geo.M == 2 || geo.M == 4)) {
         const u32x4* cb = static_cast<const u32x4*>(w.codebooks);
 #define AQ_REC16(K3, MC) \
@@ -403,7 +505,7 @@ hipError_t launch_operand_records(const Geom& geo, const FusedPlan& plan, const 
 }
 
 int records_batch_key(const Geom& geo, const FusedPlan& plan, const DeviceWeights& w) {
-    if (w.cb_dtype != AQ_F16) return -1;
+    if (w.cb_dtype != AQ_F16 || plan.tile != AQ_F16) return -1;
     const int mi = geo.M == 1 ? 0 : geo.M == 2 ? 1 : geo.M == 4 ? 2 : -1;
     if (mi < 0) return -1;
     const int c16 = geo.B > 8;

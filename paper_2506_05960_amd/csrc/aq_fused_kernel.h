@@ -1,4 +1,5 @@
-// Fused decode + matrix-core forward (fp16 tiles, group size 8), gfx950.
+// Fused decode + matrix-core forward (fp16 tiles, group size 8; linear layers
+// also in bf16), gfx950.
 //
 // Work split.  A workgroup owns a BM (tokens) x BN (output channels) tile of Y
 // and its four waves split the reduction dimension: wave w takes K chunks
@@ -57,9 +58,15 @@ __device__ __forceinline__ void wave_sync() {
     asm volatile("" ::: "memory");
 }
 
-__device__ __forceinline__ floatx16 mfma_f16(const u32x4& a, const u32x4& b, const floatx16& c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0,
-                                                  0);
+// One matrix-core step on fp16 operands (bf16 ones where the input is bf16).
+template <int XT>
+__device__ __forceinline__ floatx16 mfma_step(const u32x4& a, const u32x4& b, const floatx16& c) {
+    if constexpr (XT == AQ_BF16)
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
+                                                       0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0,
+                                                      0, 0);
 }
 
 // Dword made of fp16 half `hlo` of xlo (low half) and half `hhi` of xhi (high half).
@@ -151,6 +158,19 @@ __device__ __forceinline__ u32x4 combine_group(const GroupRaw<DEC, MC>& g) {
         for (int d = 0; d < 4; ++d) {
             const float a = opaque_f32(s[2 * d]), b = opaque_f32(s[2 * d + 1]);
             r[d] = (uint32_t)f32_to_f16(a) | ((uint32_t)f32_to_f16(b) << 16);
+        }
+        return r;
+    } else if constexpr (DEC == FUSED_DEC_BF16) {
+        u32x4 r;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            float lo = __uint_as_float(g.w[0][d] << 16), hi = __uint_as_float(g.w[0][d] & 0xFFFF0000u);
+#pragma unroll
+            for (int m = 1; m < MC; ++m) {
+                lo = __fadd_rn(lo, __uint_as_float(g.w[m][d] << 16));
+                hi = __fadd_rn(hi, __uint_as_float(g.w[m][d] & 0xFFFF0000u));
+            }
+            r[d] = (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16);
         }
         return r;
     } else {   // M == 1: the codeword is already the fp16 weight
@@ -558,8 +578,8 @@ fused_fwd_kernel(Geom geo, FusedPlan plan, const void* __restrict__ cb, const ui
                 for (int b = 0; b < AN; ++b)
 #pragma unroll
                     for (int a = 0; a < AM; ++a) {
-                        if constexpr (CONV) acc[a][b] = mfma_f16(rec[P][s][b], afb[(s + P * NS) & 1][a], acc[a][b]);
-                        else acc[a][b] = mfma_f16(afb[(s + P * NS) & 1][a], rec[P][s][b], acc[a][b]);
+                        if constexpr (CONV) acc[a][b] = mfma_step<XT>(rec[P][s][b], afb[(s + P * NS) & 1][a], acc[a][b]);
+                        else acc[a][b] = mfma_step<XT>(afb[(s + P * NS) & 1][a], rec[P][s][b], acc[a][b]);
                     }
                 // each product followed by a share of the loads and fragment reads
 #pragma unroll
@@ -627,8 +647,8 @@ fused_fwd_kernel(Geom geo, FusedPlan plan, const void* __restrict__ cb, const ui
                 }
 #pragma unroll
                 for (int a = 0; a < AM; ++a) {
-                    if constexpr (CONV) acc[a][b] = mfma_f16(bf, af[s][a], acc[a][b]);   // rows: channels
-                    else acc[a][b] = mfma_f16(af[s][a], bf, acc[a][b]);                  // rows: tokens
+                    if constexpr (CONV) acc[a][b] = mfma_step<XT>(bf, af[s][a], acc[a][b]);   // rows: channels
+                    else acc[a][b] = mfma_step<XT>(af[s][a], bf, acc[a][b]);                  // rows: tokens
                 }
             }
             if (have_next) {

@@ -23,15 +23,20 @@ static hipError_t lin_tiles(const Geom& geo, const FusedPlan& p, const FusedLaun
 
 template <int XT>
 static hipError_t lin_dec(const Geom& geo, const FusedPlan& p, const FusedLaunch& fl) {
-    if (p.dec == FUSED_DEC_PK16 && p.mc == 2) return lin_tiles<XT, FUSED_DEC_PK16, 2>(geo, p, fl);
-    if (p.dec == FUSED_DEC_PK16 && p.mc == 4) return lin_tiles<XT, FUSED_DEC_PK16, 4>(geo, p, fl);
-    if (p.dec == FUSED_DEC_T16G) return lin_tiles<XT, FUSED_DEC_T16G, 1>(geo, p, fl);
+    constexpr int DEC = XT == AQ_BF16 ? FUSED_DEC_BF16 : FUSED_DEC_PK16;
+    if (p.dec == DEC && p.mc == 2) return lin_tiles<XT, DEC, 2>(geo, p, fl);
+    if (p.dec == DEC && p.mc == 4) return lin_tiles<XT, DEC, 4>(geo, p, fl);
+    if constexpr (XT != AQ_BF16) {
+        if (p.dec == FUSED_DEC_T16G) return lin_tiles<XT, FUSED_DEC_T16G, 1>(geo, p, fl);
+    }
     if (p.dec == FUSED_DEC_REC) return lin_tiles<XT, FUSED_DEC_REC, 1>(geo, p, fl);
     return hipErrorInvalidConfiguration;
 }
 
 hipError_t launch_fused_linear(const Geom& geo, const FusedPlan& p, const FusedLaunch& fl) {
+    if ((fl.x_dtype == AQ_BF16) != (p.tile == AQ_BF16)) return hipErrorInvalidConfiguration;
     if (fl.x_dtype == AQ_I8) return lin_dec<AQ_I8>(geo, p, fl);
+    if (fl.x_dtype == AQ_BF16) return lin_dec<AQ_BF16>(geo, p, fl);
     return lin_dec<AQ_F16>(geo, p, fl);
 }
 

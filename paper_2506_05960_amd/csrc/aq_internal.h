@@ -71,12 +71,12 @@ struct LutPlan {
     bool mfma_table;              // table built on the matrix cores (fp16 codebook, fp16/int8 input, g == 8)
 };
 
-// ---- fused decode + matrix-core path (fp16 tiles, g == 8) ----
+// ---- fused decode + matrix-core path (fp16 tiles; bf16 tiles for linear layers with bf16 input) ----
 
 enum FusedDec {
     FUSED_DEC_PK16 = 0,   // fp16 codebooks in LDS, codewords accumulated with packed fp16 adds
     FUSED_DEC_F32L = 1,   // fp32 codebooks in LDS, fp32 sum in ascending m
-    FUSED_DEC_T16L = 2,   // M == 1, codebook pre-rounded to fp16, in LDS
+    FUSED_DEC_BF16 = 2,   // bf16 codebooks in LDS, fp32 sum in ascending m, rounded once to bf16
     FUSED_DEC_T16G = 3,   // M == 1, codebook pre-rounded to fp16, read from global memory (B > 8)
     FUSED_DEC_REC = 4     // operands decoded beforehand into per-step records (one 16-byte load each)
 };
@@ -87,6 +87,7 @@ struct FusedPlan {
     int nchunk;           // chunks along K
     int rec_bytes;        // code record bytes per (chunk, output channel, lane half)
     int dec;              // FusedDec
+    int tile;             // aq_dtype of the decoded operands (F16, or BF16 with bf16 input)
     int mc;               // M
     int cb_bytes;         // LDS codebook bytes (0 when read from global memory)
     int rec_only;         // no in-loop decode for this format: always the pre-decoded mode

@@ -292,8 +292,11 @@ bool lut_plan_create(const aq_layer_desc& d, int g, int M, int G, LutPlan* p) {
 
 bool fused_plan_create(const aq_layer_desc& d, int g, int M, int B, aq::FusedPlan* p) {
     std::memset(p, 0, sizeof(*p));
-    if (d.tile_dtype != AQ_F16 || (g != 8 && g != 9)) return false;
     const bool conv = is_conv(d);
+    // bf16 tiles: linear layers with bf16 input (other bf16 layers run on the generic kernel)
+    const bool bf16 = d.tile_dtype == AQ_BF16 && !conv && d.x_dtype == AQ_BF16 && g == 8;
+    if ((d.tile_dtype != AQ_F16 && !bf16) || (g != 8 && g != 9)) return false;
+    p->tile = d.tile_dtype;
     if (g == 9 && !(conv && d.conv_kh == 3 && d.conv_kw == 3)) return false;   // g = 9: one 3x3 filter per group
     if (conv) {
         if (d.x_dtype != AQ_F16 || d.in_w < 2 || d.conv_cin % 8 != 0) return false;
@@ -310,7 +313,7 @@ bool fused_plan_create(const aq_layer_desc& d, int g, int M, int B, aq::FusedPla
         // the g = 9 format is taken on even widths and whole 16-channel chunks only
         if (g == 9 && (d.in_w % 2 != 0 || d.conv_cin % 16 != 0)) return false;
     } else {
-        if (d.x_dtype != AQ_F16 && d.x_dtype != AQ_I8) return false;
+        if (!bf16 && d.x_dtype != AQ_F16 && d.x_dtype != AQ_I8) return false;
         p->kind = 0;
         p->cm = 4;
         p->nchunk = (d.in_features + 63) / 64;
@@ -318,10 +321,11 @@ bool fused_plan_create(const aq_layer_desc& d, int g, int M, int B, aq::FusedPla
     // a convolution whose last chunk is not whole: its codes past the end must
     // decode to zeros, which the records do
     const bool whole = !conv || d.conv_cin % (16 * p->cm) == 0;
-    if (whole && g == 8 && (M == 2 || M == 4) && B <= 8 && d.codebook_dtype == AQ_F16) {
-        p->dec = aq::FUSED_DEC_PK16;
+    const bool in_lds = whole && g == 8 && (M == 2 || M == 4) && B <= 8;
+    if (in_lds && d.codebook_dtype == d.tile_dtype) {
+        p->dec = bf16 ? aq::FUSED_DEC_BF16 : aq::FUSED_DEC_PK16;
         p->cb_bytes = M * 256 * 16;             // LDS keeps 256 rows per codebook
-    } else if (whole && g == 8 && M == 1 && B > 8 && d.codebook_dtype == AQ_F16) {
+    } else if (whole && g == 8 && M == 1 && B > 8 && d.codebook_dtype == AQ_F16 && !bf16) {
         p->dec = aq::FUSED_DEC_T16G;
         p->cb_bytes = 0;
     } else {
@@ -541,7 +545,7 @@ bool fused_plan_tile(const Geom& geo, const aq::Options& opt, size_t part_cap, i
         if (p->kind == 0 && p->dec == aq::FUSED_DEC_REC && !(t.bm == 64 && t.bn == 64)) tcost *= 1.25;
         if (narrow && !widen) tcost *= 1.15;             // bank conflicts on the A-fragment reads (measured)
         const bool under = underfilled(geo);
-        if (under && p->dec == aq::FUSED_DEC_PK16) tcost *= 1.0 + 32.0 * p->mc / t.bm;
+        if (under && (p->dec == aq::FUSED_DEC_PK16 || p->dec == aq::FUSED_DEC_BF16)) tcost *= 1.0 + 32.0 * p->mc / t.bm;
         for (int S = 1; S <= aq::kMaxSplitK; ++S) {
             if (opt.split_k != 0 && S != opt.split_k && !(S == 1 && opt.split_k > 1)) continue;
             if (S > 1) {
@@ -772,7 +776,7 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
     aq::FusedPlan gp = fp;
     // dense product over the records: a comparator route (AQ_OPT_RECORD_PRODUCT = 2);
     // measured slower than the fused kernel's pre-decoded mode on most layer shapes here
-    if (L->fused_ok && fits31 && !r.uneven && fp.dec == aq::FUSED_DEC_REC && opt.rec_product == 2 &&
+    if (L->fused_ok && fits31 && !r.uneven && fp.tile == AQ_F16 && fp.dec == aq::FUSED_DEC_REC && opt.rec_product == 2 &&
         gemm_plan_tile(geo, opt, &gp)) {
         order(gp);
         r.kind = Route::DENSE;
@@ -913,7 +917,7 @@ aq_status run_route(aq_layer* L, const Geom& geo, const Route& r, const void* X,
         break;
     }
     default: {   // FUSED, REC_LINEAR
-        const void* cbsrc = fp.dec == aq::FUSED_DEC_PK16   ? L->d_cb
+        const void* cbsrc = fp.dec == aq::FUSED_DEC_PK16 || fp.dec == aq::FUSED_DEC_BF16 ? L->d_cb
                             : fp.dec == aq::FUSED_DEC_F32L ? static_cast<const void*>(L->d_cb32)
                                                            : L->d_cbtile;
         const uint8_t* recs = L->d_crec;
@@ -1346,7 +1350,8 @@ aq_status aq_layer_forward_static(aq_layer* L, const void* X, const float* x_sca
     Workspace wk;
     // sizes first, so a refused call launches nothing
     s = static_workspace(L, geo, r, reinterpret_cast<uint8_t*>(uintptr_t(256)), &wk);
-    if (s != AQ_OK && r.kind == Route::FUSED && r.uneven) {
+    if (s != AQ_OK && (r.kind == Route::FUSED || r.kind == Route::REC_LINEAR) &&
+        (r.uneven || L->fplan.tile == AQ_BF16)) {
         r.kind = Route::GENERIC;      // needs no scratch
         s = static_workspace(L, geo, r, reinterpret_cast<uint8_t*>(uintptr_t(256)), &wk);
     }
@@ -1366,7 +1371,7 @@ aq_status aq_layer_describe(const aq_layer* L, int64_t n, char* buf, int64_t siz
     if (geo.tokens > L->desc.max_tokens) return fail(AQ_ERR_INVALID_ARGUMENT, "tokens exceed max_tokens");
     const Route r = plan_route(L, geo);
     static const char* kinds[] = {"table", "fp32", "generic", "dense-records", "fused", "rec-linear", "none"};
-    static const char* decs[] = {"in-loop-lds-fp16", "in-loop-lds-fp32", "in-loop-lds-fp16", "in-loop-l2-fp16",
+    static const char* decs[] = {"in-loop-lds-fp16", "in-loop-lds-fp32", "in-loop-lds-bf16", "in-loop-l2-fp16",
                                  "records"};
     const char* route = r.kind == Route::FUSED && r.fp.wsplit ? "rec-conv" : kinds[r.kind];
     std::string t = std::string("path=") + (r.kind == Route::LUT ? "lut" : "decode") + " route=" + route;

@@ -205,8 +205,8 @@ rec_gemm_kernel(Geom geo, FusedPlan plan, GemmArgs ga) {
             for (int a = 0; a < AM; ++a)
 #pragma unroll
                 for (int b = 0; b < AN; ++b) {
-                    if constexpr (CONV) acc[a][b] = mfma_f16(bf[s & 1][b], af[s & 1][a], acc[a][b]);   // rows: channels
-                    else acc[a][b] = mfma_f16(af[s & 1][a], bf[s & 1][b], acc[a][b]);                  // rows: tokens
+                    if constexpr (CONV) acc[a][b] = mfma_step<AQ_F16>(bf[s & 1][b], af[s & 1][a], acc[a][b]);   // rows: channels
+                    else acc[a][b] = mfma_step<AQ_F16>(af[s & 1][a], bf[s & 1][b], acc[a][b]);                  // rows: tokens
                 }
             __builtin_amdgcn_sched_barrier(0);
         }

@@ -12,7 +12,7 @@
 // Operands, per 64-wide K chunk (4 matrix-core steps of 16):
 //  * Weights: record (chunk, step, channel, lane half) holds the 8 fp16
 //    weights of that lane's v_mfma_f32_32x32x16_f16 A operand (k = 64 chunk +
-//    16 step + 8 half + 0..7).  A wave reads its channel blocks' records
+//    16 step + 8 half + 0..7; bf16 for layers with bf16 tiles and input).  A wave reads its channel blocks' records
 //    straight into registers; the two waves of a channel half read the same
 //    records, the second read hitting the L1 cache.
 //  * Activations: the tile's 64-wide slice of X (fp16, or int8 widened exactly
@@ -54,9 +54,15 @@ struct RecLinArgs {
     uint32_t step_bytes;      // record bytes of one (chunk, step): C_out * 32
 };
 
+// One matrix-core step: bf16 operands where the input is bf16, else fp16.
+template <int XT>
 __device__ __forceinline__ floatx16 mfma16(const u32x4& a, const u32x4& b, const floatx16& c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0,
-                                                  0);
+    if constexpr (XT == AQ_BF16)
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
+                                                       0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0,
+                                                      0, 0);
 }
 
 // 8 fp16 values from 8 int8 values, exactly: the fp16 bit pattern
@@ -227,7 +233,7 @@ rec_linear_kernel(RecLinArgs ar, const uint8_t* __restrict__ rec, const float* _
 #pragma unroll
             for (int b = 0; b < TN; ++b)
 #pragma unroll
-                for (int a = 0; a < TM; ++a) acc[b][a] = mfma16(rc[P][b][s], xf[s & 1][a], acc[b][a]);
+                for (int a = 0; a < TM; ++a) acc[b][a] = mfma16<XT>(rc[P][b][s], xf[s & 1][a], acc[b][a]);
             // order within the step: each product followed by a share of the
             // loads, fragment reads, widening and staging writes
 #pragma unroll
@@ -368,7 +374,7 @@ hipError_t rec_linear_cfg(const RecLinArgs& ar, const FusedLaunch& fl) {
 
 bool rec_linear_supported(const Geom& geo, const FusedPlan& plan, int x_dtype) {
     if (geo.conv || plan.kind != 0 || plan.cm != 4 || geo.g != 8) return false;
-    if (x_dtype != AQ_F16 && x_dtype != AQ_I8) return false;
+    if (x_dtype != (plan.tile == AQ_BF16 ? AQ_BF16 : AQ_F16) && !(x_dtype == AQ_I8 && plan.tile == AQ_F16)) return false;
     if (geo.C_out % 4 != 0) return false;
     const int64_t lim = int64_t(1) << 31;
     const int64_t rec_bytes = (int64_t)plan.nchunk * 4 * geo.C_out * 32;
@@ -413,6 +419,11 @@ hipError_t launch_rec_linear(const Geom& geo, const FusedPlan& plan, const Fused
         if (var == 1) return rec_linear_cfg<AQ_I8, 4, 2, 2>(ar, fl);
         if (var == 2) return rec_linear_cfg<AQ_I8, 4, 1, 1>(ar, fl);
         return rec_linear_cfg<AQ_I8, 2, 2, 2>(ar, fl);
+    }
+    if (fl.x_dtype == AQ_BF16) {
+        if (var == 1) return rec_linear_cfg<AQ_BF16, 4, 2, 2>(ar, fl);
+        if (var == 2) return rec_linear_cfg<AQ_BF16, 4, 1, 1>(ar, fl);
+        return rec_linear_cfg<AQ_BF16, 2, 2, 2>(ar, fl);
     }
     if (var == 1) return rec_linear_cfg<AQ_F16, 4, 2, 2>(ar, fl);
     if (var == 2) return rec_linear_cfg<AQ_F16, 4, 1, 1>(ar, fl);

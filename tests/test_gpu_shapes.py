@@ -91,3 +91,53 @@ def test_uneven_convolution_static_and_limits():
         layer.forward(torch.zeros((1, 32, 24, 24), dtype=torch.float16, device="cuda"))
     assert e.value.status == 2
     layer.close()
+
+
+def _bf16(name, n, K, C_out, M=2, B=8, cb="bf16", y="f32"):
+    return LayerSpec(name=name, C_out=C_out, K=K, g=8, M=M, B=B, n=n, codebook_dtype=cb, x_dtype="bf16", y_dtype=y,
+                     tile_dtype="bf16")
+
+
+BF16 = [
+    _bf16("b_1", 1, 64, 64),
+    _bf16("b_ragged", 77, 200, 131, M=2, B=6),                # a partial chunk, a C_out that is no multiple of 4
+    _bf16("b_m4_splitk", 130, 2304, 96, M=4),                 # a K split
+    _bf16("b_m3", 70, 136, 72, M=3),                          # records, M loop
+    _bf16("b_m1_b12", 65, 64, 68, M=1, B=12),                 # 16-bit codes
+    _bf16("b_cb16", 90, 264, 100, M=1, cb="f16", y="f16"),
+    _bf16("b_cb32", 90, 264, 100, M=2, cb="f32", y="f16"),
+    _bf16("b_wide", 2100, 128, 1664, y="f16"),                # enough tiles for the wave-split linear kernel
+]
+
+
+@pytest.mark.parametrize("spec", BF16, ids=lambda s: s.name)
+@pytest.mark.parametrize("weights", [0, 2])
+def test_bf16_linear(spec, weights):
+    """bf16 linear layers against the 64-bit product of the inputs and the decode's rounded weights (host
+    emulation): within the rounding of an fp32 sum of K exact products and the two scalings, |dY| <= 4 K 2^-24
+    sum |x w|, plus that of an fp16 output; the generic kernel, on the same weights, within twice that."""
+    import paper_2506_05960_amd as P
+    inp = generate(spec, 7101)
+    xb = torch.from_numpy(inp["x"].view(np.int16)).cuda().view(torch.bfloat16)
+    layer = P.AQLayer(spec, inp)
+    layer.set_option("lut_max_tokens", -1)
+    layer.set_option("weights", weights)
+    route = layer.describe(spec.n)
+    print(spec.name, weights, route, flush=True)
+    assert route["route"] in ("fused", "rec-linear")
+    y, y2 = layer.forward(xb), layer.forward(xb)
+    assert torch.equal(y, y2)
+    assert torch.equal(y, layer.forward(xb, static=True))
+    layer.set_option("generic", 1)
+    assert layer.describe(spec.n)["route"] == "generic"
+    y_gen = layer.forward(xb)
+    w = O.decode_emulate(inp["codebooks"], inp["codes"], inp["scales"], 8, spec.codebook_dtype, "bf16", scaled=False)
+    w = torch.from_numpy(w.view(np.int16)).cuda().view(torch.bfloat16).double() * torch.from_numpy(
+        inp["scales"]).cuda().double()[:, None]
+    bound = 4 * spec.K * 2.0**-24 * (xb.double().abs() @ w.abs().t())
+    ref = xb.double() @ w.t()
+    if spec.y_dtype == "f16":
+        bound = bound + 2.0**-11 * ref.abs() + 2.0**-24
+    assert torch.all((y.double() - ref).abs() <= bound)
+    assert torch.all((y.double() - y_gen.double()).abs() <= 2 * bound)
+    layer.close()
