@@ -1,95 +1,271 @@
-// fp32 decode path: weight tiles are expanded from codes into LDS in fp32
-// (any group size g) and contracted with fp32 FMAs.  Serves layers whose
-// tile dtype is fp32, where the matrix-core fp16/bf16 rounding of the weight
-// tile is not wanted.
+// fp32 decode path: layers whose tile dtype is fp32, where the matrix-core
+// fp16/bf16 rounding of the weight tile is not wanted.  Weights are expanded
+// from codes in fp32 (any group size g) and contracted with fp32 matrix-core
+// products (v_mfma_f32_32x32x2_f32: exact fp32 operands, fp32 accumulation).
+//
+// Work split.  A workgroup owns 32 TM tokens x 32 output channels and its NW
+// waves split K into contiguous runs, so that a small layer still puts many
+// waves on the chip; the partial tiles meet in LDS and are added in wave
+// order.  Each step of a wave covers 8 k: a lane loads 4 consecutive
+// activations of each of its tokens and decodes 4 consecutive weights of its
+// channel (half a group of g = 8: one 16-byte read per codeword), straight
+// into operand registers, and four products per 32 tokens consume them.
+//
+// Bound by the vector-memory path of the few compute units a small layer
+// occupies: a wave's 64 lanes read 32 different rows, so an instruction costs
+// tens of cycles whatever it fetches (codes read byte by byte for every step
+// and codebook took most of a 64 x 256 -> 256 layer's time).  So where M
+// divides 16 and B <= 8, a lane reads the codes of 16 / M groups as one
+// 16-byte piece of the table path's code layout, in which consecutive channels
+// are consecutive, and gathers its codewords from a copy of the codebooks in
+// LDS (about 50 cycles a gather, 130 through the L1).
+//
+// Measured, M = 2: 64 tokens x 256 -> 256 5.9 us (52.8 with the 64 x 64 vector-ALU
+// tiles this replaces, which decoded 16 k at a time between barriers); 256 x
+// 512 -> 512 8.6 us (101); 1000 x 704 -> 704 22.8 us (131), 43 TFLOP/s.
+#include <algorithm>
+
 #include "aq_device.h"
 
 namespace aq {
 
-constexpr int kF32BM = 64, kF32BN = 64, kF32BK = 16;
+constexpr int kF32Tile = 32;
+constexpr int kF32Steps = 4;       // steps of 8 k whose loads are in flight together
+constexpr int kF32Pitch = kF32Tile + 1;
 
-template <int XT, typename CodeT>
-__global__ void __launch_bounds__(256)
+// MC > 0: g == 8 and M == MC, codes in chunks of 16 bytes and codebooks in LDS;
+// else one of
+constexpr int kF32AnyG = 0;    // any group size, codewords value by value from memory
+constexpr int kF32G8 = -1;     // g == 8, any M and B, codewords from memory
+
+template <int XT, typename CodeT, int MC, int NW, int TM>
+__global__ void __launch_bounds__(64 * NW)
 f32_fwd_kernel(Geom geo, const float* __restrict__ cb32, const CodeT* __restrict__ codes,
                const float* __restrict__ scales, const void* __restrict__ X, const float* __restrict__ x_scales,
-               void* __restrict__ Y, int y_dtype) {
-    __shared__ float xs[kF32BK][kF32BM + 4];
-    __shared__ float wsh[kF32BK][kF32BN + 4];
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
-    const int64_t m0 = (int64_t)blockIdx.x * kF32BM;
-    const int n0 = blockIdx.y * kF32BN;
-    const int g = geo.g, M = geo.M;
-    const int64_t nk = (int64_t)1 << geo.B;
-    float acc[4][4] = {};
+               void* __restrict__ Y, int y_dtype, int tiles_n) {
+    extern __shared__ __attribute__((aligned(16))) float lds_f32[];   // codebooks, then the partial tiles
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, q = lane >> 5;
+    const int64_t m0 = (int64_t)(blockIdx.x / (unsigned)tiles_n) * (kF32Tile * TM);
+    const int n0 = (int)(blockIdx.x % (unsigned)tiles_n) * kF32Tile;
+    const int g = geo.g, M = geo.M, K = geo.K;
+    const int nk = 1 << geo.B;
 
-    for (int k0 = 0; k0 < geo.K; k0 += kF32BK) {
-        // 64 x 16 activations and 64 x 16 decoded weights, 4 of each per thread
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = tid + q * 256;
-            const int row = e & 63;
-            const int kk = e >> 6;
-            const int k = k0 + kk;
-            const int64_t tok = m0 + row;
-            xs[kk][row] = (tok < geo.tokens && k < geo.K) ? x_elem<XT>(geo, X, tok, k) : 0.0f;
-            const int co = n0 + row;
-            float w = 0.0f;
-            if (co < geo.C_out && k < geo.K) {
-                const int j = k / g;
-                const int t = k - j * g;
-                const CodeT* bp = codes + ((int64_t)co * geo.G + j) * M;
-                w = cb32[(int64_t)bp[0] * g + t];
-                for (int m = 1; m < M; ++m) w = __fadd_rn(w, cb32[((int64_t)m * nk + bp[m]) * g + t]);
-            }
-            wsh[kk][row] = w;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < kF32BK; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                a[i] = xs[kk][ty * 4 + i];
-                b[i] = wsh[kk][tx * 4 + i];
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) acc[i][jj] = fmaf(a[i], b[jj], acc[i][jj]);
-        }
-        __syncthreads();
+    if constexpr (MC > 0) {
+        const int n4 = MC * nk * 2;
+        for (int i = tid; i < n4; i += 64 * NW)
+            reinterpret_cast<floatx4*>(lds_f32)[i] = reinterpret_cast<const floatx4*>(cb32)[i];
     }
+    // rows past the last token or channel repeat it; their outputs are not stored
+    int64_t tok[TM];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t tok = m0 + ty * 4 + i;
-        if (tok >= geo.tokens) continue;
+    for (int a = 0; a < TM; ++a) {
+        const int64_t t = m0 + 32 * a + l32;
+        tok[a] = t < geo.tokens ? t : geo.tokens - 1;
+    }
+    const int co = min(n0 + l32, geo.C_out - 1);
+    const CodeT* crow = codes + (int64_t)co * geo.G * M;
+    const bool xvec = XT == AQ_F32 && !geo.conv && K % 4 == 0;   // whole 16-byte pieces of a row
+
+    floatx16 acc[TM];
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            const int co = n0 + tx * 4 + jj;
-            if (co >= geo.C_out) continue;
-            float v = acc[i][jj] * scales[co];
-            if (x_scales) v *= x_scales[tok];
-            const int64_t yi = y_index(geo, tok, co);
-            if (y_dtype == AQ_F32) static_cast<float*>(Y)[yi] = v;
-            else static_cast<uint16_t*>(Y)[yi] = f32_to_f16(v);
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[a][r] = 0.0f;
+
+    auto load_x = [&](const int64_t t, int k) -> floatx4 {   // k .. k + 3 (past K: the last ones again)
+        if (xvec) return *reinterpret_cast<const floatx4*>(static_cast<const float*>(X) + t * K + min(k, K - 4));
+        floatx4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = x_elem<XT>(geo, X, t, min(k + e, K - 1));
+        return v;
+    };
+    if constexpr (MC > 0) {
+        constexpr int JC = 16 / MC;                  // groups (steps) per chunk
+        const int nchunk = (geo.G + JC - 1) / JC;
+        const int per = (nchunk + NW - 1) / NW;
+        const int c_end = min(nchunk, (wave + 1) * per);
+        const u32x4* cchunk = reinterpret_cast<const u32x4*>(codes) + co;
+        u32x4 cw = {};
+        if (wave * per < c_end) cw = cchunk[(int64_t)(wave * per) * geo.C_out];
+        __syncthreads();
+        for (int c = wave * per; c < c_end; ++c) {
+            constexpr int U = JC < 8 ? JC : 8;       // steps whose operands are in registers together
+            const u32x4 cur = cw;
+            if (c + 1 < c_end) cw = cchunk[(int64_t)(c + 1) * geo.C_out];
+#pragma unroll
+            for (int h = 0; h < JC / U; ++h) {
+                floatx4 xv[TM][U], wv[U];
+#pragma unroll
+                for (int a = 0; a < TM; ++a)
+#pragma unroll
+                    for (int u = 0; u < U; ++u) xv[a][u] = load_x(tok[a], 8 * (c * JC + h * U + u) + 4 * q);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+#pragma unroll
+                    for (int m = 0; m < MC; ++m) {
+                        const int i = (h * U + u) * MC + m;
+                        const uint32_t code = (cur[i >> 2] >> (8 * (i & 3))) & 0xFFu;
+                        const floatx4 w = *reinterpret_cast<const floatx4*>(lds_f32 + (m * nk + code) * 8 + 4 * q);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) wv[u][e] = m == 0 ? w[e] : __fadd_rn(wv[u][e], w[e]);
+                    }
+                    if (c * JC + h * U + u >= geo.G) {   // past K (uniform): zeros
+                        wv[u] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                        for (int a = 0; a < TM; ++a) xv[a][u] = wv[u];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int a = 0; a < TM; ++a)
+                            acc[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(xv[a][u][e], wv[u][e], acc[a], 0, 0, 0);
+            }
+        }
+    } else {
+        const int nstep = (K + 7) / 8;
+        const int per = (nstep + NW - 1) / NW;
+        const int s_end = min(nstep, (wave + 1) * per);
+        for (int s0 = wave * per; s0 < s_end; s0 += kF32Steps) {
+            // steps past the wave's last read its last group (every address is
+            // in range) and become zeros before the products
+            floatx4 xv[TM][kF32Steps], wv[kF32Steps];
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int u = 0; u < kF32Steps; ++u) xv[a][u] = load_x(tok[a], 8 * (s0 + u) + 4 * q);
+            if constexpr (MC == kF32G8) {
+                const CodeT* cp[kF32Steps];
+#pragma unroll
+                for (int u = 0; u < kF32Steps; ++u) cp[u] = crow + (int64_t)min(s0 + u, s_end - 1) * M;
+                for (int m = 0; m < M; ++m) {
+                    int64_t row[kF32Steps];
+#pragma unroll
+                    for (int u = 0; u < kF32Steps; ++u) row[u] = (int64_t)m * nk + cp[u][m];
+#pragma unroll
+                    for (int u = 0; u < kF32Steps; ++u) {
+                        const floatx4 c = *reinterpret_cast<const floatx4*>(cb32 + row[u] * 8 + 4 * q);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) wv[u][e] = m == 0 ? c[e] : __fadd_rn(wv[u][e], c[e]);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < kF32Steps; ++u)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int k = min(8 * (s0 + u) + 4 * q + e, K - 1);
+                        const int j = k / g, t = k - j * g;
+                        const CodeT* bp = crow + (int64_t)j * M;
+                        float w = cb32[(int64_t)bp[0] * g + t];
+                        for (int m = 1; m < M; ++m) w = __fadd_rn(w, cb32[((int64_t)m * nk + bp[m]) * g + t]);
+                        wv[u][e] = w;
+                    }
+            }
+#pragma unroll
+            for (int u = 0; u < kF32Steps; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool live = s0 + u < s_end && 8 * (s0 + u) + 4 * q + e < K;
+                    wv[u][e] = live ? wv[u][e] : 0.0f;
+#pragma unroll
+                    for (int a = 0; a < TM; ++a) xv[a][u][e] = live ? xv[a][u][e] : 0.0f;
+                }
+#pragma unroll
+            for (int u = 0; u < kF32Steps; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int a = 0; a < TM; ++a)
+                        acc[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(xv[a][u][e], wv[u][e], acc[a], 0, 0, 0);
         }
     }
+
+    // lane (l32, q) holds channel l32 of tokens 32 a + 8 (r / 4) + 4 q + r % 4
+    constexpr int PART = kF32Tile * TM * kF32Pitch;
+    float* red = lds_f32;
+    if constexpr (MC > 0) __syncthreads();   // the last codebook reads
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            red[wave * PART + (32 * a + 8 * (r >> 2) + 4 * q + (r & 3)) * kF32Pitch + l32] = acc[a][r];
+    __syncthreads();
+    constexpr int ROWS = kF32Tile * TM;
+    for (int e = tid; e < ROWS * kF32Tile; e += 64 * NW) {
+        // consecutive lanes store along the output's fast dimension
+        const int row = geo.conv ? e % ROWS : e / kF32Tile;
+        const int col = geo.conv ? e / ROWS : e % kF32Tile;
+        const int64_t t = m0 + row;
+        const int c = n0 + col;
+        if (t >= geo.tokens || c >= geo.C_out) continue;
+        float v = red[row * kF32Pitch + col];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) v += red[w * PART + row * kF32Pitch + col];
+        v *= scales[c];
+        if (x_scales) v *= x_scales[t];
+        const int64_t yi = y_index(geo, t, c);
+        if (y_dtype == AQ_F32) static_cast<float*>(Y)[yi] = v;
+        else static_cast<uint16_t*>(Y)[yi] = f32_to_f16(v);
+    }
+}
+
+template <int XT, typename CodeT, int MC, int NW, int TM>
+static hipError_t f32_launch_cfg(const Geom& geo, const DeviceWeights& w, const void* X, const float* x_scales,
+                                 void* Y, int y_dtype, hipStream_t st) {
+    auto kern = f32_fwd_kernel<XT, CodeT, MC, NW, TM>;
+    const int64_t tm = (geo.tokens + kF32Tile * TM - 1) / (kF32Tile * TM);
+    const int tn = (geo.C_out + kF32Tile - 1) / kF32Tile;
+    if (tm * tn >= (int64_t(1) << 31)) return hipErrorInvalidConfiguration;
+    const size_t part = (size_t)NW * TM * kF32Tile * kF32Pitch * sizeof(float);
+    const size_t lds = std::max(part, MC > 0 ? ((size_t)geo.M << geo.B) * 8 * sizeof(float) : size_t(0));
+    const hipError_t e = ensure_dynamic_lds((const void*)kern, lds);
+    if (e != hipSuccess) return e;
+    const void* codes = MC > 0 ? static_cast<const void*>(w.codes_lut) : w.codes;
+    kern<<<(unsigned)(tm * tn), 64 * NW, lds, st>>>(geo, w.cb32, static_cast<const CodeT*>(codes), w.scales, X,
+                                                    x_scales, Y, y_dtype, tn);
+    note_launch(st, "f32_fwd_kernel", {XT, 8 * (int)sizeof(CodeT), MC, NW, TM});
+    return hipGetLastError();
+}
+
+// Waves per tile and tile height: 32-token tiles while those leave compute
+// units idle, with four waves where K is at most four chunks, else sixteen;
+// else 64-token tiles, which decode half as often.
+template <int XT, typename CodeT, int MC>
+static hipError_t f32_launch_mode(const Geom& geo, const DeviceWeights& w, const void* X, const float* x_scales,
+                                  void* Y, int y_dtype, hipStream_t st) {
+    const int64_t tiles = ((geo.tokens + kF32Tile - 1) / kF32Tile) * ((geo.C_out + kF32Tile - 1) / kF32Tile);
+    if (tiles > 256) return f32_launch_cfg<XT, CodeT, MC, 4, 2>(geo, w, X, x_scales, Y, y_dtype, st);
+    if (geo.K * std::max(1, MC) <= 512) return f32_launch_cfg<XT, CodeT, MC, 4, 1>(geo, w, X, x_scales, Y, y_dtype, st);
+    return f32_launch_cfg<XT, CodeT, MC, 16, 1>(geo, w, X, x_scales, Y, y_dtype, st);
+}
+
+template <int XT, typename CodeT>
+static hipError_t f32_launch_x(const Geom& geo, const DeviceWeights& w, const void* X, const float* x_scales, void* Y,
+                               int y_dtype, hipStream_t st) {
+    if (geo.g != 8) return f32_launch_mode<XT, CodeT, kF32AnyG>(geo, w, X, x_scales, Y, y_dtype, st);
+    if constexpr (sizeof(CodeT) == 1 && XT == AQ_F32) {
+        // chunks of 16 code bytes per channel (the table path's code layout for these M)
+        if (w.codes_lut && geo.M == 1) return f32_launch_mode<XT, CodeT, 1>(geo, w, X, x_scales, Y, y_dtype, st);
+        if (w.codes_lut && geo.M == 2) return f32_launch_mode<XT, CodeT, 2>(geo, w, X, x_scales, Y, y_dtype, st);
+        if (w.codes_lut && geo.M == 4) return f32_launch_mode<XT, CodeT, 4>(geo, w, X, x_scales, Y, y_dtype, st);
+    }
+    return f32_launch_mode<XT, CodeT, kF32G8>(geo, w, X, x_scales, Y, y_dtype, st);
 }
 
 template <typename CodeT>
 static hipError_t f32_launch_codes(const Geom& geo, const DeviceWeights& w, const void* X, int x_dtype,
                                    const float* x_scales, void* Y, int y_dtype, hipStream_t st) {
-    const dim3 grid((unsigned)((geo.tokens + kF32BM - 1) / kF32BM), (unsigned)((geo.C_out + kF32BN - 1) / kF32BN));
-    const CodeT* codes = static_cast<const CodeT*>(w.codes);
     switch (x_dtype) {
-    case AQ_F32: f32_fwd_kernel<AQ_F32, CodeT><<<grid, 256, 0, st>>>(geo, w.cb32, codes, w.scales, X, x_scales, Y, y_dtype); break;
-    case AQ_F16: f32_fwd_kernel<AQ_F16, CodeT><<<grid, 256, 0, st>>>(geo, w.cb32, codes, w.scales, X, x_scales, Y, y_dtype); break;
-    case AQ_BF16: f32_fwd_kernel<AQ_BF16, CodeT><<<grid, 256, 0, st>>>(geo, w.cb32, codes, w.scales, X, x_scales, Y, y_dtype); break;
-    default: f32_fwd_kernel<AQ_I8, CodeT><<<grid, 256, 0, st>>>(geo, w.cb32, codes, w.scales, X, x_scales, Y, y_dtype); break;
+    case AQ_F32: return f32_launch_x<AQ_F32, CodeT>(geo, w, X, x_scales, Y, y_dtype, st);
+    case AQ_F16: return f32_launch_x<AQ_F16, CodeT>(geo, w, X, x_scales, Y, y_dtype, st);
+    case AQ_BF16: return f32_launch_x<AQ_BF16, CodeT>(geo, w, X, x_scales, Y, y_dtype, st);
+    default: return f32_launch_x<AQ_I8, CodeT>(geo, w, X, x_scales, Y, y_dtype, st);
     }
-    note_launch(st, "f32_fwd_kernel", {x_dtype, 8 * (int)sizeof(CodeT)});
-    return hipGetLastError();
 }
 
 hipError_t launch_f32_forward(const Geom& geo, const DeviceWeights& w, const void* X, int x_dtype,

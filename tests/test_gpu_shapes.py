@@ -141,3 +141,56 @@ def test_bf16_linear(spec, weights):
     assert torch.all((y.double() - ref).abs() <= bound)
     assert torch.all((y.double() - y_gen.double()).abs() <= 2 * bound)
     layer.close()
+
+
+def _f32(name, n, K, C_out, g=8, M=2, B=8, x="f32", conv=None, y="f32"):
+    return LayerSpec(name=name, C_out=C_out, K=K, g=g, M=M, B=B, n=n, codebook_dtype="f32", x_dtype=x, y_dtype=y,
+                     tile_dtype="f32", conv=conv)
+
+
+F32 = [
+    _f32("s_1", 1, 8, 1),                                     # one step, one output
+    _f32("s_k24", 33, 24, 33),                                # fewer steps than waves
+    _f32("s_k264", 70, 264, 40, M=3, B=5),                    # a last wave with fewer steps
+    _f32("s_g3", 40, 27, 50, g=3),                            # groups across lanes, rows not 16-byte multiples
+    _f32("s_g16", 20, 48, 30, g=16, M=1, B=12),               # 16-bit codes
+    _f32("s_wide", 600, 200, 500, M=4),                       # four waves per tile
+    _f32("s_wide_g9", 520, 90, 512, g=9, B=6),
+    _f32("s_i8", 50, 64, 40, x="i8", y="f16"),
+    _f32("s_bf16", 50, 64, 40, x="bf16"),
+    _f32("s_conv", 2, 12 * 9, 36, g=4, conv=ConvGeom(12, 3, 3, 2, 1, 9, 7)),
+]
+
+
+@pytest.mark.parametrize("spec", F32, ids=lambda s: s.name)
+def test_f32_kernel(spec):
+    """fp32 layers against the oracle on every output: 1e-5 (fp32 output) and the rounding bound."""
+    import paper_2506_05960_amd as P
+    inp = generate(spec, 7201)
+    layer = P.AQLayer(spec, inp)
+    layer.set_path("decode")
+    x = torch.from_numpy(inp["x"].view(np.int16) if spec.x_dtype == "bf16" else inp["x"]).cuda()
+    xs = None if inp["x_scales"] is None else torch.from_numpy(inp["x_scales"]).cuda()
+    y, y2 = layer.forward(x, xs), layer.forward(x, xs)
+    print(spec.name, layer.last_launches(), flush=True)
+    assert torch.equal(y, y2)
+    layer.close()
+    tok, ch = np.arange(spec.tokens), np.arange(spec.C_out)
+    check_against_oracle(spec, inp, sampled_outputs(spec, y.double().cpu().numpy(), tok, ch), tok, ch, "decode",
+                         1e-5 if spec.y_dtype == "f32" else TOL)
+
+
+def test_f32_infinite_codeword():
+    """A codeword that no code of a row selects does not reach that row, whatever steps its waves share."""
+    import paper_2506_05960_amd as P
+    spec = _f32("s_inf", 5, 24, 40, M=1, B=2)
+    inp = generate(spec, 7202)
+    inp["codebooks"][0, 3] = np.inf
+    inp["codes"][:, :, 0] = inp["codes"][:, :, 0] % 3
+    inp["codes"][7, 2, 0] = 3
+    layer = P.AQLayer(spec, inp)
+    layer.set_path("decode")
+    inp["x"][:, 16:] = np.abs(inp["x"][:, 16:])
+    y = layer.forward(torch.from_numpy(inp["x"]).cuda()).cpu().numpy()
+    layer.close()
+    assert np.all(np.isposinf(y[:, 7])) and np.all(np.isfinite(np.delete(y, 7, axis=1)))
