@@ -16,6 +16,7 @@
 //      the kernel sums their s-scaled gradient groups over all splits in a
 //      fixed order.  No atomics: repeated calls give identical bits.
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -28,6 +29,11 @@ namespace {
 
 constexpr int kGradChunk = 64;   // tokens per chunk: four 16-deep MFMA steps
 constexpr int kGradPitch = 72;   // halves per LDS row: 64 tokens plus 8 padding halves
+// LDS stages of the direct-to-LDS convolution kernel: three let three four-wave
+// workgroups share a CU (8 x 8 images, 960 -> 960: 104 against 120 us with
+// four); an eight-wave workgroup has its CU to itself, where the chunks in
+// flight over the memory latency are what bounds it, and takes eight.
+constexpr int conv_stages(int halves) { return halves == 2 ? 8 : 3; }
 
 struct GradArgs {
     const uint16_t* X;
@@ -300,6 +306,17 @@ __device__ __forceinline__ u32x4 shift_down(const u32x4& v, uint32_t nb) {
                  __builtin_amdgcn_alignbyte(v[2], v[1], 2), __builtin_amdgcn_alignbyte(v[3], v[2], 2)};
 }
 
+// Wait until at most `after` (<= N) chunks of L loads each are outstanding.
+template <int N, int L>
+__device__ __forceinline__ void wait_chunks(int after) {
+    if constexpr (N == 0) {
+        wait_vmcnt<0>();
+    } else {
+        if (after >= N) wait_vmcnt<N * L>();
+        else wait_chunks<N - 1, L>(after);
+    }
+}
+
 // Convolution weight gradient with both operands streamed into LDS by
 // direct-to-LDS loads.  Needs stride 1, same padding, OW dividing 64 and
 // OH * OW a multiple of 64, so that a 64-token chunk is whole output rows of
@@ -312,19 +329,29 @@ __device__ __forceinline__ u32x4 shift_down(const u32x4& v, uint32_t nb) {
 // (c, r) -- and the q variants of every dY fragment are built in registers
 // from the fragment and its two neighbouring values.  Rows are 128 bytes with
 // the 16-byte pieces XOR-swizzled by the row index (conflict-free fragment
-// reads); three stages keep two chunks of loads in flight.
-template <int KIND, int DT, int BM, int BNP>
-__global__ void __launch_bounds__(256, 2) wgrad_conv_dma_kernel(Geom geo, GradArgs ga, const uint8_t* zero) {
+// reads); three or four stages keep all but one chunk of them in flight.
+//
+// TH = 2: eight waves, the second four taking the second half of every chunk's
+// tokens; the two partial tiles meet in LDS.  A layer with few tiles then puts
+// the same number of waves on the chip with half the token splits, whose fp32
+// partials (C_out x K each) are written and read back through memory.
+//
+// The tile leaves through LDS as whole rows of KQ BNP consecutive columns: the
+// lane layout's own stores are 4 bytes wide and KQ columns apart.  2 images of
+// 64 x 64, 192 -> 192: 23.9 -> 20.8 us, the whole gradient 28.2 -> 24.0 us.
+template <int KIND, int DT, int BM, int BNP, int TH>
+__global__ void __launch_bounds__(256 * TH, 2) wgrad_conv_dma_kernel(Geom geo, GradArgs ga, const uint8_t* zero) {
     constexpr int KQ = KIND == 1 ? 3 : 1;        // kernel columns: variants of dY
     constexpr int KR = KIND == 1 ? 3 : 1;        // kernel rows
     constexpr int PAD = KIND == 1 ? 1 : 0;
     constexpr int WM = BM / 2, WN = BNP / 2, AM = WM / 32, AN = WN / 32;
     constexpr int ROWS = BM + BNP;
     constexpr int STAGE = ROWS * 128;
-    constexpr int NST = 3;
-    constexpr int LOADS = ROWS / 32;             // 16-byte loads per thread per chunk
-    static_assert(ROWS % 32 == 0, "rows per stage");
-    __shared__ __attribute__((aligned(16))) uint8_t lds[NST * STAGE];
+    constexpr int NST = conv_stages(TH);
+    constexpr int NW = 4 * TH;
+    constexpr int LOADS = ROWS / (8 * NW);       // 16-byte loads per thread per chunk
+    static_assert(ROWS % (8 * NW) == 0, "rows per stage");
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
     const int total = ga.S * ga.tiles_m * ga.tiles_n;
     const int per_xcd = (total + 7) / 8;
@@ -337,49 +364,74 @@ __global__ void __launch_bounds__(256, 2) wgrad_conv_dma_kernel(Geom geo, GradAr
     const int c_beg = z * ga.cps, c_end = min(ga.nchunk, c_beg + ga.cps);
     const int nch = max(0, c_end - c_beg);
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int th = TH == 2 ? wave >> 2 : 0;      // the wave's token half
+    const int wm = (wave >> 1) & 1, wn = wave & 1;
     const int l32 = lane & 31, hi = lane >> 5;
     const int P = geo.OH * geo.OW;
     const int npairs = geo.cin * KR;
     const uint8_t* dyb = reinterpret_cast<const uint8_t*>(ga.dY);
     const uint8_t* xb = reinterpret_cast<const uint8_t*>(ga.X);
 
-    // this lane's slot in every load: row (8 g + lane / 8), logical piece pc
+    // this lane's slot in every load: row (8 g + lane / 8), logical piece pc.
+    // With same padding and stride 1 a chunk's rows of dY and of X both start
+    // at the chunk's position in their image, so a load's address is a fixed
+    // per-lane part plus a uniform part; only the kernel rows' image borders
+    // are checked per chunk.
     const int lrow = lane >> 3;
     const int lpc = (lane & 7) ^ lrow;
-    auto issue = [&](int chunk, uint8_t* st) {
-        const int n0 = chunk * 64;
-        const int b = n0 / P;
-        const int pb = n0 - b * P;
+    const uint8_t* base[LOADS];
+    int rel[LOADS];              // X: input row relative to the chunk's first output row
+    {
         const int t = 8 * lpc;                   // token of the piece within the chunk
-        const int oh = pb / geo.OW + t / geo.OW, ow = t % geo.OW;
+        const int trow = t / geo.OW, ow = t - trow * geo.OW;
 #pragma unroll
         for (int j = 0; j < LOADS; ++j) {
-            const int grp = wave + 4 * j;
+            const int grp = wave + NW * j;
             const int row = 8 * grp + lrow;
-            const uint8_t* src = zero;
             if (8 * grp < BM) {
                 const int i = i0 + row;
-                if (i < geo.C_out) src = dyb + ((int64_t)(b * geo.C_out + i) * P + pb + t) * 2;
+                rel[j] = 0;
+                base[j] = i < geo.C_out ? dyb + ((int64_t)i * P + t) * 2 : nullptr;
             } else {
                 const int pr = p0 + row - BM;
                 const int c = pr / KR, r = pr - c * KR;
-                const int ih = oh + r - PAD;
-                if (pr < npairs && ih >= 0 && ih < geo.H)
-                    src = xb + ((int64_t)(b * geo.cin + c) * geo.H * geo.W + ih * geo.W + ow) * 2;
+                rel[j] = trow + r - PAD;
+                base[j] = pr < npairs ? xb + ((int64_t)c * geo.H * geo.W + (int64_t)rel[j] * geo.W + ow) * 2 : nullptr;
             }
-            lds_dma16(src, st + grp * 1024);
+        }
+    }
+    // position of the next chunk to load: image, first token and output row in it
+    int nb = c_beg * 64 / P, np = c_beg * 64 - nb * P, nrow = np / geo.OW;
+    const int rows_per_chunk = 64 / geo.OW;
+    auto issue = [&](uint8_t* st) {
+        const int64_t ofs_y = ((int64_t)nb * geo.C_out * P + np) * 2;
+        const int64_t ofs_x = ((int64_t)nb * geo.cin * P + np) * 2;
+#pragma unroll
+        for (int j = 0; j < LOADS; ++j) {
+            const int grp = wave + NW * j;
+            const bool is_y = 8 * grp < BM;
+            const bool ok = base[j] != nullptr && (is_y || (unsigned)(nrow + rel[j]) < (unsigned)geo.H);
+            lds_dma16(ok ? base[j] + (is_y ? ofs_y : ofs_x) : zero, st + grp * 1024);
+        }
+        np += 64;
+        nrow += rows_per_chunk;
+        if (np == P) {
+            np = 0;
+            nrow = 0;
+            ++nb;
         }
     };
 
     // neighbour masks: the piece starts (ends) an output row
-    bool lft_ok[4], rgt_ok[4];
+    constexpr int SW = 4 / TH;                   // steps of a wave per chunk
+    uint32_t lft_ok[SW], rgt_ok[SW];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const int pc = 2 * s + hi;
-        lft_ok[s] = (8 * pc) % geo.OW != 0;
-        rgt_ok[s] = (8 * pc + 8) % geo.OW != 0;
+    for (int s = 0; s < SW; ++s) {
+        const int pc = 2 * (s + SW * th) + hi;
+        lft_ok[s] = (8 * pc) % geo.OW != 0 ? 0xFFFFu : 0u;
+        rgt_ok[s] = (8 * pc + 8) % geo.OW != 0 ? 0xFFFFu : 0u;
     }
 
     floatx16 acc[KQ][AM][AN];
@@ -394,31 +446,37 @@ __global__ void __launch_bounds__(256, 2) wgrad_conv_dma_kernel(Geom geo, GradAr
 
     auto compute = [&](const uint8_t* st) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int pc = 2 * s + hi;
-            u32x4 av[KQ][AM], bf[AN];
+        for (int s = 0; s < SW; ++s) {
+            const int pc = 2 * (s + SW * th) + hi;
+            u32x4 v[AM], bf[AN];
+            uint32_t left[AM], right[AM];
+            // every read is unconditional (the pieces wrap within the row): a read
+            // under a lane mask becomes a branch that waits for all before it
 #pragma unroll
             for (int a = 0; a < AM; ++a) {
                 const int row = WM * wm + 32 * a + l32;
                 const uint8_t* rp = st + row * 128;
-                const u32x4 v = *reinterpret_cast<const u32x4*>(rp + ((pc ^ (row & 7)) << 4));
+                v[a] = *reinterpret_cast<const u32x4*>(rp + ((pc ^ (row & 7)) << 4));
                 if constexpr (KQ == 3) {
-                    const uint32_t left = lft_ok[s] ? *reinterpret_cast<const uint16_t*>(
-                                                          rp + ((((pc - 1) & 7) ^ (row & 7)) << 4) + 14)
-                                                    : 0u;
-                    const uint32_t right =
-                        rgt_ok[s] ? *reinterpret_cast<const uint16_t*>(rp + ((((pc + 1) & 7) ^ (row & 7)) << 4)) : 0u;
-                    av[0][a] = shift_up(v, right);     // q = 0: dY[m + 1]
-                    av[1][a] = v;                      // q = 1
-                    av[2][a] = shift_down(v, left);    // q = 2: dY[m - 1]
-                } else {
-                    av[0][a] = v;
+                    left[a] = *reinterpret_cast<const uint32_t*>(rp + ((((pc - 1) & 7) ^ (row & 7)) << 4) + 12);
+                    right[a] = *reinterpret_cast<const uint32_t*>(rp + ((((pc + 1) & 7) ^ (row & 7)) << 4));
                 }
             }
 #pragma unroll
             for (int b = 0; b < AN; ++b) {
                 const int row = BM + WN * wn + 32 * b + l32;
                 bf[b] = *reinterpret_cast<const u32x4*>(st + row * 128 + ((pc ^ (row & 7)) << 4));
+            }
+            u32x4 av[KQ][AM];
+#pragma unroll
+            for (int a = 0; a < AM; ++a) {
+                if constexpr (KQ == 3) {
+                    av[0][a] = shift_up(v[a], right[a] & rgt_ok[s]);              // q = 0: dY[m + 1]
+                    av[1][a] = v[a];                                              // q = 1
+                    av[2][a] = shift_down(v[a], (left[a] >> 16) & lft_ok[s]);     // q = 2: dY[m - 1]
+                } else {
+                    av[0][a] = v[a];
+                }
             }
 #pragma unroll
             for (int q = 0; q < KQ; ++q)
@@ -429,36 +487,72 @@ __global__ void __launch_bounds__(256, 2) wgrad_conv_dma_kernel(Geom geo, GradAr
         }
     };
 
+    // NST - 1 chunks in flight; before chunk t + 1 is read, at most the loads of
+    // the chunks after it may be outstanding
     auto stg = [&](int c) { return lds + (c % NST) * STAGE; };
-    if (nch > 0) issue(c_beg, stg(0));
-    if (nch > 1) issue(c_beg + 1, stg(1));
-    if (nch > 1) wait_vmcnt<LOADS>();
-    else wait_vmcnt<0>();
+    auto landed = [&](int after) { wait_chunks<NST - 2, LOADS>(after); };   // `after` chunks issued after the one awaited
+#pragma unroll
+    for (int c = 0; c < NST - 1; ++c)
+        if (c < nch) issue(stg(c));
+    landed(min(nch, NST - 1) - 1);
     lds_barrier();
     for (int t = 0; t < nch; ++t) {
-        if (t + 2 < nch) issue(c_beg + t + 2, stg(t + 2));
+        if (t + NST - 1 < nch) issue(stg(t + NST - 1));
         compute(stg(t));
-        if (t + 2 < nch) wait_vmcnt<LOADS>();    // chunk t + 1 landed
-        else wait_vmcnt<0>();
+        landed(min(nch - 1, t + NST - 1) - (t + 1));
         lds_barrier();
     }
 
-    float* Pz = ga.P + (int64_t)z * geo.C_out * geo.K;
+    // ---- epilogue: the tile as rows of KQ BNP columns in LDS (the stages are
+    // free after the last barrier), then s[i] times whole 16-byte row pieces ----
+    constexpr int COLS = KQ * BNP, PITCH = COLS + 4;
+    constexpr int NP = BM * (COLS / 4) / (64 * NW);           // 16-byte pieces per thread
+    static_assert(NP * 64 * NW == BM * (COLS / 4), "pieces per thread");
+    float* out = reinterpret_cast<float*>(lds);
+    // every scale of this thread's pieces is loaded before the first is needed
+    const __amdgpu_buffer_rsrc_t sr = buffer_rsrc(ga.scales, (uint64_t)geo.C_out * 4u);
+    float sc[NP];
 #pragma unroll
-    for (int a = 0; a < AM; ++a)
+    for (int e = 0; e < NP; ++e)
+        sc[e] = __uint_as_float(
+            __builtin_amdgcn_raw_buffer_load_b32(sr, (uint32_t)(i0 + (tid + 64 * NW * e) / (COLS / 4)) * 4u, 0, 0));
 #pragma unroll
-        for (int b = 0; b < AN; ++b) {
-            const int pr = p0 + WN * wn + 32 * b + l32;
+    for (int h = 0; h < TH; ++h) {
+        if (th == h) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int i = i0 + WM * wm + 32 * a + 8 * (r >> 2) + 4 * hi + (r & 3);
-                if (i < geo.C_out && pr < npairs) {
-                    const float sc = ga.scales[i];
+            for (int a = 0; a < AM; ++a)
 #pragma unroll
-                    for (int q = 0; q < KQ; ++q) Pz[(int64_t)i * geo.K + pr * KQ + q] = sc * acc[q][a][b][r];
-                }
-            }
+                for (int b = 0; b < AN; ++b)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int row = WM * wm + 32 * a + 8 * (r >> 2) + 4 * hi + (r & 3);
+                        float* o = out + row * PITCH + (WN * wn + 32 * b + l32) * KQ;
+#pragma unroll
+                        for (int q = 0; q < KQ; ++q) o[q] = h == 0 ? acc[q][a][b][r] : o[q] + acc[q][a][b][r];
+                    }
         }
+        __syncthreads();
+    }
+    float* Pz = ga.P + (int64_t)z * geo.C_out * geo.K;
+    const int k0 = p0 * KQ;
+    if (geo.K % 4 == 0) {
+#pragma unroll
+        for (int e = 0; e < NP; ++e) {
+            const int p = tid + 64 * NW * e;
+            const int row = p / (COLS / 4), c4 = 4 * (p % (COLS / 4));
+            const int i = i0 + row;
+            floatx4 v = *reinterpret_cast<const floatx4*>(out + row * PITCH + c4);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = sc[e] * v[u];
+            if (i < geo.C_out && k0 + c4 < geo.K) *reinterpret_cast<floatx4*>(Pz + (int64_t)i * geo.K + k0 + c4) = v;
+        }
+    } else {
+        for (int e = tid; e < BM * COLS; e += 64 * NW) {
+            const int row = e / COLS, c = e % COLS;
+            const int i = i0 + row;
+            if (i < geo.C_out && k0 + c < geo.K) Pz[(int64_t)i * geo.K + k0 + c] = ga.scales[i] * out[row * PITCH + c];
+        }
+    }
 }
 
 // Linear weight gradient with both operands streamed into LDS by
@@ -598,6 +692,209 @@ __global__ void __launch_bounds__(256, 2) wgrad_linear_dma_kernel(Geom geo, Grad
     }
 }
 
+// The same for layers with enough channels and inputs: a 128 x 192 tile, whose
+// bytes brought into LDS feed 77 FLOP each (32 for the 64 x 64 tile, which the
+// path from L2 to LDS bounds), held as 64-wide panels of the layout above.
+// Eight waves: four cover the tile with 64 x 96 each (2 x 3 blocks: five
+// fragments for six products), the other four do the same over the second half
+// of every chunk's tokens, so that two waves per SIMD cover each other's LDS
+// waits with one partial tile per workgroup.  The chunks pass through registers
+// (two chunks in flight, loads past the data return zeros): direct-to-LDS
+// loads would make the compiler drain them before every transpose read, or the
+// reads opaque to its scheduler.  The halves' accumulators meet in LDS: each
+// half adds and stores every other block.  8192 tokens, 576 -> 1728, bf16: 50.5
+// us with the 64 x 64 tile (4 splits), 25.8 with this one (6 splits); the whole
+// gradient 57.0 -> 37.2 us.
+constexpr int kWideM = 128, kWideN = 192;
+constexpr int kWideStage = (kWideM + kWideN) / 64 * 8192;
+
+typedef short short4v __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ u32x2 tr_read(const uint8_t* p) {
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                         (__attribute__((address_space(3))) short4v*)(uint32_t)(uintptr_t)(
+                                             const __attribute__((address_space(3))) uint8_t*)p));
+}
+
+template <int DT>
+__global__ void __launch_bounds__(512, 2) wgrad_linear_wide_kernel(Geom geo, GradArgs ga) {
+    constexpr int AM = 2, AN = 3, PA = kWideM / 64, PB = kWideN / 64;
+    constexpr int LOADS = PA + PB;               // 16-byte loads per thread per chunk, one per panel
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+
+    const int total = ga.S * ga.tiles_m * ga.tiles_n;
+    const int per_xcd = (total + 7) / 8;
+    const int w = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
+    if (w >= total) return;
+    const int tn = w % ga.tiles_n;
+    const int tm = (w / ga.tiles_n) % ga.tiles_m;
+    const int z = w / (ga.tiles_n * ga.tiles_m);
+    const int i0 = tm * kWideM, k0 = tn * kWideN;
+    const int c_beg = z * ga.cps, c_end = min(ga.nchunk, c_beg + ga.cps);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int th = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+    const int l32 = lane & 31, hi = lane >> 5;
+
+    // this thread's piece of every panel: token row 8 wave + lane / 8, slot lane % 8
+    // (X and dY are below 2 GiB, so byte offsets fit 32 bits; rows past the last
+    // token lie past the buffer and read zeros)
+    const int row = 8 * wave + (lane >> 3);
+    const int pc = (lane & 7) ^ lin_swz(row);
+    const __amdgpu_buffer_rsrc_t ry = buffer_rsrc(ga.dY, (uint64_t)geo.tokens * geo.C_out * 2);
+    const __amdgpu_buffer_rsrc_t rx = buffer_rsrc(ga.X, (uint64_t)geo.tokens * geo.K * 2);
+    const uint32_t step_y = 128u * (uint32_t)geo.C_out, step_x = 128u * (uint32_t)geo.K;
+    uint32_t off[LOADS];                         // next chunk's byte offset, bit 31 set where there is no column
+    uint32_t none[LOADS];
+#pragma unroll
+    for (int j = 0; j < LOADS; ++j) {
+        const int len = j < PA ? geo.C_out : geo.K;
+        const int col = (j < PA ? i0 + 64 * j : k0 + 64 * (j - PA)) + 8 * pc;
+        none[j] = col < len ? 0u : kOutOfRange;
+        off[j] = ((uint32_t)(c_beg * 64 + row) * (uint32_t)len + (uint32_t)(col < len ? col : 0)) * 2u;
+    }
+    int c_next = c_beg;                          // the chunk the next load fetches
+    auto load = [&](u32x4 (&r)[LOADS]) {
+        // whole chunks past the split or the data: out of range (a row offset may pass 2^32 there)
+        const uint32_t past = c_next < c_end ? 0u : kOutOfRange;
+        const bool rok = (int64_t)c_next * 64 + row < geo.tokens;
+#pragma unroll
+        for (int j = 0; j < LOADS; ++j) {
+            const uint32_t o = rok ? off[j] | none[j] | past : kOutOfRange;
+            r[j] = j < PA ? __builtin_amdgcn_raw_buffer_load_b128(ry, o, 0, 0)
+                          : __builtin_amdgcn_raw_buffer_load_b128(rx, o, 0, 0);
+            off[j] += j < PA ? step_y : step_x;
+        }
+        ++c_next;
+    };
+    auto store = [&](uint8_t* st, const u32x4 (&r)[LOADS]) {
+#pragma unroll
+        for (int j = 0; j < LOADS; ++j) *reinterpret_cast<u32x4*>(st + j * 8192 + wave * 1024 + lane * 16) = r[j];
+    };
+
+    // transpose-read addresses (bytes within a stage) of this lane for step 2 th:
+    // channels 16 (g16 % 2) + 4 qo of a block at token 8 (g16 / 2) + fo; the
+    // swizzle depends on fo alone
+    const int g16 = lane >> 4, j16 = lane & 15;
+    const int fo = j16 >> 2, qo = j16 & 3;
+    const int n_l = 32 * th + 8 * (g16 >> 1) + fo;
+    auto block_off = [&](int panel0, int blk) {
+        const int c = 32 * (blk & 1) + 16 * (g16 & 1) + 4 * qo;
+        return (uint32_t)((panel0 + (blk >> 1)) * 8192 + n_l * 128 + (((c >> 3) ^ lin_swz(fo)) << 4) + (c & 7) * 2);
+    };
+    uint32_t offa[AM], offb[AN];
+#pragma unroll
+    for (int a = 0; a < AM; ++a) offa[a] = block_off(0, AM * wm + a);
+#pragma unroll
+    for (int b = 0; b < AN; ++b) offb[b] = block_off(PA, AN * wn + b);
+
+    floatx16 acc[AM][AN];
+#pragma unroll
+    for (int a = 0; a < AM; ++a)
+#pragma unroll
+        for (int b = 0; b < AN; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
+
+    // the half's two 16-token steps: every fragment of both is read before the first product
+    auto compute = [&](const uint8_t* st) {
+        u32x4 av[2][AM], bv[2][AN];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+#pragma unroll
+            for (int a = 0; a < AM; ++a) {
+                const u32x2 lo = tr_read(st + offa[a] + s * 2048), h4 = tr_read(st + offa[a] + s * 2048 + 512);
+                av[s][a] = u32x4{lo[0], lo[1], h4[0], h4[1]};
+            }
+#pragma unroll
+            for (int b = 0; b < AN; ++b) {
+                const u32x2 lo = tr_read(st + offb[b] + s * 2048), h4 = tr_read(st + offb[b] + s * 2048 + 512);
+                bv[s][b] = u32x4{lo[0], lo[1], h4[0], h4[1]};
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int b = 0; b < AN; ++b)
+#pragma unroll
+                for (int a = 0; a < AM; ++a) acc[a][b] = mfma_grad<DT>(av[s][a], bv[s][b], acc[a][b]);
+    };
+
+    // chunk c computes from stage (c - c_beg) % 2 while one register set holds
+    // chunk c + 1 and the other receives chunk c + 2
+    u32x4 ra[LOADS], rb[LOADS];
+    uint8_t* st0 = lds;
+    uint8_t* st1 = lds + kWideStage;
+    load(ra);
+    store(st0, ra);
+    load(ra);
+    lds_barrier();
+    int c = c_beg;
+    while (true) {
+        load(rb);
+        compute(st0);
+        store(st1, ra);                          // past the end: zeros, never read
+        lds_barrier();
+        if (++c >= c_end) break;
+        load(ra);
+        compute(st1);
+        store(st0, rb);
+        lds_barrier();
+        if (++c >= c_end) break;
+    }
+
+    // ---- epilogue: half h stores the blocks with (3 a + b) % 2 == h; the other
+    // half's accumulators of them come through LDS.  Scales (whole quads: C_out
+    // is a multiple of 8) are loaded before the exchange; stores outside the
+    // matrix go to an offset past the slice. ----
+    const __amdgpu_buffer_rsrc_t sr = buffer_rsrc(ga.scales, (uint64_t)geo.C_out * 4u);
+    const __amdgpu_buffer_rsrc_t pr =
+        buffer_rsrc(ga.P + (int64_t)z * geo.C_out * geo.K, (uint64_t)geo.C_out * geo.K * 4u);
+    u32x4 sc[AM][4];
+#pragma unroll
+    for (int a = 0; a < AM; ++a)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            sc[a][i] = __builtin_amdgcn_raw_buffer_load_b128(sr, (uint32_t)(i0 + 32 * (AM * wm + a) + 8 * i + 4 * hi) * 4u, 0, 0);
+    floatx4* red = reinterpret_cast<floatx4*>(lds);           // [wave][3 blocks][4][64], past the last barrier
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (th != h) continue;
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            const int blk = 2 * e + 1 - h;                    // the other half's blocks
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                red[((wave * 3 + e) * 4 + i) * 64 + lane] =
+                    floatx4{acc[blk / 3][blk % 3][4 * i], acc[blk / 3][blk % 3][4 * i + 1],
+                            acc[blk / 3][blk % 3][4 * i + 2], acc[blk / 3][blk % 3][4 * i + 3]};
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (th != h) continue;
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            const int blk = 2 * e + h, a = blk / 3, b = blk % 3;
+            const int k = k0 + 32 * (AN * wn + b) + l32;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const floatx4 o = red[(((wave ^ 4) * 3 + e) * 4 + i) * 64 + lane];
+                const int r0 = i0 + 32 * (AM * wm + a) + 8 * i + 4 * hi;
+                const bool ok = r0 < geo.C_out && k < geo.K;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float v = h == 0 ? acc[a][b][4 * i + u] + o[u] : o[u] + acc[a][b][4 * i + u];
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(__uint_as_float(sc[a][i][u]) * v), pr,
+                                                          ok ? (uint32_t)((r0 + u) * geo.K + k) * 4u : kOutOfRange, 0, 0);
+                }
+            }
+        }
+    }
+}
+
 // One group of LPB lanes per codebook entry (m, k); lanes split into
 // LPB / g entry slots times g positions t.  Each slot sums its entries in
 // list order, then lane t adds the slots in order.
@@ -693,21 +990,40 @@ hipError_t wgrad_launch(const Geom& geo, const GradArgs& ga, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <int KIND, int DT, int BM, int BNP>
+template <int KIND, int DT, int BM, int BNP, int TH>
 hipError_t wgrad_dma_launch(const Geom& geo, const GradArgs& ga, const uint8_t* zero, hipStream_t st) {
+    auto kern = wgrad_conv_dma_kernel<KIND, DT, BM, BNP, TH>;
     const int total = ga.S * ga.tiles_m * ga.tiles_n;
     const unsigned grid = (unsigned)(8 * ((total + 7) / 8));
-    wgrad_conv_dma_kernel<KIND, DT, BM, BNP><<<grid, 256, 0, st>>>(geo, ga, zero);
-    note_launch(st, "wgrad_conv_dma_kernel", {KIND, DT, BM, BNP});
+    const size_t lds = std::max<size_t>((size_t)conv_stages(TH) * (BM + BNP) * 128,
+                                        (size_t)BM * ((KIND == 1 ? 3 : 1) * BNP + 4) * sizeof(float));
+    const hipError_t e = ensure_dynamic_lds((const void*)kern, lds);
+    if (e != hipSuccess) return e;
+    kern<<<grid, 256 * TH, lds, st>>>(geo, ga, zero);
+    note_launch(st, "wgrad_conv_dma_kernel", {KIND, DT, BM, BNP, TH});
     return hipGetLastError();
 }
 
 template <int KIND, int DT>
 hipError_t wgrad_dma_dispatch(const Geom& geo, const GradPlan& gp, const GradArgs& ga, const uint8_t* zero,
                               hipStream_t st) {
-    if (gp.bm == 128 && gp.bn == 64) return wgrad_dma_launch<KIND, DT, 128, 64>(geo, ga, zero, st);
-    if (gp.bm == 64 && gp.bn == 64) return wgrad_dma_launch<KIND, DT, 64, 64>(geo, ga, zero, st);
+    if (gp.bm == 128 && gp.bn == 64) return wgrad_dma_launch<KIND, DT, 128, 64, 1>(geo, ga, zero, st);
+    if (gp.bm == 64 && gp.bn == 64)
+        return gp.halves == 2 ? wgrad_dma_launch<KIND, DT, 64, 64, 2>(geo, ga, zero, st)
+                              : wgrad_dma_launch<KIND, DT, 64, 64, 1>(geo, ga, zero, st);
     return hipErrorInvalidConfiguration;
+}
+
+template <int DT>
+hipError_t wgrad_wide_launch(const Geom& geo, const GradArgs& ga, hipStream_t st) {
+    auto kern = wgrad_linear_wide_kernel<DT>;
+    const unsigned grid = (unsigned)(8 * ((ga.S * ga.tiles_m * ga.tiles_n + 7) / 8));
+    const size_t lds = std::max<size_t>(2 * kWideStage, 8 * 3 * 4 * 64 * 16);   // two stages, or the exchanged blocks
+    const hipError_t e = ensure_dynamic_lds((const void*)kern, lds);
+    if (e != hipSuccess) return e;
+    kern<<<grid, 512, lds, st>>>(geo, ga);
+    note_launch(st, "wgrad_linear_wide_kernel", {DT});
+    return hipGetLastError();
 }
 
 template <int KIND, int DT>
@@ -729,18 +1045,58 @@ static bool grad_dma_ok(const Geom& geo, const Options& opt) {
     return 64 % geo.OW == 0 && ((int64_t)geo.OH * geo.OW) % 64 == 0;
 }
 
-// Tile and split choice: the largest tile that still gives about one
-// workgroup per CU, then token splits up to about four workgroups per CU
-// while the partial gradients stay within 32 MiB (each split adds a full
-// C_out x K fp32 partial to write and to sum).
+// Token splits of a gradient over nchunk 64-token chunks.  Register-staged
+// kernels: about four workgroups per CU.  Direct-to-LDS kernels: the least of
+//     chunks per split x chunk time x rounds of workgroups
+//   + partial gradients written and read back at about 4 TB/s (+ 3 us for
+//     the sum's launch),
+// with the chunk times (us) and the workgroups a CU runs at full rate measured
+// on U-Net shapes (one to sixteen splits each): 405 tokens x 1224 -> 1336 takes
+// 24 us with one split, 32 with the three of the first rule.
+static int grad_splits(const GradPlan& gp, const Geom& geo, int64_t nchunk) {
+    const int64_t tiles = (int64_t)gp.tiles_m * gp.tiles_n;
+    const int64_t slice = (int64_t)geo.C_out * geo.K * 4;
+    const int64_t cap = std::min<int64_t>({16, nchunk, std::max<int64_t>(1, (int64_t(32) << 20) / slice)});
+    if (!gp.dma) return (int)std::min<int64_t>(cap, std::max<int64_t>(1, (960 + tiles - 1) / tiles));
+    const bool wide = !geo.conv && gp.bm == kWideM, one = wide || gp.halves == 2;   // one workgroup per CU
+    const double chunk_us = wide ? 0.75 : geo.conv ? 0.6 : 0.5;
+    const double slots = one ? 256.0 : geo.conv ? 280.0 : 640.0;
+    int best = 1;
+    double best_us = 0;
+    for (int S = 1; S <= cap; ++S) {
+        const double rounds = std::max(1.0, (double)(tiles * S) / slots);
+        const double us = (double)((nchunk + S - 1) / S) * chunk_us * (one ? std::ceil(rounds) : rounds) +
+                          (S > 1 ? 3.0 + (double)(2 * S * slice) / 4.0e6 : (double)slice / 4.0e6);
+        if (S == 1 || us < best_us) {
+            best = S;
+            best_us = us;
+        }
+    }
+    return best;
+}
+
+// Tile choice (the register-staged kernels: the largest tile that still gives
+// about one workgroup per CU), and the most token splits of any call: the
+// partial gradients stay within 32 MiB (each split adds a full C_out x K fp32
+// partial to write and to sum).
 GradPlan grad_plan_create(const Geom& geo, int64_t max_tokens, const Options& opt) {
     GradPlan gp{};
     gp.dma = grad_dma_ok(geo, opt);
     const int want_bm = opt.grad_bm, want_bn = opt.grad_bn;
+    const int64_t nchunk = std::max<int64_t>(1, (max_tokens + kGradChunk - 1) / kGradChunk);
+    gp.halves = 1;
     if (gp.dma && !geo.conv) {
         gp.bm = gp.bn = 64;
-        gp.tiles_m = (geo.C_out + 63) / 64;
-        gp.tiles_n = (geo.K + 63) / 64;
+        // the 128 x 192 tile (one workgroup per CU) where little of it is padding
+        // and its tiles, given four chunks of tokens each, occupy half the chip
+        const int64_t wm = (geo.C_out + kWideM - 1) / kWideM, wn = (geo.K + kWideN - 1) / kWideN;
+        const bool full = (int64_t)geo.C_out * geo.K * 10 >= wm * wn * kWideM * kWideN * 7;
+        if (want_bm ? want_bm == kWideM && want_bn == kWideN : full && wm * wn * std::max<int64_t>(1, nchunk / 4) >= 128) {
+            gp.bm = kWideM;
+            gp.bn = kWideN;
+        }
+        gp.tiles_m = (geo.C_out + gp.bm - 1) / gp.bm;
+        gp.tiles_n = (geo.K + gp.bn - 1) / gp.bn;
     } else if (gp.dma) {
         // rows of C_out x (input channel, kernel row) pairs; 64 x 64 measured
         // faster than 128 x 64 on every layer shape here (more workgroups per
@@ -750,6 +1106,8 @@ GradPlan grad_plan_create(const Geom& geo, int64_t max_tokens, const Options& op
         gp.bn = 64;
         gp.tiles_m = (geo.C_out + gp.bm - 1) / gp.bm;
         gp.tiles_n = (npairs + gp.bn - 1) / gp.bn;
+        // few tiles: eight waves on each, with half the token splits
+        if (gp.bm == 64 && gp.tiles_m * (int64_t)gp.tiles_n < 256) gp.halves = 2;
     } else {
         const int shapes[3][2] = {{128, 128}, {64, 128}, {64, 64}};
         int pick = 2;
@@ -773,11 +1131,7 @@ GradPlan grad_plan_create(const Geom& geo, int64_t max_tokens, const Options& op
         gp.tiles_m = (geo.C_out + gp.bm - 1) / gp.bm;
         gp.tiles_n = (geo.K + gp.bn - 1) / gp.bn;
     }
-    const int64_t tiles = (int64_t)gp.tiles_m * gp.tiles_n;
-    const int64_t nchunk = std::max<int64_t>(1, (max_tokens + kGradChunk - 1) / kGradChunk);
-    const int64_t slice = (int64_t)geo.C_out * geo.K * 4;
-    gp.s_max = (int)std::min<int64_t>({16, nchunk, std::max<int64_t>(1, (960 + tiles - 1) / tiles),
-                                       std::max<int64_t>(1, (int64_t(32) << 20) / slice)});
+    gp.s_max = grad_splits(gp, geo, nchunk);
     if (opt.grad_splits > 0) gp.s_max = (int)std::min<int64_t>({16, nchunk, (int64_t)opt.grad_splits});
     return gp;
 }
@@ -796,8 +1150,8 @@ hipError_t launch_codebook_grad(const Geom& geo, const GradPlan& gp, int dtype, 
     ga.scales = scales;
     ga.P = P;
     ga.nchunk = (int)((geo.tokens + kGradChunk - 1) / kGradChunk);
-    int S = std::min(gp.s_max, ga.nchunk);
-    if (splits_override > 0) S = std::min(S, splits_override);
+    int S = std::min(gp.s_max, splits_override > 0 ? splits_override : grad_splits(gp, geo, ga.nchunk));
+    S = std::min(S, ga.nchunk);
     ga.cps = (ga.nchunk + S - 1) / S;
     ga.S = (ga.nchunk + ga.cps - 1) / ga.cps;     // every split owns at least one chunk
     ga.tiles_m = gp.tiles_m;
@@ -805,7 +1159,9 @@ hipError_t launch_codebook_grad(const Geom& geo, const GradPlan& gp, int dtype, 
     const int kind = grad_kind(geo);
     hipError_t e;
     const uint8_t* z16 = static_cast<const uint8_t*>(zero);
-    if (gp.dma && kind == 0) {
+    if (gp.dma && kind == 0 && gp.bm == kWideM) {
+        e = dtype == AQ_BF16 ? wgrad_wide_launch<AQ_BF16>(geo, ga, st) : wgrad_wide_launch<AQ_F16>(geo, ga, st);
+    } else if (gp.dma && kind == 0) {
         const unsigned grid = (unsigned)(8 * ((ga.S * ga.tiles_m * ga.tiles_n + 7) / 8));
         if (dtype == AQ_BF16)
             wgrad_linear_dma_kernel<AQ_BF16><<<grid, 256, 0, st>>>(geo, ga, z16);

@@ -194,3 +194,45 @@ def test_f32_infinite_codeword():
     y = layer.forward(torch.from_numpy(inp["x"]).cuda()).cpu().numpy()
     layer.close()
     assert np.all(np.isposinf(y[:, 7])) and np.all(np.isfinite(np.delete(y, 7, axis=1)))
+
+
+def _glin(name, C_out, K, n, M=2, B=8):
+    return LayerSpec(name=name, C_out=C_out, K=K, g=8, M=M, B=B, n=n)
+
+
+GRAD = [
+    # (layer, dtype, options): the 128 x 192 linear tile forced on edges of its tile, of a token chunk and of a split
+    (_glin("gw_one_tile", 128, 192, 64), "f16", {"grad_tile": "128x192"}),
+    (_glin("gw_less", 8, 8, 1), "bf16", {"grad_tile": "128x192"}),
+    (_glin("gw_edges", 136, 200, 65), "f16", {"grad_tile": "128x192"}),
+    (_glin("gw_long", 264, 392, 700, M=4), "bf16", {"grad_tile": "128x192"}),
+    (_glin("gw_auto", 1160, 584, 1500, M=1), "f16", {}),
+    # convolutions with few tiles (two waves' token halves) and many, whole and ragged tiles
+    (_conv("gc_few", 2, 24, 40, 3, 16, 16), "f16", {}),
+    (_conv("gc_one_chunk", 1, 8, 8, 3, 8, 8), "bf16", {}),
+    (_conv("gc_w64", 1, 16, 72, 3, 4, 64, M=1), "f16", {}),
+    (_conv("gc_1x1", 3, 88, 72, 1, 16, 16, M=4), "bf16", {}),
+    (_conv("gc_many", 1, 352, 1032, 3, 8, 8, M=1), "f16", {}),
+    # rows of K that are not whole 16-byte pieces (g = 9, odd channel count)
+    (LayerSpec(name="gc_k_odd", C_out=40, K=27 * 9, g=9, M=2, B=6, n=2, conv=ConvGeom(27, 3, 3, 1, 1, 8, 8)), "f16", {}),
+]
+
+
+@pytest.mark.parametrize("spec,dt,opts", GRAD, ids=lambda v: getattr(v, "name", None))
+def test_codebook_gradient_tiles(spec, dt, opts):
+    """Codebook gradients against the oracle, bar as in the gradient's own tests (2e-5, fp32 sums)."""
+    import paper_2506_05960_amd as P
+    from workloads import generate_grad_inputs
+    inp, gi = generate(spec, 7301), generate_grad_inputs(spec, 7302, dt)
+    layer = P.AQLayer(spec, inp)
+    for k, v in opts.items():
+        layer.set_option(k, v)
+    dev = [torch.from_numpy(gi[k].view(np.int16)).cuda().view(torch.bfloat16) if dt == "bf16"
+           else torch.from_numpy(gi[k]).cuda() for k in ("x", "dy")]
+    a, b = layer.codebook_grad(*dev), layer.codebook_grad(*dev)
+    print(spec.name, layer.last_launches(), flush=True)
+    assert torch.equal(a, b)
+    layer.close()
+    ref = O.codebook_grad(spec, {"codes": inp["codes"], "scales": inp["scales"], "x": gi["x"]}, gi["dy"], x_dtype=dt,
+                          dy_dtype=dt)
+    assert O.rel_err_inf(a.double().cpu().numpy(), ref) <= 2e-5
