@@ -223,11 +223,16 @@ def aq_version() -> str:
 
 # ---- convenience object over the same calls ----
 
+_TORCH_DTYPES: dict = {}   # storage dtype -> accepted torch dtypes, filled at first use (torch is imported late)
+
+
 def _torch_dtypes(name: str):
     """torch dtypes accepted for a storage dtype (bf16 also as its int16 bit pattern)."""
-    import torch
-    return {"f32": (torch.float32,), "f16": (torch.float16,), "bf16": (torch.bfloat16, torch.int16),
-            "i8": (torch.int8,)}[name]
+    if not _TORCH_DTYPES:
+        import torch
+        _TORCH_DTYPES.update({"f32": (torch.float32,), "f16": (torch.float16,),
+                              "bf16": (torch.bfloat16, torch.int16), "i8": (torch.int8,)})
+    return _TORCH_DTYPES[name]
 
 
 def _torch_dtype(name: str):
@@ -245,12 +250,23 @@ def _check_tensor(what: str, t, dtypes, shape, device) -> None:
         raise ValueError(f"{what} must be a torch tensor, got {type(t).__name__}")
     if t.dtype not in dtypes:
         raise ValueError(f"{what} must have dtype {' or '.join(str(d) for d in dtypes)}, got {t.dtype}")
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError(f"{what} must have shape {tuple(shape)}, got {tuple(t.shape)}")
     if not t.is_contiguous():
         raise ValueError(f"{what} must be contiguous")
-    if t.device.type != _DEVICE_TYPE or (device is not None and t.device.index != device):
-        raise ValueError(f"{what} must be on {_DEVICE_TYPE}:{device}, got {t.device}")
+    dev = t.device
+    if dev.type != _DEVICE_TYPE or (device is not None and dev.index != device):
+        raise ValueError(f"{what} must be on {_DEVICE_TYPE}:{device}, got {dev}")
+
+
+def _current_stream(index: Optional[int]) -> int:
+    """Raw handle of torch's current stream on device ``index`` (None: the current device)."""
+    import torch
+    # torch's own query of the raw handle: building the Stream object costs more than a small layer's launch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or index is None:
+        return torch.cuda.current_stream(index).cuda_stream
+    return raw(index)
 
 
 class AQLayer:
@@ -323,7 +339,7 @@ class AQLayer:
         if out is None:
             out = torch.empty(self.out_shape(n), dtype=_torch_dtype(s.y_dtype), device=x.device)
         _check_tensor("out", out, _torch_dtypes(s.y_dtype), self.out_shape(n), self.device)
-        st = stream if stream is not None else torch.cuda.current_stream(x.device).cuda_stream
+        st = stream if stream is not None else _current_stream(x.device.index)
         xs = 0 if x_scales is None else x_scales.data_ptr()
         (aq_layer_forward_static if static else aq_layer_forward)(self.handle, x.data_ptr(), xs, out.data_ptr(), n, st)
         return out
@@ -339,7 +355,7 @@ class AQLayer:
         n = self.spec.n if n is None else n
         if not isinstance(n, int) or n < 1:
             raise ValueError("n must be a positive int")
-        st = stream if stream is not None else torch.cuda.current_stream(self.device).cuda_stream
+        st = stream if stream is not None else _current_stream(self.device)
         aq_layer_prepare(self.handle, n, st)
 
     @staticmethod
@@ -357,7 +373,7 @@ class AQLayer:
         dev = layers[0].device
         if any(lay.device != dev for lay in layers):
             raise ValueError("layers on different devices")
-        st = stream if stream is not None else torch.cuda.current_stream(dev).cuda_stream
+        st = stream if stream is not None else _current_stream(dev)
         aq_layers_prepare([lay.handle for lay in layers], ns, st)
 
     def decode(self, out=None, stream=None):
@@ -387,7 +403,7 @@ class AQLayer:
         if out is None:
             out = torch.empty((s.M, 1 << s.B, s.g), dtype=torch.float32, device=x.device)
         _check_tensor("out", out, (torch.float32,), (s.M, 1 << s.B, s.g), self.device)
-        st = stream if stream is not None else torch.cuda.current_stream(x.device).cuda_stream
+        st = stream if stream is not None else _current_stream(x.device.index)
         dt = "f16" if x.dtype == torch.float16 else "bf16"
         aq_layer_codebook_grad(self.handle, x.data_ptr(), dy.data_ptr(), dt, out.data_ptr(), n, st)
         return out

@@ -20,6 +20,57 @@ using aq::DeviceWeights;
 using aq::Geom;
 using aq::LutPlan;
 
+namespace {
+
+// Kernels of a call's launches as reported (a kernel name is a string literal),
+// put into words only when a caller asks: one line each, name<arguments>.
+class LaunchNames {
+public:
+    void clear() { n_ = 0; more_.clear(); }
+    void add(const char* kernel, std::initializer_list<int> args) {
+        if (n_ < kHeld && args.size() <= kArgs) {
+            Entry& e = held_[n_++];
+            e.kernel = kernel;
+            e.nargs = (int)args.size();
+            std::copy(args.begin(), args.end(), e.args);
+        } else {
+            more_ += '\n';
+            line(more_, kernel, args.begin(), (int)args.size());
+        }
+    }
+    std::string text() const {
+        std::string t;
+        for (int i = 0; i < n_; ++i) {
+            if (i) t += '\n';
+            line(t, held_[i].kernel, held_[i].args, held_[i].nargs);
+        }
+        return t + more_;
+    }
+
+private:
+    static constexpr int kHeld = 8, kArgs = 10;
+    struct Entry {
+        const char* kernel;
+        int nargs;
+        int args[kArgs];
+    };
+    static void line(std::string& t, const char* kernel, const int* args, int nargs) {
+        t += kernel;
+        for (int i = 0; i < nargs; ++i) {
+            t += i ? ", " : "<";
+            t += std::to_string(args[i]);
+        }
+        if (nargs) t += '>';
+    }
+    int n_ = 0;
+    Entry held_[kHeld];
+    std::string more_;
+};
+
+}  // namespace
+
+struct aq_layer_plan;
+
 struct aq_layer {
     aq_layer_desc desc;
     int g, M, B, G;
@@ -52,11 +103,12 @@ struct aq_layer {
     size_t gpart_bytes;       // bytes allocated at d_gpart
     bool lut_ok, dec_ok, fused_ok;
     aq_path path;
+    aq_layer_plan* planned;   // route of the last forward's n (made by the first forward)
     int64_t lut_max_tokens;   // the measured rule for this layer
     aq::Options opt;
     std::vector<hipEvent_t> events;   // caller's timing events (aq_layer_set_launch_events)
     int32_t last_launches;            // kernel launches of the last traced call
-    std::string last_names;           // and their kernels, one per line
+    LaunchNames last_names;           // and their kernels
     int64_t prepared_n;               // aq_layer_prepare decoded the records of a forward of this
                                       // many tokens / images into d_wrec (0: none pending)
 };
@@ -71,7 +123,7 @@ struct LaunchTrace {
     int n_ev = 0;
     int count = 0;
     hipError_t err = hipSuccess;
-    std::string names;
+    LaunchNames* names = nullptr;
 };
 thread_local LaunchTrace g_trace;
 
@@ -80,18 +132,7 @@ thread_local LaunchTrace g_trace;
 void note_launch(hipStream_t st, const char* kernel, std::initializer_list<int> template_args) {
     LaunchTrace& t = g_trace;
     if (!t.active) return;
-    if (!t.names.empty()) t.names += '\n';
-    t.names += kernel;
-    if (template_args.size()) {
-        t.names += '<';
-        bool first = true;
-        for (int a : template_args) {
-            if (!first) t.names += ", ";
-            t.names += std::to_string(a);
-            first = false;
-        }
-        t.names += '>';
-    }
+    t.names->add(kernel, template_args);
     ++t.count;
     if (t.ev && t.count < t.n_ev && t.err == hipSuccess) {
         t.err = hipEventRecordWithFlags(t.ev[t.count], st, 0u);
@@ -141,6 +182,8 @@ struct TraceScope {
         aq::LaunchTrace& t = aq::g_trace;
         t = aq::LaunchTrace{};
         t.active = true;
+        L->last_names.clear();
+        t.names = &L->last_names;
         t.ev = L->events.empty() ? nullptr : L->events.data();
         t.n_ev = (int)L->events.size();
         if (t.ev) {
@@ -155,7 +198,7 @@ struct TraceScope {
     ~TraceScope() {
         aq::LaunchTrace& t = aq::g_trace;
         L->last_launches = t.count;
-        L->last_names = t.names;
+        t.names = nullptr;
         t.active = false;
         t.ev = nullptr;
     }
@@ -237,6 +280,8 @@ aq_path choose(const aq_layer* L, int64_t tokens) {
     return AQ_PATH_DECODE;
 }
 
+void free_plan(aq_layer* L);
+
 void free_layer(aq_layer* L) {
     if (!L) return;
     void* ptrs[] = {L->d_cb,     L->d_cb32, L->d_cbtile, L->d_codes, L->d_codes_lut, L->d_scales,
@@ -244,6 +289,7 @@ void free_layer(aq_layer* L) {
                     L->d_gidx_ent, L->d_gpart, L->d_part, L->d_arrivals, L->d_lut_arrivals, L->d_cb9};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
+    free_plan(L);
     delete L;
 }
 
@@ -853,6 +899,30 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
     return r;
 }
 
+}  // namespace
+
+struct aq_layer_plan {
+    int64_t n = 0;     // 0: none, or outdated by a path or option set since
+    Route route;
+};
+
+namespace {
+
+void free_plan(aq_layer* L) { delete L->planned; }
+
+// The route of a forward over n tokens or images.  A program's forwards of a
+// layer mostly repeat one n; planning (every tile and K split priced, with
+// occupancy look-ups) costs more host time than a small layer's kernel.
+const Route& forward_route(aq_layer* L, const Geom& geo, int64_t n) {
+    if (!L->planned) L->planned = new aq_layer_plan();
+    if (L->planned->n != n) {
+        L->planned->n = 0;
+        L->planned->route = plan_route(L, geo);
+        L->planned->n = n;
+    }
+    return L->planned->route;
+}
+
 // Where a forward's per-call scratch lives: the layer's workspace, or the
 // static array of the allocation-free entry point.
 struct Workspace {
@@ -864,7 +934,7 @@ struct Workspace {
     void* xpack;              // dense product: repacked activations
 };
 
-aq_status check_forward(const aq_layer* L, const void* X, const float* x_scales, const void* Y, int64_t n, Geom* geo,
+aq_status check_forward(aq_layer* L, const void* X, const float* x_scales, const void* Y, int64_t n, Geom* geo,
                         Route* r) {
     if (!L || !X || !Y) return fail(AQ_ERR_INVALID_ARGUMENT, "null pointer argument");
     if (n < 1) return fail(AQ_ERR_INVALID_ARGUMENT, "n must be >= 1");
@@ -874,7 +944,7 @@ aq_status check_forward(const aq_layer* L, const void* X, const float* x_scales,
     if (d.x_dtype == AQ_I8 && !x_scales) return fail(AQ_ERR_INVALID_ARGUMENT, "int8 activations need x_scales");
     if ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y)) & 15)
         return fail(AQ_ERR_INVALID_ARGUMENT, "X and Y must be 16-byte aligned");
-    *r = plan_route(L, *geo);
+    *r = forward_route(L, *geo, n);
     if (r->kind == Route::NONE)
         return fail(AQ_ERR_UNSUPPORTED, "g = 9 layers run on the fused kernel only (it was disabled or its "
                                         "tiles do not fit this shape)");
@@ -1500,12 +1570,14 @@ aq_status aq_layer_set_path(aq_layer* L, aq_path path) {
     if (path == AQ_PATH_DECODE && !L->dec_ok)
         return fail(AQ_ERR_UNSUPPORTED, "fp16/bf16 decode path needs g == 8 (or g == 9 on a 3x3 convolution)");
     L->path = path;
+    if (L->planned) L->planned->n = 0;
     return AQ_OK;
 }
 
 aq_status aq_layer_set_option(aq_layer* L, int32_t option, int64_t value) {
     if (!L) return fail(AQ_ERR_INVALID_ARGUMENT, "null layer");
     aq::Options& o = L->opt;
+    if (L->planned) L->planned->n = 0;
     auto in = [&](int64_t lo, int64_t hi) { return value >= lo && value <= hi; };
     auto bad = [&]() { return fail(AQ_ERR_INVALID_ARGUMENT, "option " + std::to_string(option) +
                                                                 ": value " + std::to_string(value) + " out of range"); };
@@ -1616,8 +1688,9 @@ aq_status aq_layer_last_launches(const aq_layer* L, int32_t* n_launches, char* n
     if (!L || !n_launches) return fail(AQ_ERR_INVALID_ARGUMENT, "null pointer argument");
     *n_launches = L->last_launches;
     if (names && names_size > 0) {
-        const size_t n = std::min<size_t>(L->last_names.size(), (size_t)names_size - 1);
-        std::memcpy(names, L->last_names.data(), n);
+        const std::string text = L->last_names.text();
+        const size_t n = std::min<size_t>(text.size(), (size_t)names_size - 1);
+        std::memcpy(names, text.data(), n);
         names[n] = '\0';
     }
     return AQ_OK;
