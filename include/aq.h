@@ -34,6 +34,10 @@
  *     faster (formats without an in-loop decode always take them);
  *     AQ_OPT_WEIGHTS forces either source.
  * aq_layer_forward picks a path per call (AQ_PATH_AUTO) unless one is forced.
+ * For one to four tokens of a linear layer with fp16 codebooks, AUTO may run a
+ * kernel of its own instead of either path: the codewords a row selects are
+ * read from LDS and multiplied with the tokens' inputs in fp32, in one launch
+ * (aq_layer_choose_path still names the path it replaces).
  *
  * Conventions for every entry point:
  *   - Return value is an aq_status; nothing aborts or throws across the ABI.

@@ -199,6 +199,12 @@ hipError_t launch_mfma_forward(const Geom& geo, const DeviceWeights& w, const vo
                                const float* x_scales, void* Y, int y_dtype, int tile_dtype,
                                hipStream_t stream);
 
+// One to four tokens with the codewords read from LDS (aq_few.hip); codes_lut is
+// in 16-byte chunks (M divides 16).
+bool few_supported(const Geom& geo, int cb_dtype, int x_dtype);
+hipError_t launch_few_forward(const Geom& geo, const DeviceWeights& w, const void* X, int x_dtype,
+                              const float* x_scales, void* Y, int y_dtype, hipStream_t stream);
+
 // Codebook preparation at create time: fp32 widening and tile-dtype rounding.
 hipError_t launch_codebook_prep(const void* cb, int cb_dtype, int64_t n, float* cb32, void* cbtile, int tile_dtype,
                                 hipStream_t stream);

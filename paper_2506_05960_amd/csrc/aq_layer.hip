@@ -764,7 +764,7 @@ bool wsplit_plan(const Geom& geo, const aq::Options& opt, int wk, aq::FusedPlan*
 }
 
 struct Route {
-    enum Kind { LUT = 0, F32 = 1, GENERIC = 2, DENSE = 3, FUSED = 4, REC_LINEAR = 5, NONE = 6 } kind;
+    enum Kind { LUT = 0, F32 = 1, GENERIC = 2, DENSE = 3, FUSED = 4, REC_LINEAR = 5, NONE = 6, FEW = 7 } kind;
     aq::FusedPlan fp;
     Geom geo;          // the geometry the kernels run on (kernel_geom)
     bool uneven;       // a convolution outside even_tiles
@@ -779,11 +779,31 @@ bool even_tiles(const Geom& geo, const aq::FusedPlan& p) {
     return geo.W % 2 == 0 && geo.cin % (16 * p.cm) == 0 && (128 % geo.OW == 0 || geo.OW % 64 == 0);
 }
 
+// The few-token kernel instead of the table path or the matrix cores, where no
+// option asks for one of those.  Its work grows with tokens x rows x codewords,
+// the matrix cores' does not grow with the tokens: measured over K = 512 to
+// 17280 and C_out = 96 to 3840 it is faster everywhere for M <= 2 (1 token,
+// 17280 -> 960: 5.6 against 9.8 us, 4 tokens, 17280 -> 3840: 20.8 against 26.3)
+// and for M = 4 up to about 100 M tokens x K x C_out (1 token, 17280 -> 960:
+// 7.5 against 11.8 us; 4 tokens, 8640 -> 3840: 18.4 against 15.3).
+bool few_route(const aq_layer* L, const Geom& geo) {
+    const aq::Options& o = L->opt;
+    if (!L->lut_ok || L->desc.tile_dtype != AQ_F16 || !aq::few_supported(geo, L->desc.codebook_dtype, L->desc.x_dtype))
+        return false;
+    if (o.table_one_launch || o.weights || o.generic || o.rec_product || o.fused_bm || o.split_k) return false;
+    if (o.lut_max_tokens != 0 && geo.tokens > o.lut_max_tokens) return false;
+    return geo.tokens * geo.K * geo.C_out <= (geo.M == 4 ? int64_t(100) * 1000000 : int64_t(300) * 1000000);
+}
+
 Route plan_route(const aq_layer* L, const Geom& geo) {
     Route r{};
     const aq_layer_desc& d = L->desc;
     if (choose(L, geo.tokens) == AQ_PATH_LUT) {
-        r.kind = Route::LUT;
+        r.kind = L->path == AQ_PATH_AUTO && few_route(L, geo) ? Route::FEW : Route::LUT;
+        return r;
+    }
+    if (L->path == AQ_PATH_AUTO && few_route(L, geo)) {
+        r.kind = Route::FEW;
         return r;
     }
     if (d.tile_dtype == AQ_F32) {
@@ -972,6 +992,9 @@ aq_status run_route(aq_layer* L, const Geom& geo, const Route& r, const void* X,
     case Route::LUT:
         e = aq::launch_lut_forward(geo, w, L->plan, X, d.x_dtype, xs, Y, d.y_dtype, wk.lut_ws, wk.lut_arrivals,
                                    L->opt.table_one_launch != 0, st);
+        break;
+    case Route::FEW:
+        e = aq::launch_few_forward(geo, w, X, d.x_dtype, xs, Y, d.y_dtype, st);
         break;
     case Route::F32:
         e = aq::launch_f32_forward(geo, w, X, d.x_dtype, xs, Y, d.y_dtype, st);
@@ -1440,7 +1463,7 @@ aq_status aq_layer_describe(const aq_layer* L, int64_t n, char* buf, int64_t siz
     const Geom geo = make_geom(L, n);
     if (geo.tokens > L->desc.max_tokens) return fail(AQ_ERR_INVALID_ARGUMENT, "tokens exceed max_tokens");
     const Route r = plan_route(L, geo);
-    static const char* kinds[] = {"table", "fp32", "generic", "dense-records", "fused", "rec-linear", "none"};
+    static const char* kinds[] = {"table", "fp32", "generic", "dense-records", "fused", "rec-linear", "none", "few-token"};
     static const char* decs[] = {"in-loop-lds-fp16", "in-loop-lds-fp32", "in-loop-lds-bf16", "in-loop-l2-fp16",
                                  "records"};
     const char* route = r.kind == Route::FUSED && r.fp.wsplit ? "rec-conv" : kinds[r.kind];

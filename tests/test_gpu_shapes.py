@@ -236,3 +236,58 @@ def test_codebook_gradient_tiles(spec, dt, opts):
     ref = O.codebook_grad(spec, {"codes": inp["codes"], "scales": inp["scales"], "x": gi["x"]}, gi["dy"], x_dtype=dt,
                           dy_dtype=dt)
     assert O.rel_err_inf(a.double().cpu().numpy(), ref) <= 2e-5
+
+
+FEW = [
+    # (C_out, K, M, B, tokens, x dtype, y dtype)
+    (1, 8, 1, 8, 1, "f16", "f32"),            # one group
+    (5, 128, 2, 8, 1, "f16", "f16"),          # a partial row tile, one whole chunk
+    (70, 136, 2, 4, 2, "i8", "f32"),          # a chunk past K, few codewords
+    (33, 264, 4, 8, 3, "f16", "f32"),         # three tokens in four slots
+    (300, 1000, 4, 6, 4, "i8", "f16"),
+    (130, 16384, 1, 8, 4, "f16", "f32"),      # exactly as many chunks as lanes
+    (40, 17280, 4, 8, 1, "f16", "f32"),       # several rounds of codes per lane
+    (24, 40960, 2, 8, 1, "f16", "f32"),       # more rounds than are loaded ahead
+    (20, 65536, 2, 8, 1, "f16", "f32"),       # the largest K that fits LDS, nearly
+    (1541, 520, 2, 8, 4, "f16", "f32"),       # eight rows per workgroup, a partial tile
+    (3077, 264, 4, 8, 2, "i8", "f16"),        # sixteen
+]
+
+
+@pytest.mark.parametrize("case", FEW, ids=lambda c: "x".join(str(v) for v in c))
+def test_few_token_kernel(case):
+    """One to four tokens: every output against the oracle and the table path's bound (fp32 products and sums)."""
+    import paper_2506_05960_amd as P
+    C_out, K, M, B, n, xd, yd = case
+    spec = LayerSpec(name="few", C_out=C_out, K=K, g=8, M=M, B=B, n=n, x_dtype=xd, y_dtype=yd)
+    inp = generate(spec, 7401)
+    layer = P.AQLayer(spec, inp)
+    layer.set_option("lut_max_tokens", 4)      # the table path's token count: the kernel replaces it
+    x = torch.from_numpy(inp["x"]).cuda()
+    xs = None if inp["x_scales"] is None else torch.from_numpy(inp["x_scales"]).cuda()
+    assert layer.describe(n)["route"] == "few-token"
+    y, y2 = layer.forward(x, xs), layer.forward(x, xs)
+    print(case, layer.last_launches(), flush=True)
+    assert torch.equal(y, y2) and torch.equal(y, layer.forward(x, xs, static=True))
+    tok, ch = np.arange(n), np.arange(C_out)
+    check_against_oracle(spec, inp, y.double().cpu().numpy(), tok, ch, "lut", 1e-5 if yd == "f32" else TOL)
+    layer.set_path("lut")                      # the table kernels stay behind their path
+    assert layer.describe(n)["route"] == "table"
+    layer.close()
+
+
+def test_few_token_infinite_codeword():
+    """The codeword that pads a last chunk does not reach a row that does not select it."""
+    import paper_2506_05960_amd as P
+    spec = LayerSpec(name="few_inf", C_out=9, K=24, g=8, M=1, B=2, n=2, y_dtype="f32")
+    inp = generate(spec, 7402)
+    inp["codebooks"][0, 0] = np.inf
+    inp["codes"][:, :, 0] = 1 + inp["codes"][:, :, 0] % 3
+    inp["codes"][4, 1, 0] = 0
+    inp["x"][:] = np.abs(inp["x"]) + 1
+    layer = P.AQLayer(spec, inp)
+    layer.set_option("lut_max_tokens", 4)
+    assert layer.describe(2)["route"] == "few-token"
+    y = layer.forward(torch.from_numpy(inp["x"]).cuda()).cpu().numpy()
+    layer.close()
+    assert np.all(np.isposinf(y[:, 4])) and np.all(np.isfinite(np.delete(y, 4, axis=1)))
