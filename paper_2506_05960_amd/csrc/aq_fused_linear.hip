@@ -24,6 +24,7 @@ static hipError_t lin_tiles(const Geom& geo, const FusedPlan& p, const FusedLaun
 template <int XT>
 static hipError_t lin_dec(const Geom& geo, const FusedPlan& p, const FusedLaunch& fl) {
     constexpr int DEC = XT == AQ_BF16 ? FUSED_DEC_BF16 : FUSED_DEC_PK16;
+    if (p.dec == DEC && p.mc == 1) return lin_tiles<XT, DEC, 1>(geo, p, fl);
     if (p.dec == DEC && p.mc == 2) return lin_tiles<XT, DEC, 2>(geo, p, fl);
     if (p.dec == DEC && p.mc == 4) return lin_tiles<XT, DEC, 4>(geo, p, fl);
     if constexpr (XT != AQ_BF16) {

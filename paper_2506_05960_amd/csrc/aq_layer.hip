@@ -367,7 +367,7 @@ bool fused_plan_create(const aq_layer_desc& d, int g, int M, int B, aq::FusedPla
     // a convolution whose last chunk is not whole: its codes past the end must
     // decode to zeros, which the records do
     const bool whole = !conv || d.conv_cin % (16 * p->cm) == 0;
-    const bool in_lds = whole && g == 8 && (M == 2 || M == 4) && B <= 8;
+    const bool in_lds = whole && g == 8 && (M == 1 || M == 2 || M == 4) && B <= 8;
     if (in_lds && d.codebook_dtype == d.tile_dtype) {
         p->dec = bf16 ? aq::FUSED_DEC_BF16 : aq::FUSED_DEC_PK16;
         p->cb_bytes = M * 256 * 16;             // LDS keeps 256 rows per codebook
