@@ -158,45 +158,64 @@ operand_records_kernel(const void* __restrict__ cb, const CodeT* __restrict__ co
     }
 }
 
-// Same records for fp16 codebooks with g = 8 and M in {1, 2, 4}: a codeword is
-// one 16-byte load, the M codewords of a group are summed with packed fp16
-// adds in ascending m (the same IEEE fp16 sums as above), and every load of a
-// thread is issued before any sum.
+// Same records for fp16 codebooks with g = 8 and M in {1, 2, 4}: the M
+// codewords of a group are summed with packed fp16 adds in ascending m (the
+// same IEEE fp16 sums as above).  A thread's codes are one code record, in the
+// order of the records it writes: a wave reads and writes contiguous bytes.
+// Codebooks of up to 256 rows are gathered from a copy in LDS, larger ones from
+// memory.  (A wave's gather of 64 random rows takes about 130 cycles through
+// the L1 and 50 from LDS, and code bytes read one by one from 64 rows cost as
+// much each: the U-Net pass's batched decodes, 160 MB of records, take 43 us
+// against 66 with byte codes and gathers through the L1.)
 template <typename CodeT, bool K3, int MC>
-__device__ __forceinline__ void records_f16_body(const u32x4* __restrict__ cb, const CodeT* __restrict__ codes,
+constexpr int records_code_dwords() { return ((K3 ? 9 : 4) * MC * (int)sizeof(CodeT) + 3) / 4; }
+
+template <typename CodeT, bool K3, int MC, bool LDS>
+__device__ __forceinline__ void records_f16_body(const u32x4* __restrict__ cb, const uint32_t* __restrict__ crec,
                                                  u32x4* __restrict__ rec, int nchunk, int C_out, int Gn, int B,
-                                                 int64_t idx) {   // idx: (chunk, channel, half)
+                                                 uint32_t idx,        // (chunk, channel, half)
+                                                 u32x4* cb_lds) {     // LDS: MC << B rows
     constexpr int ns = K3 ? 9 : 4;
     constexpr int NG = K3 ? 9 : 4;                 // groups a thread decodes
-    if (idx >= (int64_t)nchunk * C_out * 2) return;
-    const int c = (int)(idx / (2 * C_out));
-    const int rem = (int)(idx - (int64_t)c * 2 * C_out);
-    const int n = rem >> 1, q = rem & 1;
-    const uint32_t rows = 1u << B;
-    const int j0 = K3 ? (16 * c + 8 * q) * 9 / 8 : 0;
-    uint32_t code[NG][MC];
+    constexpr int ND = records_code_dwords<CodeT, K3, MC>();
+    const uint32_t total = (uint32_t)nchunk * (uint32_t)C_out * 2u;
+    const bool live = idx < total;
+    uint32_t dw[ND];
+    {
+        const uint32_t* p = crec + (size_t)(live ? idx : 0u) * ND;
 #pragma unroll
-    for (int s = 0; s < NG; ++s) {
-        const int j = K3 ? j0 + s : c * 2 * ns + 2 * s + q;
-        const int jc = j < Gn ? j : Gn - 1;       // groups past the end of K are zeroed below
-#pragma unroll
-        for (int m = 0; m < MC; ++m) code[s][m] = codes[((int64_t)n * Gn + jc) * MC + m];
+        for (int d = 0; d < ND; ++d) dw[d] = p[d];
     }
+    const uint32_t rows = 1u << B;
+    if constexpr (LDS) {
+        for (uint32_t i = threadIdx.x; i < MC * rows; i += 256) cb_lds[i] = cb[i];
+        __syncthreads();
+    }
+    if (!live) return;
+    const uint32_t c = idx / (2u * (uint32_t)C_out);
+    const uint32_t rem = idx - c * 2u * (uint32_t)C_out;
+    const int n = (int)(rem >> 1), q = (int)(rem & 1u);
+    const int j0 = K3 ? (16 * (int)c + 8 * q) * 9 / 8 : 0;
     u32x4 w[NG][MC];
 #pragma unroll
     for (int s = 0; s < NG; ++s)
 #pragma unroll
-        for (int m = 0; m < MC; ++m) w[s][m] = cb[m * rows + code[s][m]];
+        for (int m = 0; m < MC; ++m) {
+            const int i = s * MC + m;
+            const uint32_t code = sizeof(CodeT) == 1 ? (dw[i >> 2] >> (8 * (i & 3))) & 0xFFu
+                                                     : (dw[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
+            w[s][m] = LDS ? cb_lds[m * rows + code] : cb[m * rows + code];
+        }
     u32x4 g[NG];
 #pragma unroll
     for (int s = 0; s < NG; ++s) {
-        const int j = K3 ? j0 + s : c * 2 * ns + 2 * s + q;
+        const int j = K3 ? j0 + s : (int)c * 2 * ns + 2 * s + q;
         g[s] = w[s][0];
 #pragma unroll
         for (int m = 1; m < MC; ++m)
 #pragma unroll
             for (int d = 0; d < 4; ++d) g[s][d] = add_f16x2(g[s][d], w[s][m][d]);
-        if (j >= Gn) g[s] = u32x4{0u, 0u, 0u, 0u};
+        if (j >= Gn) g[s] = u32x4{0u, 0u, 0u, 0u};   // groups past the end of K
     }
 #pragma unroll
     for (int s = 0; s < ns; ++s) {
@@ -300,18 +319,18 @@ operand_records_bf16_kernel(const void* __restrict__ cb, const CodeT* __restrict
     }
 }
 
-template <typename CodeT, bool K3, int MC>
+template <typename CodeT, bool K3, int MC, bool LDS>
 __global__ void __launch_bounds__(256)
-operand_records_f16_kernel(const u32x4* __restrict__ cb, const CodeT* __restrict__ codes, u32x4* __restrict__ rec,
+operand_records_f16_kernel(const u32x4* __restrict__ cb, const uint32_t* __restrict__ crec, u32x4* __restrict__ rec,
                            int nchunk, int C_out, int Gn, int B) {
-    records_f16_body<CodeT, K3, MC>(cb, codes, rec, nchunk, C_out, Gn, B,
-                                    (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+    __shared__ u32x4 cb_lds[LDS ? MC * 256 : 1];
+    records_f16_body<CodeT, K3, MC, LDS>(cb, crec, rec, nchunk, C_out, Gn, B, blockIdx.x * 256u + threadIdx.x, cb_lds);
 }
 
 // Records of a 3x3 chunk in the kernel-aware format (g = 9: one group per
 // input channel's 3x3 filter) from fp16 codebooks padded to 16 values per row:
-// a codeword is one 16-byte and one 4-byte load, every load of a thread is
-// issued before any sum, and the M codewords of a group are summed in fp16 in
+// a codeword is one 16-byte and one 4-byte read, of a copy in LDS where codes
+// are 8 bits wide (1152 -> 576, M = 2: 9.6 -> 8.1 us), and the M codewords of a group are summed in fp16 in
 // ascending m (the same IEEE fp16 sums as operand_records_kernel).  A record
 // (chunk c, position s, channel n, lane half q) holds tap s of the 8 input
 // channels 16c + 8q + e; two threads share it, each decoding 4 channels and
@@ -319,31 +338,44 @@ operand_records_f16_kernel(const u32x4* __restrict__ cb, const CodeT* __restrict
 template <typename CodeT, int MC>
 __device__ __forceinline__ void records_g9_f16_body(const uint8_t* __restrict__ cbp, const CodeT* __restrict__ codes,
                                                     uint8_t* __restrict__ rec, int nchunk, int C_out, int Gn, int B,
-                                                    int64_t idx) {   // idx: (chunk, channel, half, quarter)
-    if (idx >= (int64_t)nchunk * C_out * 4) return;
-    const int hq = (int)(idx & 1);
-    const int64_t rid = idx >> 1;
-    const int c = (int)(rid / (2 * C_out));
-    const int rem = (int)(rid - (int64_t)c * 2 * C_out);
+                                                    uint32_t idx,        // (chunk, channel, half, quarter)
+                                                    u32x4* cb_lds) {     // 8-bit codes: 2 MC << B pieces
+    constexpr bool LDS = sizeof(CodeT) == 1;
+    const bool live = idx < (uint32_t)nchunk * (uint32_t)C_out * 4u;
+    const uint32_t rid = live ? idx >> 1 : 0u;
+    const int hq = (int)(idx & 1u);
+    const int c = (int)(rid / (2u * (uint32_t)C_out));
+    const int rem = (int)(rid - (uint32_t)c * 2u * (uint32_t)C_out);
     const int n = rem >> 1, q = rem & 1;
     const uint32_t rows = 1u << B;
     const int j0 = 16 * c + 8 * q + 4 * hq;
-    uint32_t code[4][MC];
+    // the codes of 4 consecutive channels: 4 MC consecutive values, aligned to
+    // their size (C_in is a multiple of 16)
+    constexpr int ND = MC * (int)sizeof(CodeT);
+    uint32_t dw[ND];
+    {
+        const uint32_t* p = reinterpret_cast<const uint32_t*>(codes + ((int64_t)n * Gn + min(j0, Gn - 4)) * MC);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int jc = j0 + e < Gn ? j0 + e : Gn - 1;   // groups past the end of K are zeroed below
-#pragma unroll
-        for (int m = 0; m < MC; ++m) code[e][m] = codes[((int64_t)n * Gn + jc) * MC + m];
+        for (int d = 0; d < ND; ++d) dw[d] = p[d];
     }
+    const u32x4* cb4 = reinterpret_cast<const u32x4*>(cbp);   // two 16-byte pieces per codeword
+    if constexpr (LDS) {
+        for (uint32_t i = threadIdx.x; i < 2u * MC * rows; i += 256) cb_lds[i] = cb4[i];
+        __syncthreads();
+    }
+    if (!live) return;
     u32x4 lo[4][MC];
     uint32_t hi[4][MC];
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
         for (int m = 0; m < MC; ++m) {
-            const uint8_t* row = cbp + ((size_t)m * rows + code[e][m]) * 32u;
-            lo[e][m] = *reinterpret_cast<const u32x4*>(row);
-            hi[e][m] = *reinterpret_cast<const uint32_t*>(row + 16);
+            const int i = e * MC + m;
+            const uint32_t code = sizeof(CodeT) == 1 ? (dw[i >> 2] >> (8 * (i & 3))) & 0xFFu
+                                                     : (dw[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
+            const u32x4* row = (LDS ? cb_lds : cb4) + 2u * (m * rows + code);
+            lo[e][m] = row[0];
+            hi[e][m] = *reinterpret_cast<const uint32_t*>(row + 1);
         }
     uint16_t v[4][9];
 #pragma unroll
@@ -377,8 +409,8 @@ template <typename CodeT, int MC>
 __global__ void __launch_bounds__(256)
 operand_records_g9_f16_kernel(const uint8_t* __restrict__ cbp, const CodeT* __restrict__ codes,
                               uint8_t* __restrict__ rec, int nchunk, int C_out, int Gn, int B) {
-    records_g9_f16_body<CodeT, MC>(cbp, codes, rec, nchunk, C_out, Gn, B,
-                                   (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+    __shared__ u32x4 cb_lds[sizeof(CodeT) == 1 ? 2 * MC * 256 : 1];
+    records_g9_f16_body<CodeT, MC>(cbp, codes, rec, nchunk, C_out, Gn, B, blockIdx.x * 256u + threadIdx.x, cb_lds);
 }
 
 // Batched forms: one launch decodes the records of several layers that share
@@ -399,18 +431,20 @@ template <typename CodeT, bool K3, int MC>
 __global__ void __launch_bounds__(256) operand_records_f16_batch_kernel(const RecordBatch b) {
     const int l = record_job_of(b, blockIdx.x);
     const RecordJob& j = b.job[l];
-    records_f16_body<CodeT, K3, MC>(static_cast<const u32x4*>(j.cb), static_cast<const CodeT*>(j.codes),
+    __shared__ u32x4 cb_lds[sizeof(CodeT) == 1 ? MC * 256 : 1];
+    records_f16_body<CodeT, K3, MC, sizeof(CodeT) == 1>(static_cast<const u32x4*>(j.cb), static_cast<const uint32_t*>(j.codes),
                                     static_cast<u32x4*>(j.rec), j.nchunk, j.C_out, j.G, j.B,
-                                    (int64_t)(blockIdx.x - b.start[l]) * blockDim.x + threadIdx.x);
+                                    (blockIdx.x - b.start[l]) * 256u + threadIdx.x, cb_lds);
 }
 
 template <typename CodeT, int MC>
 __global__ void __launch_bounds__(256) operand_records_g9_f16_batch_kernel(const RecordBatch b) {
     const int l = record_job_of(b, blockIdx.x);
     const RecordJob& j = b.job[l];
+    __shared__ u32x4 cb_lds[sizeof(CodeT) == 1 ? 2 * MC * 256 : 1];
     records_g9_f16_body<CodeT, MC>(static_cast<const uint8_t*>(j.cb), static_cast<const CodeT*>(j.codes),
                                    static_cast<uint8_t*>(j.rec), j.nchunk, j.C_out, j.G, j.B,
-                                   (int64_t)(blockIdx.x - b.start[l]) * blockDim.x + threadIdx.x);
+                                   (blockIdx.x - b.start[l]) * 256u + threadIdx.x, cb_lds);
 }
 
 size_t operand_record_bytes(const Geom& geo, const FusedPlan& plan) {
@@ -446,10 +480,24 @@ static hipError_t records_dispatch(const Geom& geo, const FusedPlan& plan, const
         note_launch(st, "operand_records_bf16_kernel", {w.cb_dtype, 8 * (int)sizeof(CodeT), geo.M <= 2 ? geo.M : 0});
         return hipGetLastError();
     }
-    if (w.cb_dtype == AQ_F16 && geo.g == 8 && (geo.M == 1 || geo.M == 2 || geo.M == 4)) {
+    if (w.cb_dtype == AQ_F16 && geo.g == 8 && w.crec && (geo.M == 1 || geo.M == 2 || geo.M == 4)) {
         const u32x4* cb = static_cast<const u32x4*>(w.codebooks);
+        const uint32_t* crec = reinterpret_cast<const uint32_t*>(w.crec);
+        // with less than a workgroup per CU the copy's barrier only adds latency
+        // (8192 x 576 -> 1728, M = 4, 122 workgroups: 5.1 us without, 5.3 with)
+        const bool lds = n >= 256 * 256;
 #define AQ_REC16(K3, MC) \
-    operand_records_f16_kernel<CodeT, K3, MC><<<grid, block, 0, st>>>(cb, codes, r, plan.nchunk, geo.C_out, geo.G, geo.B)
+    do {                                                                                                        \
+        if constexpr (sizeof(CodeT) == 1) {                                                                     \
+            if (lds) {                                                                                          \
+                operand_records_f16_kernel<CodeT, K3, MC, true><<<grid, block, 0, st>>>(cb, crec, r, plan.nchunk, \
+                                                                                        geo.C_out, geo.G, geo.B); \
+                break;                                                                                          \
+            }                                                                                                   \
+        }                                                                                                       \
+        operand_records_f16_kernel<CodeT, K3, MC, false><<<grid, block, 0, st>>>(cb, crec, r, plan.nchunk,        \
+                                                                                 geo.C_out, geo.G, geo.B);        \
+    } while (0)
         if (plan.kind == 1) {
             if (geo.M == 1) AQ_REC16(true, 1);
             else if (geo.M == 2) AQ_REC16(true, 2);
@@ -509,7 +557,7 @@ int records_batch_key(const Geom& geo, const FusedPlan& plan, const DeviceWeight
     const int mi = geo.M == 1 ? 0 : geo.M == 2 ? 1 : geo.M == 4 ? 2 : -1;
     if (mi < 0) return -1;
     const int c16 = geo.B > 8;
-    if (geo.g == 8 && (plan.kind == 1 || plan.cm == 4)) return ((0 * 2 + c16) * 2 + (plan.kind == 1)) * 3 + mi;
+    if (geo.g == 8 && w.crec && (plan.kind == 1 || plan.cm == 4)) return ((0 * 2 + c16) * 2 + (plan.kind == 1)) * 3 + mi;
     if (geo.g == 9 && plan.kind == 1 && w.cb9) return ((1 * 2 + c16) * 2 + 1) * 3 + mi;
     return -1;
 }
@@ -518,7 +566,7 @@ RecordJob records_batch_job(const Geom& geo, const FusedPlan& plan, const Device
                             uint32_t* blocks) {
     const int64_t n = (int64_t)plan.nchunk * geo.C_out * (geo.g == 9 ? 4 : 2);   // threads
     *blocks = (uint32_t)((n + 255) / 256);
-    return RecordJob{geo.g == 9 ? w.cb9 : w.codebooks, w.codes, rec, plan.nchunk, geo.C_out, geo.G, geo.B};
+    return RecordJob{geo.g == 9 ? w.cb9 : w.codebooks, geo.g == 9 ? w.codes : static_cast<const void*>(w.crec), rec, plan.nchunk, geo.C_out, geo.G, geo.B};
 }
 
 hipError_t launch_operand_records_batch(int key, const RecordBatch& b, hipStream_t st) {

@@ -60,6 +60,7 @@ struct DeviceWeights {
     const float* scales;          // [C_out]
     int cb_dtype;                 // aq_dtype
     const void* cb9;              // g = 9 fp16 codebooks padded to 16 values per row [M][2^B][16], else null
+    const uint8_t* crec;          // code records [chunk][C_out][half] (FusedPlan::rec_bytes each), else null
 };
 
 // LUT-path blocking chosen at create time.
@@ -157,7 +158,7 @@ hipError_t launch_operand_records(const Geom& geo, const FusedPlan& plan, const 
 // records kernel is the same, passed by value as the kernel argument.
 struct RecordJob {
     const void* cb;       // fp16 codebooks [M][2^B][8], or the padded g = 9 rows [M][2^B][16]
-    const void* codes;    // [C_out][G][M] uint8 | uint16
+    const void* codes;    // code records (g = 8), or [C_out][G][M] uint8 | uint16 (g = 9)
     void* rec;            // the layer's record buffer
     int nchunk, C_out, G, B;
 };

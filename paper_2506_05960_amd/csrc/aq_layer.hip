@@ -272,6 +272,11 @@ Geom make_geom(const aq_layer* L, int64_t n) {
     return geo;
 }
 
+DeviceWeights device_weights(const aq_layer* L) {
+    return DeviceWeights{L->d_cb,     L->d_cb32,   L->d_cbtile,           L->d_codes, L->d_codes_lut,
+                         L->d_scales, L->desc.codebook_dtype, L->d_cb9, L->d_crec};
+}
+
 aq_path choose(const aq_layer* L, int64_t tokens) {
     if (L->path != AQ_PATH_AUTO) return L->path;
     const int64_t lim = L->opt.lut_max_tokens == 0 ? L->lut_max_tokens : L->opt.lut_max_tokens < 0 ? 0
@@ -383,7 +388,7 @@ bool fused_plan_create(const aq_layer_desc& d, int g, int M, int B, aq::FusedPla
     }
     p->mc = M;
     const int ns = p->kind == 1 ? 9 : p->cm;
-    const int ent_b = p->dec == aq::FUSED_DEC_T16G ? 2 : 1;
+    const int ent_b = B > 8 ? 2 : 1;
     p->rec_bytes = (ns * M * ent_b + 3) / 4 * 4;
     return true;
 }
@@ -393,7 +398,7 @@ bool fused_plan_create(const aq_layer_desc& d, int g, int M, int B, aq::FusedPla
 // when B > 8), padded to whole dwords.
 std::vector<uint8_t> fused_records(const aq::FusedPlan& p, const void* codes, int C_out, int G, int M, int B) {
     const int ns = p.kind == 1 ? 9 : p.cm;
-    const int ent_b = p.dec == aq::FUSED_DEC_T16G ? 2 : 1;
+    const int ent_b = B > 8 ? 2 : 1;
     std::vector<uint8_t> rec((size_t)p.nchunk * C_out * 2 * p.rec_bytes, 0);
     for (int c = 0; c < p.nchunk; ++c)
         for (int n = 0; n < C_out; ++n)
@@ -982,8 +987,7 @@ aq_status run_route(aq_layer* L, const Geom& geo, const Route& r, const void* X,
                     int64_t n, hipStream_t st, const Workspace& wk) {
     const aq_layer_desc& d = L->desc;
     const float* xs = d.x_dtype == AQ_I8 ? x_scales : nullptr;
-    const DeviceWeights w{L->d_cb,         L->d_cb32,   L->d_cbtile,      L->d_codes,
-                          L->d_codes_lut, L->d_scales, d.codebook_dtype, L->d_cb9};
+    const DeviceWeights w = device_weights(L);
     TraceScope trace(L, st);
     if (trace.error() != hipSuccess) return hip_fail(trace.error(), "launch event");
     hipError_t e = hipSuccess;
@@ -1245,7 +1249,9 @@ aq_status aq_layer_create(const aq_layer_desc* desc, const void* codebooks, cons
     L->fused_ok = fused_ok;
     L->fplan = fplan;
     if (L->fused_ok) {
-        if (!fplan.rec_only) {
+        // code records: what the in-loop decode and the fp16 g = 8 records kernel read
+        if (!fplan.rec_only || (g == 8 && fplan.tile == AQ_F16 && desc->codebook_dtype == AQ_F16 &&
+                                (M == 1 || M == 2 || M == 4))) {
             std::vector<uint8_t> rec = fused_records(L->fplan, codes, C_out, G, M, B);
             AQ_TRY(dev_upload(&L->d_crec, rec.data(), rec.size(), "fused code records"));
         }
@@ -1337,8 +1343,7 @@ aq_status aq_layer_prepare(aq_layer* L, int64_t n, void* stream) {
                      r.fp.dec == aq::FUSED_DEC_REC;
     if (!rec) return AQ_OK;                      // nothing of this forward depends on the weights alone
     const aq_layer_desc& d = L->desc;
-    const DeviceWeights w{L->d_cb,         L->d_cb32,   L->d_cbtile,      L->d_codes,
-                          L->d_codes_lut, L->d_scales, d.codebook_dtype, L->d_cb9};
+    const DeviceWeights w = device_weights(L);
     const hipError_t e = aq::launch_operand_records(geo, r.fp, w, L->d_wrec, st);
     if (e != hipSuccess) return hip_fail(e, "records launch");
     if (trace.error() != hipSuccess) return hip_fail(trace.error(), "launch event");
@@ -1386,8 +1391,7 @@ aq_status aq_layers_prepare(aq_layer* const* layers, const int64_t* n, int32_t c
                          it.r.fp.dec == aq::FUSED_DEC_REC;
         if (!rec) continue;
         aq_layer* L = it.L;
-        const DeviceWeights w{L->d_cb,         L->d_cb32,   L->d_cbtile,      L->d_codes,
-                              L->d_codes_lut, L->d_scales, L->desc.codebook_dtype, L->d_cb9};
+        const DeviceWeights w = device_weights(L);
         it.key = aq::records_batch_key(it.geo, it.r.fp, w);
         if (it.key < 0) {                       // no batched form: the layer's own launch
             e = aq::launch_operand_records(it.geo, it.r.fp, w, L->d_wrec, st);
@@ -1413,8 +1417,7 @@ aq_status aq_layers_prepare(aq_layer* const* layers, const int64_t* n, int32_t c
         for (Item& it : items) {
             if (it.key != key) continue;
             aq_layer* L = it.L;
-            const DeviceWeights w{L->d_cb,         L->d_cb32,   L->d_cbtile,      L->d_codes,
-                                  L->d_codes_lut, L->d_scales, L->desc.codebook_dtype, L->d_cb9};
+            const DeviceWeights w = device_weights(L);
             uint32_t blocks = 0;
             const aq::RecordJob job = aq::records_batch_job(it.geo, it.r.fp, w, L->d_wrec, &blocks);
             if (b.count == aq::kRecordBatchMax ||
@@ -1578,8 +1581,7 @@ aq_status aq_layer_codebook_grad(aq_layer* L, const void* X, const void* dY, int
 aq_status aq_layer_decode(aq_layer* L, void* W, void* stream) {
     if (!L || !W) return fail(AQ_ERR_INVALID_ARGUMENT, "null pointer argument");
     const Geom geo = make_geom(L, 1);
-    const DeviceWeights w{L->d_cb, L->d_cb32, L->d_cbtile, L->d_codes, L->d_codes_lut, L->d_scales,
-                          L->desc.codebook_dtype};
+    const DeviceWeights w = device_weights(L);
     hipError_t e = aq::launch_decode_to_global(geo, w, L->desc.tile_dtype, W, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "decode launch");
     return AQ_OK;
