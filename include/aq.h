@@ -236,7 +236,8 @@ aq_status aq_layer_set_path(aq_layer* layer, aq_path path);
  *                           decode (W never in memory), 2 pre-decoded
  *                           records (W written per forward); formats with
  *                           no in-loop decode (g = 9, M not in {1, 2, 4},
- *                           fp32/bf16 codebooks) always take the records
+ *                           codebooks not of the tile's type) always take the
+ *                           records
  *   AQ_OPT_GENERIC          1 = generic decode kernel instead of the fused
  *                           decode kernel (0: fused kernel where it applies)
  *   AQ_OPT_RECORD_PRODUCT   product kernel over records: 0 auto (linear

@@ -249,7 +249,8 @@ static hipError_t f32_launch_x(const Geom& geo, const DeviceWeights& w, const vo
                                int y_dtype, hipStream_t st) {
     if (geo.g != 8) return f32_launch_mode<XT, CodeT, kF32AnyG>(geo, w, X, x_scales, Y, y_dtype, st);
     if constexpr (sizeof(CodeT) == 1 && XT == AQ_F32) {
-        // chunks of 16 code bytes per channel (the table path's code layout for these M)
+        // chunks of 16 code bytes per channel (the table path's code layout for these M:
+        // its chunk of 16 / M groups fills 64 KB of table, so it never takes more)
         if (w.codes_lut && geo.M == 1) return f32_launch_mode<XT, CodeT, 1>(geo, w, X, x_scales, Y, y_dtype, st);
         if (w.codes_lut && geo.M == 2) return f32_launch_mode<XT, CodeT, 2>(geo, w, X, x_scales, Y, y_dtype, st);
         if (w.codes_lut && geo.M == 4) return f32_launch_mode<XT, CodeT, 4>(geo, w, X, x_scales, Y, y_dtype, st);

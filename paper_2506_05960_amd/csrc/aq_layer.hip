@@ -9,6 +9,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <new>
 #include <numeric>
 #include <string>
 #include <utility>
@@ -436,6 +437,7 @@ struct TileCand {
 constexpr double kFixedChunks = 3.0;
 constexpr double kFixedChunksUnderfilled = 12.0;
 constexpr double kSplitChunks = 1.0;
+constexpr double kLoop3Fixed = 3.2, kLoop3Publish = 0.7, kLoop3Split = 1.66;   // us, see fused_plan_tile
 
 // Fewer than 256 tiles of 64 tokens x 64 channels: the layer cannot fill the chip.
 bool underfilled(const Geom& geo) {
@@ -546,8 +548,8 @@ bool fused_plan_tile(const Geom& geo, const aq::Options& opt, size_t part_cap, i
     static const TileCand conv1[] = {{64, 96, 4}, {64, 64, 4}, {64, 64, 8}};
     static const TileCand lin[] = {{64, 96, 8}, {64, 64, 8}, {32, 128, 4}, {32, 64, 4}};
     const TileCand* cands = p->kind == 1 ? conv3 : p->kind == 2 ? conv1 : lin;
-    const int rec_only = p->kind != 0 && p->dec != aq::FUSED_DEC_REC ? 1 : 0;
-    const int ncand = (p->kind == 1 ? 6 : p->kind == 2 ? 3 : 4) - rec_only;
+    const bool in_loop = p->dec != aq::FUSED_DEC_REC;
+    const int ncand = p->kind == 1 ? (in_loop ? 5 : 6) : p->kind == 2 ? (in_loop ? 2 : 3) : 4;
     const int want_bm = opt.fused_bm, want_bn = opt.fused_bn;
     double best = 0;
     aq::FusedPlan bestp{};
@@ -596,6 +598,12 @@ bool fused_plan_tile(const Geom& geo, const aq::Options& opt, size_t part_cap, i
         if (p->kind == 0 && p->dec == aq::FUSED_DEC_REC && !(t.bm == 64 && t.bn == 64)) tcost *= 1.25;
         if (narrow && !widen) tcost *= 1.15;             // bank conflicts on the A-fragment reads (measured)
         const bool under = underfilled(geo);
+        // under-filled 3x3 layers decoding one or two codebooks in the loop: a tile's
+        // chunk time barely depends on its size, publishing and summing its K
+        // splits does; in us, fitted to forced tiles and splits of the 512-token
+        // U-Net layers (K = 8640: 64 x 96 with three splits 21.4, 64 x 64 with two
+        // 22.9; K = 17280: 64 x 96 with three 32.1, 128 x 64 with four 34.9)
+        const bool in_loop3 = under && p->kind == 1 && p->dec == aq::FUSED_DEC_PK16 && p->mc <= 2;
         if (under && (p->dec == aq::FUSED_DEC_PK16 || p->dec == aq::FUSED_DEC_BF16)) tcost *= 1.0 + 32.0 * p->mc / t.bm;
         for (int S = 1; S <= aq::kMaxSplitK; ++S) {
             if (opt.split_k != 0 && S != opt.split_k && !(S == 1 && opt.split_k > 1)) continue;
@@ -608,6 +616,12 @@ bool fused_plan_tile(const Geom& geo, const aq::Options& opt, size_t part_cap, i
             const double cpw = std::ceil((double)p->nchunk / (4.0 * S)) + (S > 1 ? kSplitChunks : 0.0);
             double cost = tcost * cu_time((nwg * S + 255) / 256, occ, cpw,
                                           under ? kFixedChunksUnderfilled : kFixedChunks);
+            if (in_loop3) {
+                const double area = (double)t.bm * t.bn / 4096.0;
+                cost = kLoop3Fixed + (t.bn == 96 ? 2.25 : t.bm == 128 ? 2.3 : 2.05) * (cpw - (S > 1 ? kSplitChunks : 0.0)) +
+                       (S > 1 ? kLoop3Publish + kLoop3Split * S * area : 0.0);
+                if (narrow && !widen) cost *= 1.15;
+            }
             // a forced split wins over the unsplit fallback of the same tile
             if (opt.split_k > 1 && S == 1) cost *= 1e6;
             if (!found || cost < best) {
@@ -685,6 +699,15 @@ bool gemm_plan_tile(const Geom& geo, const aq::Options& opt, aq::FusedPlan* p) {
     return found;
 }
 
+// A 3x3 layer of one or two codebooks whose weights are few: its tiles decode
+// them in the loop faster than a records launch does once (32768 tokens, M = 2:
+// 64 -> 64 10.0 against 13.1 us, 48 -> 96 8.0 against 11.7; 32 -> 192 the same,
+// 16 -> 160 16.6 against 12.0).
+bool small_weights(const Geom& geo, const aq::FusedPlan& p) {
+    return p.kind == 1 && p.dec == aq::FUSED_DEC_PK16 && p.mc <= 2 && geo.C_out <= 96 &&
+           (int64_t)geo.K * geo.C_out <= 50000;
+}
+
 // Pre-decoded mode (operands decoded once per forward into records the main
 // loop reads with plain 16-byte loads) instead of decoding inside the main
 // loop: chosen for codebooks too large for LDS (their codeword reads from L2
@@ -704,6 +727,7 @@ bool use_predecoded(const aq_layer* L, const Geom& geo) {
     // 3x3 layers for M = 2 and 4 (8 x 8 level, K = 8640: 21.8 / 27.1 us against
     // 29.5 in-loop unsplit and 32.8 with records)
     if (p.kind != 0 && p.dec == aq::FUSED_DEC_PK16 && underfilled(geo) && p.nchunk >= 8) return false;
+    if (small_weights(geo, p)) return false;
     if (p.kind == 1) {
         // 3x3 convolutions of the U-Net shapes (both routes timed per shape): with
         // M = 4 the pre-decoded route won on every shape from 512 tokens up; with
@@ -720,6 +744,9 @@ bool use_predecoded(const aq_layer* L, const Geom& geo) {
             // at 2048 tokens and up or M >= 4 (the in-loop decode then gathers 4 codewords
             // per group); with fewer tiles the in-loop decode's K split keeps more units busy
             const int64_t tiles = ((geo.tokens + 127) / 128) * (int64_t)((geo.C_out + 127) / 128);
+            // (bf16 codewords are summed in fp32 and rounded in the loop: records pay
+            // off earlier; 2663 tokens x 2256 -> 832, 147 tiles: 27.9 against 38.8 us)
+            if (p.dec == aq::FUSED_DEC_BF16) return tiles >= 128 && geo.tokens >= 1024;
             return tiles >= 192 && (geo.tokens >= 2048 || p.mc >= 4);
         }
         return p.mc >= 4 && geo.C_out >= 1152 && geo.tokens >= 2048;
@@ -793,7 +820,7 @@ bool even_tiles(const Geom& geo, const aq::FusedPlan& p) {
 // 7.5 against 11.8 us; 4 tokens, 8640 -> 3840: 18.4 against 15.3).
 bool few_route(const aq_layer* L, const Geom& geo) {
     const aq::Options& o = L->opt;
-    if (!L->lut_ok || L->desc.tile_dtype != AQ_F16 || !aq::few_supported(geo, L->desc.codebook_dtype, L->desc.x_dtype))
+    if (!L->lut_ok || L->plan.jc * L->M != 16 || L->desc.tile_dtype != AQ_F16 || !aq::few_supported(geo, L->desc.codebook_dtype, L->desc.x_dtype))
         return false;
     if (o.table_one_launch || o.weights || o.generic || o.rec_product || o.fused_bm || o.split_k) return false;
     if (o.lut_max_tokens != 0 && geo.tokens > o.lut_max_tokens) return false;
@@ -831,6 +858,9 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
                  nimg * geo.cin < lim24 && (int64_t)geo.C_out * geo.K * 2 < (int64_t(1) << 31);
         // other codebook types decode their records value by value and keep the generic kernel
         if (geo.g != 8 || d.codebook_dtype != AQ_F16) fits31 = false;
+        // 1x1 on planes of an odd pixel count with few channels: one launch of the
+        // generic kernel is faster (2 x 15 x 15, 64 -> 64: 11.7 against 14.3 us)
+        if (geo.kh == 1 && r.geo.W % 2 != 0 && geo.K <= 128) fits31 = false;
     }
     if (L->fused_ok && use_predecoded(L, geo)) {
         // pre-decoded mode: operands decoded once per forward, then read with plain loads
@@ -875,7 +905,8 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
     // selects the two-wave reduction), 1 and 2 exclude it; AQ_OPT_WEIGHTS = 1
     // keeps a layer on the in-loop decode.
     bool planned = false;
-    const bool ws_switch = fp.kind != 0 && fp.dec != aq::FUSED_DEC_REC && opt.weights == 0;
+    const bool ws_switch =
+        fp.kind != 0 && fp.dec != aq::FUSED_DEC_REC && opt.weights == 0 && !small_weights(geo, L->fplan);
     if (L->fused_ok && fits31 && opt.generic != 1 && fp.kind != 0 && (fp.dec == aq::FUSED_DEC_REC || ws_switch) &&
         (opt.rec_product == 3 || opt.rec_product == 0)) {
         aq::FusedPlan rp = fp;
@@ -887,7 +918,12 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
         const aq::FusedPlan* pick = nullptr;
         if (opt.rec_product == 3 && !ws_switch) {
             if (!r.uneven && (opt.fused_bm == 64 ? ok2 : ok1)) pick = opt.fused_bm == 64 ? &w2 : &w1;
-        } else if (opt.rec_product == 0 && r.geo.OW >= 16) {
+        } else if (opt.rec_product == 0 && r.geo.OW >= 16 &&
+                   (geo.C_out > 64 || geo.K <= (fp.kind == 1 ? 576 : 512))) {
+            // (C_out up to 64 leaves half of this kernel's tile empty, which only a
+            // short reduction repays; 8 x 64 x 64, M = 2: 3x3 576 -> 64 44.4 us here,
+            // 32.2 on the fused kernel, 1x1 576 -> 64 17.6 and 14.2, but 53 x 64 x 64
+            // 3x3 64 -> 64 42.0 and 50.0, 17 x 64 x 64 1x1 48 -> 32 9.1 and 17.5)
             // (output rows under 16 tokens: this kernel does not widen its staged
             // rows, and its fragment reads conflict; 8 x 8 images measured slower)
             if (ok1 && w1.ntiles >= (fp.kind == 1 ? 192 : 256)) pick = &w1;
@@ -915,7 +951,13 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
         fp.rlin_var = aq::rec_linear_tile(geo, opt.rlin_tile);
         // a linear layer's records feed the 2 x 2 wave-split product (AQ_OPT_RECORD_PRODUCT = 1:
         // the fused kernel's own pre-decoded mode, whose partial-tile order matches its in-loop mode)
-        const bool rlin = fp.dec == aq::FUSED_DEC_REC && opt.rec_product != 1 && aq::rec_linear_supported(geo, fp, d.x_dtype);
+        // Formats without an in-loop decode take it from 88 of its tiles up; with fewer
+        // the fused kernel keeps more units busy (M = 3: 8 tokens x 2256 -> 64 22.5
+        // against 11.3 us, 1000 x 1152 -> 1152, 72 tiles, 19.1 against 16.3).
+        const int64_t rtiles = ((geo.tokens + 127) / 128) * (int64_t)((geo.C_out + 127) / 128);
+        const bool few_tiles = L->fplan.rec_only && opt.rec_product == 0 && rtiles < 88;
+        const bool rlin = fp.dec == aq::FUSED_DEC_REC && opt.rec_product != 1 && !few_tiles &&
+                          aq::rec_linear_supported(geo, fp, d.x_dtype);
         r.kind = rlin ? Route::REC_LINEAR : Route::FUSED;
         r.fp = fp;
         return r;
@@ -938,8 +980,9 @@ void free_plan(aq_layer* L) { delete L->planned; }
 // The route of a forward over n tokens or images.  A program's forwards of a
 // layer mostly repeat one n; planning (every tile and K split priced, with
 // occupancy look-ups) costs more host time than a small layer's kernel.
-const Route& forward_route(aq_layer* L, const Geom& geo, int64_t n) {
-    if (!L->planned) L->planned = new aq_layer_plan();
+Route forward_route(aq_layer* L, const Geom& geo, int64_t n) {
+    if (!L->planned) L->planned = new (std::nothrow) aq_layer_plan();
+    if (!L->planned) return plan_route(L, geo);
     if (L->planned->n != n) {
         L->planned->n = 0;
         L->planned->route = plan_route(L, geo);

@@ -55,7 +55,7 @@ UNEVEN = [
     _conv("u36_rec", 4, 64, 256, 3, 36, 36, M=1),             # records only
     _conv("u28_b16", 2, 48, 64, 3, 28, 28, M=1, B=16),        # codewords from memory
     _conv("u1x1_24", 3, 80, 96, 1, 24, 24),                   # 1x1, a partly empty chunk, planes of 64-pixel rows
-    _conv("u1x1_odd", 2, 64, 64, 1, 15, 17),                  # 1x1, odd planes
+    _conv("u1x1_odd", 2, 136, 64, 1, 15, 17),                 # 1x1, odd planes
     _conv("u1x1_10", 7, 40, 50, 1, 10, 10, M=4),              # 1x1, 4-pixel rows
     _conv("u48_wide", 8, 48, 256, 3, 48, 48, y_dtype="f32"),  # enough tiles for the wave-split kernel
     _conv("u1x1_wide", 12, 144, 192, 1, 54, 52),
