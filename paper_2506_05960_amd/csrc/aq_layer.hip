@@ -763,7 +763,7 @@ bool use_predecoded(const aq_layer* L, const Geom& geo) {
 // AQ_OPT_FUSED_TILE picks 128 or 192 channels when its token count matches.
 // False where the kernel does not apply (tile rows, image planes not a
 // multiple of 4 tokens, more staging units than instantiated).
-bool wsplit_plan(const Geom& geo, const aq::Options& opt, int wk, aq::FusedPlan* p) {
+bool wsplit_plan(const Geom& geo, const aq::Options& opt, int wk, aq::FusedPlan* p, int max_bn = 192) {
     if (p->dec != aq::FUSED_DEC_REC || !(p->kind == 1 || (p->kind == 2 && p->cm == 4))) return false;
     if ((geo.OH * geo.OW) % 4 != 0) return false;
     const int bm = wk == 1 ? 128 : 64;
@@ -771,7 +771,7 @@ bool wsplit_plan(const Geom& geo, const aq::Options& opt, int wk, aq::FusedPlan*
     conv_staging(geo, p->kind, p->cm, bm, false, &q);
     q.upl = (wk * q.units + 255) / 256;
     if (p->kind == 1 ? q.upl > 3 : q.upl != 2) return false;
-    int bn = geo.C_out % 192 == 0 ? 192 : 128;
+    int bn = geo.C_out % 192 == 0 && max_bn >= 192 ? 192 : 128;
     if (opt.fused_bm == bm && (opt.fused_bn == 128 || opt.fused_bn == 192)) bn = opt.fused_bn;
     if (p->kind == 1 && wk == 2 && bn == 192 && q.upl > 2) bn = 128;   // registers (see the launcher)
     q.bm = bm;
@@ -897,7 +897,8 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
     //  * else, for 1x1 layers with M >= 4, 128-token tiles from 128 of them
     //    (the in-loop decode gathers 4 codewords per group).
     // Fewer tiles leave compute units idle: the fused kernel stays ahead; so
-    // does it for output rows under 16 tokens (the rule needs OW >= 16).
+    // does it for most output rows under 16 tokens (the rule needs OW >= 16, or
+    // enough 128 x 128 tiles, below).
     // Layers switch to records for it even where the in-loop decode was chosen
     // (3x3 at 8192 tokens, M = 2: 23.6 -> 20.8 us at K = 1728 -> 192 with
     // stride 2, 24.1 -> 21.7 us at K = 1728 -> 384).  AQ_OPT_RECORD_PRODUCT =
@@ -924,11 +925,26 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
             // short reduction repays; 8 x 64 x 64, M = 2: 3x3 576 -> 64 44.4 us here,
             // 32.2 on the fused kernel, 1x1 576 -> 64 17.6 and 14.2, but 53 x 64 x 64
             // 3x3 64 -> 64 42.0 and 50.0, 17 x 64 x 64 1x1 48 -> 32 9.1 and 17.5)
-            // (output rows under 16 tokens: this kernel does not widen its staged
-            // rows, and its fragment reads conflict; 8 x 8 images measured slower)
             if (ok1 && w1.ntiles >= (fp.kind == 1 ? 192 : 256)) pick = &w1;
             else if (ok2 && w2.ntiles >= 256 && fp.nchunk >= 8) pick = &w2;
             else if (ok1 && fp.kind == 2 && geo.M >= 4 && w1.ntiles >= 128) pick = &w1;
+        } else if (opt.rec_product == 0 && r.geo.OW < 16 && !r.uneven && fp.kind == 1 && geo.C_out > 64 &&
+                   geo.K <= 12000) {
+            // 3x3 on rows under 16 tokens: from 192 tiles of 128 x 128, up to where the
+            // fragment reads' conflicts even it out
+            // (8 x 8 images, records included: 64 x 960 -> 960, B = 16 82.6 against the
+            // fused kernel's 89.1 us, 128 x 512 -> 512 46.4 and 53.2, 64 x 256 -> 1024
+            // 26.6 and 35.2, 32 x 960 -> 960 with 128 tiles 61.8 and 46.7; 64 x 1920 ->
+            // 960, K = 17280, 145.5 and 144.9; widths that do not tile: 32 x 12 x 12,
+            // 960 -> 960 107 and 95).  192-channel tiles where they need fewer rounds of
+            // the 256 units per channel (512 x 4 x 4, 512 -> 768: 60.3 against 76.3 us
+            // at one round against two; 64 x 8 x 8, 960 -> 960 89.8 and 76.3 at one each)
+            aq::FusedPlan w128 = rp;
+            if (wsplit_plan(r.geo, opt, 1, &w128, 128) && w128.ntiles >= 192) {
+                const bool wide = ok1 && w1.bn == 192 && (w1.ntiles + 255) / 256 * 3 < (w128.ntiles + 255) / 256 * 2;
+                if (!wide) w1 = w128;
+                pick = &w1;
+            }
         }
         if (pick) {
             fp = *pick;

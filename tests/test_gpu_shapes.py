@@ -76,6 +76,20 @@ def test_uneven_convolutions(spec, weights):
         _check(spec, inp, y_gen)
 
 
+@pytest.mark.parametrize("spec", [
+    _conv("w8x8", 64, 16, 736, 3, 8, 8),                      # 192 tiles, the fewest; a partial channel tile, a half-empty chunk
+    _conv("w8x8_b12", 64, 16, 736, 3, 8, 8, M=1, B=12),        # records only
+    _conv("w4x4", 256, 32, 768, 3, 4, 4, M=4),                # 8 images to a tile
+    _conv("w8x8_s2", 64, 32, 768, 3, 16, 16, stride=2, y_dtype="f32"),
+    _conv("w4x4_192", 512, 16, 768, 3, 4, 4),                 # 256 tiles of 192 channels instead of 384 of 128
+], ids=lambda s: s.name)
+def test_narrow_images_on_the_wave_split_kernel(spec):
+    inp = generate(spec, 7004)
+    y, route = _forward(spec, inp)
+    assert route["route"] == "rec-conv" and route["tile"] == ("128x192" if spec.name.endswith("_192") else "128x128")
+    _check(spec, inp, y)
+
+
 def test_uneven_convolution_static_and_limits():
     """The allocation-free forward gives the forward's bits; g = 9 on an odd width stays refused."""
     import paper_2506_05960_amd as P
