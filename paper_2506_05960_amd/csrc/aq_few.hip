@@ -179,12 +179,15 @@ hipError_t few_cfg(const Geom& geo, const DeviceWeights& w, const void* X, const
 }
 
 // Rows per workgroup: the most that leave about three quarters of the compute
-// units a workgroup each.
+// units a workgroup each, and more where fewer rows give more workgroups than
+// LDS holds at once (a last round of a few workgroups: 4 tokens, 13152 -> 1403,
+// M = 1 14.7 us with 4 rows, 10.1 with 8; 17280 -> 2600 21.3 with 8, 15.6 with 16).
 template <int XT, int MC, int NT>
 hipError_t few_rows(const Geom& geo, const DeviceWeights& w, const void* X, const float* xs, void* Y, int y_dtype,
                     hipStream_t st) {
-    if (geo.C_out >= 16 * 192) return few_cfg<XT, MC, NT, 16>(geo, w, X, xs, Y, y_dtype, st);
-    if (geo.C_out >= 8 * 192) return few_cfg<XT, MC, NT, 8>(geo, w, X, xs, Y, y_dtype, st);
+    const int64_t at_once = 256 * (int64_t)std::min<size_t>(2, kFewLdsBytes / few_lds_bytes(geo, NT));
+    if (geo.C_out >= 16 * 192 || geo.C_out > 8 * at_once) return few_cfg<XT, MC, NT, 16>(geo, w, X, xs, Y, y_dtype, st);
+    if (geo.C_out >= 8 * 192 || geo.C_out > 4 * at_once) return few_cfg<XT, MC, NT, 8>(geo, w, X, xs, Y, y_dtype, st);
     return few_cfg<XT, MC, NT, 4>(geo, w, X, xs, Y, y_dtype, st);
 }
 

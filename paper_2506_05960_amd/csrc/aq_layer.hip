@@ -824,6 +824,17 @@ bool few_route(const aq_layer* L, const Geom& geo) {
         return false;
     if (o.table_one_launch || o.weights || o.generic || o.rec_product || o.fused_bm || o.split_k) return false;
     if (o.lut_max_tokens != 0 && geo.tokens > o.lut_max_tokens) return false;
+    // More rows than 16 per unit run a second round of workgroups, which long
+    // reductions do not repay (C_out = 4352, tokens x K, this kernel and the others:
+    // M = 4 1 x 4608 9.9 and 11.5, 1 x 8640 16.4 and 14.2, 4 x 4608 17.2 and 12.0;
+    // M = 2 4 x 8640 18.6 and 21.9, 1 x 17280 17.8 and 14.7; M = 1 4 x 13152 23.6 and
+    // 18.7; C_out = 10240, M = 2 4 x 1152 7.4 and 6.9).  With M = 4 a very long one
+    // is even over 2048 rows already (17280 -> 2600: 1 token 17.3 and 16.4).
+    if (geo.C_out > 4096) {
+        if (geo.M >= 2 && geo.tokens > 2 && geo.C_out > 8192) return false;
+        if (geo.M == 4 ? geo.tokens * geo.K > 4608 : geo.tokens * geo.K > 35000 || geo.K > 14000) return false;
+    }
+    if (geo.M == 4 && geo.K > 16000 && geo.C_out > 2048) return false;
     return geo.tokens * geo.K * geo.C_out <= (geo.M == 4 ? int64_t(100) * 1000000 : int64_t(300) * 1000000);
 }
 

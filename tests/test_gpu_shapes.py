@@ -265,6 +265,9 @@ FEW = [
     (20, 65536, 2, 8, 1, "f16", "f32"),       # the largest K that fits LDS, nearly
     (1541, 520, 2, 8, 4, "f16", "f32"),       # eight rows per workgroup, a partial tile
     (3077, 264, 4, 8, 2, "i8", "f16"),        # sixteen
+    (1030, 13152, 1, 8, 4, "i8", "f16"),      # eight, as LDS holds one workgroup of more than 256
+    (2060, 13152, 1, 8, 3, "f16", "f32"),     # sixteen, likewise
+    (4100, 264, 4, 8, 4, "f16", "f32"),       # more rows than sixteen per unit
 ]
 
 
