@@ -708,6 +708,18 @@ bool small_weights(const Geom& geo, const aq::FusedPlan& p) {
            (int64_t)geo.K * geo.C_out <= 50000;
 }
 
+// The product kernels index records and code records with 32-bit byte offsets,
+// of which those from 2^31 up stand for loads that return zeros.
+constexpr int64_t kOffsetLimit = int64_t(1) << 31;
+
+bool records_fit(const Geom& geo, const aq::FusedPlan& p) {
+    return (int64_t)aq::operand_record_bytes(geo, p) < kOffsetLimit;
+}
+
+bool code_records_fit(const Geom& geo, const aq::FusedPlan& p) {
+    return (int64_t)p.nchunk * geo.C_out * 2 * p.rec_bytes < kOffsetLimit;
+}
+
 // Pre-decoded mode (operands decoded once per forward into records the main
 // loop reads with plain 16-byte loads) instead of decoding inside the main
 // loop: chosen for codebooks too large for LDS (their codeword reads from L2
@@ -866,14 +878,18 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
         // (24-bit factors) before the byte offsets do
         const int64_t lim24 = int64_t(1) << 24;
         fits31 = fits31 && geo.tokens < lim24 && nimg * ((geo.OH - 1) * (int64_t)geo.stride + geo.kh) < lim24 &&
-                 nimg * geo.cin < lim24 && (int64_t)geo.C_out * geo.K * 2 < (int64_t(1) << 31);
+                 nimg * geo.cin < lim24;
         // other codebook types decode their records value by value and keep the generic kernel
         if (geo.g != 8 || d.codebook_dtype != AQ_F16) fits31 = false;
         // 1x1 on planes of an odd pixel count with few channels: one launch of the
         // generic kernel is faster (2 x 15 x 15, 64 -> 64: 11.7 against 14.3 us)
         if (geo.kh == 1 && r.geo.W % 2 != 0 && geo.K <= 128) fits31 = false;
     }
-    if (L->fused_ok && use_predecoded(L, geo)) {
+    // records too large to index: the in-loop decode, or the generic kernel for
+    // formats without one (g = 9: refused)
+    const bool rec_fit = L->fused_ok && records_fit(geo, L->fplan);
+    if (L->fused_ok && !(L->fplan.rec_only ? rec_fit : code_records_fit(geo, L->fplan))) fits31 = false;
+    if (rec_fit && use_predecoded(L, geo)) {
         // pre-decoded mode: operands decoded once per forward, then read with plain loads
         fp.dec = aq::FUSED_DEC_REC;
         fp.mc = 1;
@@ -918,7 +934,7 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
     // keeps a layer on the in-loop decode.
     bool planned = false;
     const bool ws_switch =
-        fp.kind != 0 && fp.dec != aq::FUSED_DEC_REC && opt.weights == 0 && !small_weights(geo, L->fplan);
+        fp.kind != 0 && fp.dec != aq::FUSED_DEC_REC && rec_fit && opt.weights == 0 && !small_weights(geo, L->fplan);
     if (L->fused_ok && fits31 && opt.generic != 1 && fp.kind != 0 && (fp.dec == aq::FUSED_DEC_REC || ws_switch) &&
         (opt.rec_product == 3 || opt.rec_product == 0)) {
         aq::FusedPlan rp = fp;
@@ -964,7 +980,7 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
     }
     if (!planned && L->fused_ok && fits31 && opt.generic != 1)
         planned = fused_plan_tile(r.geo, opt, L->part_bytes, d.x_dtype, &fp);
-    if (!planned && r.uneven && fits31 && opt.generic != 1 && fp.dec != aq::FUSED_DEC_REC && opt.weights != 1) {
+    if (!planned && r.uneven && fits31 && rec_fit && opt.generic != 1 && fp.dec != aq::FUSED_DEC_REC && opt.weights != 1) {
         // long output rows stage more pixels than the in-loop tiles hold
         fp.dec = aq::FUSED_DEC_REC;
         fp.mc = 1;
@@ -1326,7 +1342,8 @@ aq_status aq_layer_create(const aq_layer_desc* desc, const void* codebooks, cons
             AQ_TRY(dev_upload(&L->d_crec, rec.data(), rec.size(), "fused code records"));
         }
         const Geom g1 = make_geom(L, 1);
-        AQ_TRY(dev_upload(&L->d_wrec, nullptr, aq::operand_record_bytes(g1, L->fplan), "operand records"));
+        if (records_fit(g1, L->fplan))
+            AQ_TRY(dev_upload(&L->d_wrec, nullptr, aq::operand_record_bytes(g1, L->fplan), "operand records"));
         // the dense product's repacked activations (convolution, int8 input) and a zero block
         size_t xpack = 0;
         if (is_conv(*desc)) {

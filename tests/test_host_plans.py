@@ -1,0 +1,50 @@
+"""Routes, limits, refusals and workspaces of calls, planned on the host without a GPU (see host_device.py)."""
+import pytest
+
+import host_device as hd
+
+
+@pytest.fixture(scope="session")
+def child(tmp_path_factory):
+    so = hd.build(tmp_path_factory)
+    return lambda function, *args: hd.in_child(so, "test_host_plans", function, *args)
+
+
+# ---- weight records past the product kernels' 32-bit byte offsets ----
+
+def _large_records(n, options, kw):
+    before = hd.live_bytes()
+    layer = hd.Layer(max_n=n, **kw)
+    held = hd.live_bytes() - before
+    return layer.set(**options).describe(n), layer.forward(n), held
+
+
+BIG = 131136     # outputs: with K = 8192 the records hold 2.15 GB
+
+
+@pytest.mark.parametrize("n,options,kw,route,weights", [
+    (64, {}, dict(C_out=BIG, K=8192, M=1, B=16, x="bf16", cb="bf16", tile="bf16", y="f32"), "generic", None),
+    (64, {}, dict(C_out=BIG, K=8192, M=3, x="bf16", cb="bf16", tile="bf16"), "generic", None),
+    (64, {}, dict(C_out=BIG, K=8192, M=3), "generic", None),                            # fp16, records only
+    (4, {"weights": 2, "lut_max_tokens": -1}, dict(C_out=BIG, K=8192, M=2, x="i8"), "fused", "in-loop-lds-fp16"),
+    (1024, {}, dict(C_out=BIG, K=8192, M=1, B=16), "fused", "in-loop-l2-fp16"),         # records where they fit
+    (4, {}, dict(C_out=28800, M=1, B=16, conv=(4352, 3, 1, 1, 16, 16)), "fused", "in-loop-l2-fp16"),
+    (64, {}, dict(C_out=131008, K=8192, M=1, B=16, x="bf16", cb="bf16", tile="bf16"), "rec-linear", "records"),   # just below
+])
+def test_records_past_32_bit_offsets(child, n, options, kw, route, weights):
+    """Records of 2 GiB and more are not indexable by the kernels that read them: such layers decode in the loop or,
+    where their format has no such decode, run the generic kernel; no buffer is held for records that never exist."""
+    d, kernels, held = child("_large_records", n, options, kw)
+    assert (d["route"], d.get("weights")) == (route, weights)
+    if weights != "records":
+        assert kernels == [{"generic": "mfma_fwd_kernel", "fused": "fused_fwd_kernel"}[route]]
+        assert held < 2**31
+
+
+def test_g9_records_past_32_bit_offsets_are_refused(child):
+    kw = dict(C_out=28800, M=2, g=9, conv=(4160, 3, 1, 1, 16, 16))
+    assert child("_large_records_g9", kw) == "AQ_ERR_UNSUPPORTED"
+
+
+def _large_records_g9(kw):
+    return hd.Layer(max_n=1, **kw).set(lut_max_tokens=-1).forward(1)
