@@ -873,12 +873,14 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
                   (!geo.conv || nimg * (int64_t)geo.cin * geo.H * geo.W * 2 < (int64_t(1) << 31));
     r.geo = kernel_geom(geo);
     r.uneven = geo.conv && L->fused_ok && !even_tiles(geo, L->fplan);
-    if (r.uneven) {
-        // small images of few channels can pass what the index arithmetic takes
-        // (24-bit factors) before the byte offsets do
+    if (geo.conv) {
+        // what the index arithmetic multiplies is below 2^24; few pixels per image or
+        // tall strided images can pass that before the byte offsets pass theirs
         const int64_t lim24 = int64_t(1) << 24;
-        fits31 = fits31 && geo.tokens < lim24 && nimg * ((geo.OH - 1) * (int64_t)geo.stride + geo.kh) < lim24 &&
-                 nimg * geo.cin < lim24;
+        fits31 = fits31 && geo.tokens < lim24 && r.geo.H < lim24 && nimg * geo.cin < lim24 &&
+                 nimg * ((r.geo.OH - 1) * (int64_t)geo.stride + geo.kh) < lim24;
+    }
+    if (r.uneven) {
         // other codebook types decode their records value by value and keep the generic kernel
         if (geo.g != 8 || d.codebook_dtype != AQ_F16) fits31 = false;
         // 1x1 on planes of an odd pixel count with few channels: one launch of the

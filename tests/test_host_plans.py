@@ -48,3 +48,20 @@ def test_g9_records_past_32_bit_offsets_are_refused(child):
 
 def _large_records_g9(kw):
     return hd.Layer(max_n=1, **kw).set(lut_max_tokens=-1).forward(1)
+
+
+# ---- convolutions past the kernels' 24-bit index arithmetic ----
+
+def _conv_limit(n, options, kw):
+    return hd.Layer(max_n=n, **kw).set(lut_max_tokens=-1, **options).forward(n)
+
+
+@pytest.mark.parametrize("n,options,kw,kernels", [
+    # 2^25 (image, channel) planes of 2 x 2 pixels, and just below 2^24 of them
+    (1 << 19, {}, dict(C_out=64, conv=(64, 1, 1, 0, 2, 2)), ["mfma_fwd_kernel"]),
+    ((1 << 18) - 1, {"weights": 1}, dict(C_out=64, conv=(64, 1, 1, 0, 2, 2)), ["fused_fwd_kernel"]),
+    # odd widths, as before
+    (1 << 20, {}, dict(C_out=8, conv=(16, 3, 2, 1, 3, 3)), ["mfma_fwd_kernel"]),
+])
+def test_convolutions_past_24_bit_indices(child, n, options, kw, kernels):
+    assert child("_conv_limit", n, options, kw) == kernels
