@@ -394,10 +394,47 @@ bool fused_plan_create(const aq_layer_desc& d, int g, int M, int B, aq::FusedPla
     return true;
 }
 
+float host_f32(const void* p, int dtype, size_t i) {
+    if (dtype == AQ_F32) return static_cast<const float*>(p)[i];
+    const uint16_t b = static_cast<const uint16_t*>(p)[i];
+    if (dtype == AQ_F16) return (float)__builtin_bit_cast(_Float16, b);
+    return __builtin_bit_cast(float, (uint32_t)b << 16);
+}
+
+// The codes that fill a last chunk past K.  Its activations are zeros there,
+// and 0 * w is 0 for every finite w only: a code that no row selects must not
+// bring an infinite or NaN codeword into a product.  Taken per codebook is the
+// codeword of smallest magnitude; false where the sum of these is not surely
+// finite in the tile's type (the layer then decodes records, which hold zeros
+// past K).
+bool padding_codes(const void* cb, int cb_dtype, int tile, int g, int M, int B, uint16_t (&pad)[8]) {
+    const size_t nk = size_t(1) << B;
+    float sum = 0.0f;
+    for (int m = 0; m < M; ++m) {
+        float best = INFINITY;
+        pad[m] = 0;
+        for (size_t k = 0; k < nk; ++k) {
+            float mag = 0.0f;
+            for (int t = 0; t < g; ++t) {
+                const float v = std::fabs(host_f32(cb, cb_dtype, (m * nk + k) * g + t));
+                mag = v < INFINITY ? std::max(mag, v) : INFINITY;   // a NaN as well
+                if (mag == INFINITY) break;
+            }
+            if (mag < best) {
+                best = mag;
+                pad[m] = (uint16_t)k;
+            }
+        }
+        sum += best;
+    }
+    return sum < (tile == AQ_BF16 ? 3.3e38f : 65504.0f);
+}
+
 // Code records: for chunk c, output channel n and lane half q, the M codes of
 // every group the lane decodes, in decode order (8-bit codes, or 16-bit codes
-// when B > 8), padded to whole dwords.
-std::vector<uint8_t> fused_records(const aq::FusedPlan& p, const void* codes, int C_out, int G, int M, int B) {
+// when B > 8; `pad` for groups past K), padded to whole dwords.
+std::vector<uint8_t> fused_records(const aq::FusedPlan& p, const void* codes, int C_out, int G, int M, int B,
+                                   const uint16_t (&pad)[8]) {
     const int ns = p.kind == 1 ? 9 : p.cm;
     const int ent_b = B > 8 ? 2 : 1;
     std::vector<uint8_t> rec((size_t)p.nchunk * C_out * 2 * p.rec_bytes, 0);
@@ -407,11 +444,12 @@ std::vector<uint8_t> fused_records(const aq::FusedPlan& p, const void* codes, in
                 uint8_t* r = rec.data() + (((size_t)c * C_out + n) * 2 + q) * p.rec_bytes;
                 for (int s = 0; s < ns; ++s) {
                     const int j = p.kind == 1 ? 18 * c + 9 * q + s : c * 2 * p.cm + 2 * s + q;
-                    if (j >= G) continue;
                     for (int m = 0; m < M; ++m) {
                         const size_t src = ((size_t)n * G + j) * M + m;
-                        if (ent_b == 1) r[s * M + m] = static_cast<const uint8_t*>(codes)[src];
-                        else std::memcpy(r + 2 * (s * M + m), static_cast<const uint16_t*>(codes) + src, 2);
+                        const uint16_t code = j >= G        ? pad[m]
+                                              : ent_b == 1 ? static_cast<const uint8_t*>(codes)[src]
+                                                           : static_cast<const uint16_t*>(codes)[src];
+                        std::memcpy(r + ent_b * (s * M + m), &code, (size_t)ent_b);   // little-endian
                     }
                 }
             }
@@ -1253,6 +1291,13 @@ aq_status aq_layer_create(const aq_layer_desc* desc, const void* codebooks, cons
     const bool lut_ok = B <= 8;
     aq::FusedPlan fplan;
     const bool fused_ok = fused_plan_create(*desc, g, M, B, &fplan);
+    uint16_t pad[8] = {};
+    if (fused_ok && !fplan.rec_only && G % (2 * fplan.cm) != 0 && !is_conv(*desc) &&
+        !padding_codes(codebooks, desc->codebook_dtype, fplan.tile, g, M, B, pad)) {
+        fplan.dec = aq::FUSED_DEC_REC;
+        fplan.cb_bytes = 0;
+        fplan.rec_only = 1;
+    }
     const bool dec_ok = desc->tile_dtype == AQ_F32 || g == 8 || fused_ok;
     if (!lut_ok && !dec_ok)
         return fail(AQ_ERR_UNSUPPORTED, "no kernel for this format: LUT needs B <= 8; the fp16/bf16 decode needs "
@@ -1340,7 +1385,7 @@ aq_status aq_layer_create(const aq_layer_desc* desc, const void* codebooks, cons
         // code records: what the in-loop decode and the fp16 g = 8 records kernel read
         if (!fplan.rec_only || (g == 8 && fplan.tile == AQ_F16 && desc->codebook_dtype == AQ_F16 &&
                                 (M == 1 || M == 2 || M == 4))) {
-            std::vector<uint8_t> rec = fused_records(L->fplan, codes, C_out, G, M, B);
+            std::vector<uint8_t> rec = fused_records(L->fplan, codes, C_out, G, M, B, pad);
             AQ_TRY(dev_upload(&L->d_crec, rec.data(), rec.size(), "fused code records"));
         }
         const Geom g1 = make_geom(L, 1);

@@ -308,3 +308,58 @@ def test_few_token_infinite_codeword():
     y = layer.forward(torch.from_numpy(inp["x"]).cuda()).cpu().numpy()
     layer.close()
     assert np.all(np.isposinf(y[:, 4])) and np.all(np.isfinite(np.delete(y, 4, axis=1)))
+
+
+PAD = [
+    # (M, B, dtype, K): in-loop formats of a linear layer whose last 64-wide chunk is partly empty
+    (1, 8, "f16", 72),
+    (2, 4, "f16", 200),
+    (4, 8, "f16", 56),
+    (1, 12, "f16", 72),                       # codewords from memory
+    (1, 8, "bf16", 72),
+    (2, 8, "bf16", 200),
+    (4, 4, "bf16", 88),
+]
+
+
+@pytest.mark.parametrize("weights", [1, 2])
+@pytest.mark.parametrize("case", PAD, ids=lambda c: "x".join(str(v) for v in c))
+def test_codeword_of_no_row_past_k(case, weights):
+    """An infinite or NaN codeword that no code selects reaches no output: not through the codes past K either."""
+    import paper_2506_05960_amd as P
+    M, B, dt, K = case
+    spec = LayerSpec(name="pad", C_out=40, K=K, g=8, M=M, B=B, n=70, codebook_dtype=dt, x_dtype=dt, y_dtype="f32",
+                     tile_dtype=dt)
+    inp = generate(spec, 7501)
+    inp["codes"][inp["codes"] == 0] = 1
+    clean = {k: np.copy(v) for k, v in inp.items() if v is not None} | {"x_scales": None}
+    inp["codebooks"][:, 0] = np.array([np.inf, -np.inf, np.nan, np.inf] * 2, np.float16) if dt == "f16" else 0x7F80
+    x = torch.from_numpy(inp["x"].view(np.int16)).cuda().view(torch.bfloat16) if dt == "bf16" else torch.from_numpy(inp["x"]).cuda()
+    ys = []
+    for w in (inp, clean):
+        layer = P.AQLayer(spec, w)
+        layer.set_path("decode")
+        layer.set_option("weights", weights)
+        d = layer.describe(spec.n)
+        print(case, d, flush=True)
+        assert d["route"] in ("fused", "rec-linear") and d["weights"].startswith("in-loop" if weights == 1 else "records")
+        ys.append(layer.forward(x))
+        layer.close()
+    assert bool(torch.isfinite(ys[0]).all()) and torch.equal(ys[0], ys[1])
+
+
+def test_codewords_too_large_to_pad_take_records():
+    """No code's padding sum is surely finite: the layer decodes records, which hold zeros past K."""
+    import paper_2506_05960_amd as P
+    spec = LayerSpec(name="pad_big", C_out=40, K=72, g=8, M=4, B=4, n=70, y_dtype="f32")
+    inp = generate(spec, 7502)
+    signs = np.array([1.0, -1.0, 1.0, -1.0])[:, None, None]
+    inp["codebooks"] = (signs * 30000.0 + 2000.0 * inp["codebooks"].astype(np.float64)).astype(np.float16)
+    layer = P.AQLayer(spec, inp)
+    layer.set_path("decode")
+    layer.set_option("weights", 1)
+    assert layer.describe(spec.n)["weights"] == "records"
+    y = layer.forward(torch.from_numpy(inp["x"]).cuda()).double().cpu().numpy()
+    layer.close()
+    tok, ch = np.arange(spec.n), np.arange(spec.C_out)
+    check_against_oracle(spec, inp, y, tok, ch, "decode", TOL)
