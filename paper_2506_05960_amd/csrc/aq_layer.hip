@@ -845,6 +845,27 @@ bool wsplit_plan(const Geom& geo, const aq::Options& opt, int wk, aq::FusedPlan*
     return true;
 }
 
+// The static array of the allocation-free forward.
+constexpr size_t kScratchBytes = size_t(64) << 20;             // per GPU
+constexpr size_t kScratchCounterBytes = size_t(256) << 10;     // arrival counters first (table, then K split)
+constexpr size_t kScratchLutCounters = 0;
+constexpr size_t kScratchSplitCounters = size_t(128) << 10;
+constexpr int kScratchMaxDevices = 64;
+
+size_t align256(size_t b) { return (b + 255) / 256 * 256; }
+
+// Scratch of a fused-kernel or record-product plan within the static array's data area.
+size_t plan_scratch(const Geom& geo, const aq::FusedPlan& p) {
+    return (p.dec == aq::FUSED_DEC_REC ? align256(aq::operand_record_bytes(geo, p)) : 0) +
+           (p.splitk > 1 ? align256((size_t)p.splitk * p.ntiles * p.bm * p.bn * 4) : 0);
+}
+
+// The records alone fit the static array, the partial tiles beside them do not.
+bool static_refuses_split(const Geom& geo, const aq::FusedPlan& p) {
+    const size_t cap = kScratchBytes - kScratchCounterBytes;
+    return aq::operand_record_bytes(geo, p) <= cap && plan_scratch(geo, p) > cap;
+}
+
 struct Route {
     enum Kind { LUT = 0, F32 = 1, GENERIC = 2, DENSE = 3, FUSED = 4, REC_LINEAR = 5, NONE = 6, FEW = 7 } kind;
     aq::FusedPlan fp;
@@ -1038,7 +1059,10 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
         // the fused kernel keeps more units busy (M = 3: 8 tokens x 2256 -> 64 22.5
         // against 11.3 us, 1000 x 1152 -> 1152, 72 tiles, 19.1 against 16.3).
         const int64_t rtiles = ((geo.tokens + 127) / 128) * (int64_t)((geo.C_out + 127) / 128);
-        const bool few_tiles = L->fplan.rec_only && opt.rec_product == 0 && rtiles < 88;
+        // (where the records fit the static array and the partial tiles beside them do
+        // not, the linear kernel keeps the allocation-free forward possible)
+        const bool few_tiles = L->fplan.rec_only && opt.rec_product == 0 && rtiles < 88 &&
+                               (fp.splitk == 1 || !static_refuses_split(geo, fp));
         const bool rlin = fp.dec == aq::FUSED_DEC_REC && opt.rec_product != 1 && !few_tiles &&
                           aq::rec_linear_supported(geo, fp, d.x_dtype);
         r.kind = rlin ? Route::REC_LINEAR : Route::FUSED;
@@ -1164,14 +1188,6 @@ aq_status run_route(aq_layer* L, const Geom& geo, const Route& r, const void* X,
     return AQ_OK;
 }
 
-// ---- allocation-free forward: scratch in a static device array ----
-
-constexpr size_t kScratchBytes = size_t(64) << 20;             // per GPU
-constexpr size_t kScratchCounterBytes = size_t(256) << 10;     // arrival counters first (table, then K split)
-constexpr size_t kScratchLutCounters = 0;
-constexpr size_t kScratchSplitCounters = size_t(128) << 10;
-constexpr int kScratchMaxDevices = 64;
-
 }  // namespace
 
 // The scratch of aq_layer_forward_static.  Every GPU the library runs on holds
@@ -1216,8 +1232,6 @@ aq_status scratch_for_current_device(hipStream_t st, uint8_t** out) {
     *out = sd.ptr;
     return AQ_OK;
 }
-
-size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
 // Lay the route's scratch out in the static array, or refuse.
 aq_status static_workspace(const aq_layer* L, const Geom& geo, const Route& r, uint8_t* base, Workspace* wk) {

@@ -65,3 +65,22 @@ def _conv_limit(n, options, kw):
 ])
 def test_convolutions_past_24_bit_indices(child, n, options, kw, kernels):
     assert child("_conv_limit", n, options, kw) == kernels
+
+
+# ---- the allocation-free forward's static array ----
+
+def _static(n, kw):
+    layer = hd.Layer(max_n=n, **kw)
+    return layer.forward(n), layer.forward(n, static=True)
+
+
+@pytest.mark.parametrize("kw,product", [
+    # 65.5 MB of records fit the array's 66.8, the 2 MB of a K split's partial tiles beside them do not
+    (dict(C_out=4000, K=8192, M=3), "rec_linear_kernel"),
+    (dict(C_out=4000, K=8192, M=3, x="bf16", cb="bf16", tile="bf16"), "rec_linear_kernel"),
+    (dict(C_out=3000, K=8192, M=3), "fused_fwd_kernel"),      # both fit
+])
+def test_static_forward_of_records_only_layers(child, kw, product):
+    """A call that the array's records allow is not refused for partial tiles, and takes the forward's kernels."""
+    forward, static = child("_static", 8, kw)
+    assert forward == static and static[-1] == product
