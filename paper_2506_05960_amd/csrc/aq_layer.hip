@@ -1003,7 +1003,12 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
         rp.mc = 1;
         rp.cb_bytes = 0;
         aq::FusedPlan w1 = rp, w2 = rp;
-        const bool ok1 = wsplit_plan(r.geo, opt, 1, &w1), ok2 = wsplit_plan(r.geo, opt, 2, &w2);
+        // (a layer with output rows under 16 pixels keeps its in-loop decode, and with it
+        // the allocation-free forward, where the static array cannot hold its records)
+        const bool may_switch = !ws_switch || geo.OW >= 16 || r.uneven ||
+                                plan_scratch(geo, rp) <= kScratchBytes - kScratchCounterBytes;
+        const bool ok1 = may_switch && wsplit_plan(r.geo, opt, 1, &w1);
+        const bool ok2 = may_switch && wsplit_plan(r.geo, opt, 2, &w2);
         const aq::FusedPlan* pick = nullptr;
         if (opt.rec_product == 3 && !ws_switch) {
             if (!r.uneven && (opt.fused_bm == 64 ? ok2 : ok1)) pick = opt.fused_bm == 64 ? &w2 : &w1;
@@ -1016,7 +1021,7 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
             if (ok1 && w1.ntiles >= (fp.kind == 1 ? 192 : 256)) pick = &w1;
             else if (ok2 && w2.ntiles >= 256 && fp.nchunk >= 8) pick = &w2;
             else if (ok1 && fp.kind == 2 && geo.M >= 4 && w1.ntiles >= 128) pick = &w1;
-        } else if (opt.rec_product == 0 && r.geo.OW < 16 && !r.uneven && fp.kind == 1 && geo.C_out > 64 &&
+        } else if (may_switch && opt.rec_product == 0 && r.geo.OW < 16 && !r.uneven && fp.kind == 1 && geo.C_out > 64 &&
                    geo.K <= 12000) {
             // 3x3 on rows under 16 tokens: from 192 tiles of 128 x 128, up to where the
             // fragment reads' conflicts even it out

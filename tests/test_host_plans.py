@@ -84,3 +84,17 @@ def test_static_forward_of_records_only_layers(child, kw, product):
     """A call that the array's records allow is not refused for partial tiles, and takes the forward's kernels."""
     forward, static = child("_static", 8, kw)
     assert forward == static and static[-1] == product
+
+
+@pytest.mark.parametrize("n,kw,product", [
+    # in-loop layers that take records for the wave-split kernel: 3x3 on rows under 16 pixels, and 1x1 on small
+    # planes read as longer rows
+    (16, dict(C_out=8192, M=2, conv=(512, 3, 1, 1, 8, 8)), "fused_fwd_kernel"),       # 75 MB of records
+    (16, dict(C_out=2048, M=2, conv=(512, 3, 1, 1, 8, 8)), "fused_fwd_kernel"),       # 19 MB, too few tiles
+    (24, dict(C_out=2048, M=2, conv=(512, 3, 1, 1, 8, 8)), "rec_conv_kernel"),
+    (256, dict(C_out=8192, M=2, conv=(4160, 1, 1, 0, 8, 8)), "fused_fwd_kernel"),     # 68 MB
+    (256, dict(C_out=2048, M=2, conv=(1024, 1, 1, 0, 8, 8)), "rec_conv_kernel"),      # 4 MB
+])
+def test_static_forward_of_layers_switched_to_records(child, n, kw, product):
+    forward, static = child("_static", n, kw)
+    assert forward == static and static[-1] == product
