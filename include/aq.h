@@ -165,14 +165,20 @@ aq_status aq_layers_prepare(aq_layer* const* layers, const int64_t* n, int32_t c
  * during the call or keep per-layer workspace (code under HIP graph capture,
  * tight serving loops, harnesses that forbid allocation).  Arguments,
  * validation, route, kernels and results (bit for bit) are those of
- * aq_layer_forward; the per-call scratch of the kernels -- the table path's
+ * aq_layer_forward, but for one case (below); the per-call scratch of the kernels -- the table path's
  * partial sums and arrival counters, the fused kernel's K-split partial tiles
  * and arrival counters, the pre-decoded operand records and the dense
  * product's repacked activations -- lives in one static device array of the
  * library (64 MiB per GPU, 256 KiB of it counters) instead of the layer's
  * workspace.  It calls no hipMalloc, hipFree or allocating library routine.
  * A call whose scratch would exceed the array returns AQ_ERR_UNSUPPORTED
- * before launching anything.  The first call on a device resolves the
+ * before launching anything, except where aq_layer_forward's route over
+ * records stands in for the generic decode kernel, which needs no scratch:
+ * convolutions whose images do not tile (an odd width, C_in no multiple of a
+ * channel chunk, or output rows that neither divide 128 nor are a multiple of
+ * 64) and linear layers with bf16 tiles.  These then run the generic kernel:
+ * the same weights, the products summed in another order (the results are
+ * those of AQ_OPT_GENERIC = 1, bit for bit).  The first call on a device resolves the
  * array's address and clears its counters with a small kernel on `stream`.
  * Every call on one GPU shares that GPU's array: calls that overlap on one
  * GPU (other streams, other threads) race; serialise them.

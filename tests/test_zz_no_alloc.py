@@ -2,7 +2,9 @@
 
 Same layer, same inputs: the two entry points take the same route and plan,
 so their outputs must be identical bit for bit (stronger than the oracle
-tolerance, which both meet; the oracle comparison is made too).  Two calls in
+tolerance, which both meet; the oracle comparison is made too).  The one
+exception, records beyond the array on a route that stands in for the generic
+kernel, gives that kernel's bits.  Two calls in
 a row per layer, the second with a smaller input, exercise the shared static
 scratch being reused with other sizes; a layer whose scratch would not fit is
 refused before anything is launched.
@@ -109,4 +111,42 @@ def test_static_forward_refuses_scratch_beyond_the_array():
         layer.forward(x, out=y, static=True)
     torch.cuda.synchronize()
     assert bool((y == 7.0).all())            # nothing was launched
+    layer.close()
+
+
+@pytest.mark.parametrize("spec", [
+    # 67 MiB of records each: a bf16 linear layer, and a convolution whose rows do not tile
+    LayerSpec(name="st_generic_bf16", C_out=4288, K=8192, g=8, M=1, B=12, n=70, codebook_dtype="bf16", x_dtype="bf16",
+              y_dtype="f32", tile_dtype="bf16"),
+    LayerSpec(name="st_generic_uneven", C_out=1700, K=2304 * 9, g=8, M=3, B=6, n=1, y_dtype="f32",
+              conv=ConvGeom(2304, 3, 3, 1, 1, 3, 10)),
+], ids=lambda s: s.name)
+def test_static_forward_generic_where_records_pass_the_array(spec):
+    """The allocation-free forward runs the generic kernel, with the bits it gives when it is asked for."""
+    import paper_2506_05960_amd as P
+    inp = generate(spec, 811)
+    layer = P.AQLayer(spec, inp)
+    bf16 = spec.x_dtype == "bf16"
+    x = _dev(inp["x"].view(np.int16)).view(torch.bfloat16) if bf16 else _dev(inp["x"])
+    d = layer.describe(spec.n)
+    assert d["weights"] == "records" and int(d["records_bytes"]) > 64 * 2**20
+    y = layer.forward(x)
+    names = [k.split("<")[0] for k in layer.last_launches()[1]]
+    assert names[-1] == "fused_fwd_kernel", names
+    y_st = layer.forward(x, static=True)
+    assert [k.split("<")[0] for k in layer.last_launches()[1]] == ["mfma_fwd_kernel"]
+    layer.set_option("generic", 1)
+    assert torch.equal(y_st, layer.forward(x))
+    # both products are fp32 sums of the same K terms: each within K 2^-24 sum |x w| of the exact one
+    w = O.decode_emulate(inp["codebooks"], inp["codes"], inp["scales"], 8, spec.codebook_dtype, spec.tile_dtype, scaled=False)
+    w = (torch.from_numpy(w.view(np.int16)).view(torch.bfloat16) if bf16 else torch.from_numpy(w)).double()
+    w = (w * torch.from_numpy(inp["scales"]).double()[:, None]).cuda()
+    if spec.conv is None:
+        xm = x.double()
+    else:
+        xm = torch.nn.functional.unfold(x.double(), (3, 3), padding=1)[0].t()
+        y, y_st = (v[0].reshape(spec.C_out, -1).t() for v in (y, y_st))
+    bound = 4 * spec.K * 2.0**-24 * (xm.abs() @ w.abs().t())
+    ref = xm @ w.t()
+    assert torch.all((y.double() - ref).abs() <= bound) and torch.all((y_st.double() - ref).abs() <= bound)
     layer.close()
