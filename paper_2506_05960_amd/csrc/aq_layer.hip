@@ -104,7 +104,7 @@ struct aq_layer {
     size_t gpart_bytes;       // bytes allocated at d_gpart
     bool lut_ok, dec_ok, fused_ok;
     aq_path path;
-    aq_layer_plan* planned;   // route of the last forward's n (made by the first forward)
+    aq_layer_plan* planned;   // route of the last forward's n
     int64_t lut_max_tokens;   // the measured rule for this layer
     aq::Options opt;
     std::vector<hipEvent_t> events;   // caller's timing events (aq_layer_set_launch_events)
@@ -1092,15 +1092,14 @@ void free_plan(aq_layer* L) { delete L->planned; }
 // The route of a forward over n tokens or images.  A program's forwards of a
 // layer mostly repeat one n; planning (every tile and K split priced, with
 // occupancy look-ups) costs more host time than a small layer's kernel.
-Route forward_route(aq_layer* L, const Geom& geo, int64_t n) {
-    if (!L->planned) L->planned = new (std::nothrow) aq_layer_plan();
-    if (!L->planned) return plan_route(L, geo);
-    if (L->planned->n != n) {
-        L->planned->n = 0;
-        L->planned->route = plan_route(L, geo);
-        L->planned->n = n;
+const Route& forward_route(aq_layer* L, const Geom& geo, int64_t n) {
+    aq_layer_plan& p = *L->planned;
+    if (p.n != n) {
+        p.n = 0;
+        p.route = plan_route(L, geo);
+        p.n = n;
     }
-    return L->planned->route;
+    return p.route;
 }
 
 // Where a forward's per-call scratch lives: the layer's workspace, or the
@@ -1345,6 +1344,12 @@ aq_status aq_layer_create(const aq_layer_desc* desc, const void* codebooks, cons
     if (e != hipSuccess) {
         free_layer(L);
         return hip_fail(e, "hipGetDevice");
+    }
+
+    L->planned = new (std::nothrow) aq_layer_plan();
+    if (!L->planned) {
+        free_layer(L);
+        return fail(AQ_ERR_OUT_OF_MEMORY, "route plan");
     }
 
     const size_t cb_elems = (size_t)M * nk * g;
@@ -1748,14 +1753,14 @@ aq_status aq_layer_set_path(aq_layer* L, aq_path path) {
     if (path == AQ_PATH_DECODE && !L->dec_ok)
         return fail(AQ_ERR_UNSUPPORTED, "fp16/bf16 decode path needs g == 8 (or g == 9 on a 3x3 convolution)");
     L->path = path;
-    if (L->planned) L->planned->n = 0;
+    L->planned->n = 0;
     return AQ_OK;
 }
 
 aq_status aq_layer_set_option(aq_layer* L, int32_t option, int64_t value) {
     if (!L) return fail(AQ_ERR_INVALID_ARGUMENT, "null layer");
     aq::Options& o = L->opt;
-    if (L->planned) L->planned->n = 0;
+    L->planned->n = 0;
     auto in = [&](int64_t lo, int64_t hi) { return value >= lo && value <= hi; };
     auto bad = [&]() { return fail(AQ_ERR_INVALID_ARGUMENT, "option " + std::to_string(option) +
                                                                 ": value " + std::to_string(value) + " out of range"); };

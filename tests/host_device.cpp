@@ -1,7 +1,7 @@
 // A device that lives in host memory, for tests of the library's host path on
 // a machine without a GPU: the HIP calls libaq.so makes, with allocations in
 // (lazily committed) host memory and launches that are checked against the
-// launch limits and recorded, but run nothing.  Loaded into the global symbol
+// launch limits but run nothing.  Loaded into the global symbol
 // scope before libaq.so, its functions are the ones the library binds to.
 #include <cstddef>
 #include <cstdint>
@@ -9,7 +9,6 @@
 #include <cstring>
 #include <map>
 #include <new>
-#include <vector>
 
 #include <sys/mman.h>
 
@@ -27,8 +26,8 @@ constexpr int kOk = 0, kInvalidValue = 1, kInvalidConfiguration = 9, kOutOfMemor
 
 std::map<void*, size_t> g_live;
 size_t g_live_bytes = 0;
-int64_t g_mallocs = 0, g_news = 0;
-std::vector<Launch> g_launches;
+int64_t g_news = 0;
+Launch g_launch;
 struct Config {
     Dim grid, block;
     size_t lds;
@@ -39,22 +38,14 @@ struct Config {
 
 extern "C" {
 
-int64_t host_mallocs() { return g_mallocs; }
 int64_t host_live_bytes() { return (int64_t)g_live_bytes; }
 int64_t host_news() { return g_news; }
-int64_t host_launches() { return (int64_t)g_launches.size(); }
-void host_launch(int64_t i, uint64_t* out) {   // grid, block, dynamic LDS
-    const Launch& l = g_launches[(size_t)i];
+void host_last_launch(uint64_t* out) {   // grid, block, dynamic LDS
     for (int k = 0; k < 3; ++k) {
-        out[k] = l.grid[k];
-        out[3 + k] = l.block[k];
+        out[k] = g_launch.grid[k];
+        out[3 + k] = g_launch.block[k];
     }
-    out[6] = l.lds;
-}
-// bytes of the live allocation that starts at p, 0 if none does
-int64_t host_size(void* p) {
-    auto it = g_live.find(p);
-    return it == g_live.end() ? 0 : (int64_t)it->second;
+    out[6] = g_launch.lds;
 }
 
 int hipGetDeviceCount(int* n) { *n = 1; return kOk; }
@@ -71,7 +62,6 @@ int hipMalloc(void** p, size_t bytes) {
     if (m == MAP_FAILED) return kOutOfMemory;
     g_live[m] = bytes;
     g_live_bytes += bytes;
-    ++g_mallocs;
     *p = m;
     return kOk;
 }
@@ -123,7 +113,7 @@ int hipLaunchKernel(const void*, Dim grid, Dim block, void**, size_t lds, void*)
     if (!grid.x || !grid.y || !grid.z || block.x * block.y * block.z > 1024 ||
         (uint64_t)grid.x * block.x >= (uint64_t(1) << 32) || grid.y > 65536 || grid.z > 65536 || lds > 160 * 1024)
         return kInvalidConfiguration;
-    g_launches.push_back(Launch{{grid.x, grid.y, grid.z}, {block.x, block.y, block.z}, lds});
+    g_launch = Launch{{grid.x, grid.y, grid.z}, {block.x, block.y, block.z}, lds};
     return kOk;
 }
 

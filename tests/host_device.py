@@ -1,7 +1,7 @@
 """Runs the library's host path (validation, planning, workspaces, launch shapes) without a GPU.
 
 ``host_device.cpp`` stands in for the HIP runtime: device memory is host memory, launches are checked against the
-launch limits and recorded, and nothing runs.  It has to be bound before the library, so every test body runs in a
+launch limits, and nothing runs.  It has to be bound before the library, so every test body runs in a
 child process: a test calls ``in_child(module, function, *args)`` and the child calls that function.
 """
 import ctypes
@@ -43,10 +43,8 @@ _host = None
 def bind(so: str) -> None:
     global _host
     _host = ctypes.CDLL(so, mode=ctypes.RTLD_GLOBAL)
-    for f in ("host_mallocs", "host_live_bytes", "host_news", "host_launches", "host_size"):
+    for f in ("host_live_bytes", "host_news"):
         getattr(_host, f).restype = ctypes.c_int64
-    _host.host_size.argtypes = [ctypes.c_void_p]
-    _host.host_launch.argtypes = [ctypes.c_int64, ctypes.POINTER(ctypes.c_uint64)]
 
 
 def live_bytes() -> int:
@@ -106,5 +104,5 @@ class Layer:
 def last_launch():
     """Grid, block and dynamic LDS bytes of the last launch."""
     out = (ctypes.c_uint64 * 7)()
-    _host.host_launch(_host.host_launches() - 1, out)
+    _host.host_last_launch(out)
     return list(out)

@@ -98,3 +98,23 @@ def test_static_forward_of_records_only_layers(child, kw, product):
 def test_static_forward_of_layers_switched_to_records(child, n, kw, product):
     forward, static = child("_static", n, kw)
     assert forward == static and static[-1] == product
+
+
+# ---- a forward allocates nothing ----
+
+def _allocations(static):
+    counts = []
+    for n, kw in ((64, dict(C_out=256, K=256, x="f32", y="f32", cb="f32", tile="f32")), (1, dict(C_out=960, K=8640)),
+                  (2, dict(C_out=192, conv=(192, 3, 1, 1, 64, 64))), (512, dict(C_out=1728, K=576, x="i8"))):
+        hd.Layer(max_n=n, **kw).forward(n, static=static)      # the process's first use of these kernels
+        layer = hd.Layer(max_n=n, **kw)
+        before = hd.news()
+        f = layer.aq.aq_layer_forward_static if static else layer.aq.aq_layer_forward
+        f(layer.handle, 4096, layer.x_scales, 4096, n, 0)
+        counts.append(hd.news() - before)
+    return counts
+
+
+@pytest.mark.parametrize("static", [False, True])
+def test_first_forward_of_a_layer_allocates_nothing(child, static):
+    assert child("_allocations", static) == [0, 0, 0, 0]
