@@ -882,6 +882,21 @@ bool even_tiles(const Geom& geo, const aq::FusedPlan& p) {
     return geo.W % 2 == 0 && geo.cin % (16 * p.cm) == 0 && (128 % geo.OW == 0 || geo.OW % 64 == 0);
 }
 
+// Convolutions outside even_tiles that no forward runs on the fused kernels.
+bool uneven_generic(const Geom& geo, const Geom& kgeo, int cb_dtype) {
+    // other codebook types decode their records value by value and keep the generic kernel
+    if (geo.g != 8 || cb_dtype != AQ_F16) return true;
+    // 1x1 on planes of an odd pixel count with few channels: one launch of the
+    // generic kernel is faster (2 x 15 x 15, 64 -> 64: 11.7 against 14.3 us)
+    return geo.kh == 1 && kgeo.W % 2 != 0 && geo.K <= 128;
+}
+
+// Whether any forward of a layer may take the fused or record kernels (`geo` of any n).
+bool fused_reachable(const Geom& geo, const aq::FusedPlan& p, int cb_dtype) {
+    if (!(p.rec_only ? records_fit(geo, p) : code_records_fit(geo, p))) return false;
+    return !geo.conv || even_tiles(geo, p) || !uneven_generic(geo, kernel_geom(geo), cb_dtype);
+}
+
 // The few-token kernel instead of the table path or the matrix cores, where no
 // option asks for one of those.  Its work grows with tokens x rows x codewords,
 // the matrix cores' does not grow with the tokens: measured over K = 512 to
@@ -940,11 +955,7 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
                  nimg * ((r.geo.OH - 1) * (int64_t)geo.stride + geo.kh) < lim24;
     }
     if (r.uneven) {
-        // other codebook types decode their records value by value and keep the generic kernel
-        if (geo.g != 8 || d.codebook_dtype != AQ_F16) fits31 = false;
-        // 1x1 on planes of an odd pixel count with few channels: one launch of the
-        // generic kernel is faster (2 x 15 x 15, 64 -> 64: 11.7 against 14.3 us)
-        if (geo.kh == 1 && r.geo.W % 2 != 0 && geo.K <= 128) fits31 = false;
+        if (uneven_generic(geo, r.geo, d.codebook_dtype)) fits31 = false;
     }
     // records too large to index: the in-loop decode, or the generic kernel for
     // formats without one (g = 9: refused)
@@ -1405,19 +1416,19 @@ aq_status aq_layer_create(const aq_layer_desc* desc, const void* codebooks, cons
 
     L->fused_ok = fused_ok;
     L->fplan = fplan;
-    if (L->fused_ok) {
+    const Geom g1 = make_geom(L, 1);
+    if (L->fused_ok && fused_reachable(g1, L->fplan, desc->codebook_dtype)) {
         // code records: what the in-loop decode and the fp16 g = 8 records kernel read
         if (!fplan.rec_only || (g == 8 && fplan.tile == AQ_F16 && desc->codebook_dtype == AQ_F16 &&
                                 (M == 1 || M == 2 || M == 4))) {
             std::vector<uint8_t> rec = fused_records(L->fplan, codes, C_out, G, M, B, pad);
             AQ_TRY(dev_upload(&L->d_crec, rec.data(), rec.size(), "fused code records"));
         }
-        const Geom g1 = make_geom(L, 1);
         if (records_fit(g1, L->fplan))
             AQ_TRY(dev_upload(&L->d_wrec, nullptr, aq::operand_record_bytes(g1, L->fplan), "operand records"));
-        // the dense product's repacked activations (convolution, int8 input) and a zero block
+        // the dense product's repacked activations (convolutions that tile evenly, int8 input) and a zero block
         size_t xpack = 0;
-        if (is_conv(*desc)) {
+        if (is_conv(*desc) && even_tiles(g1, L->fplan)) {
             const int64_t nimg_max = (desc->max_tokens + (int64_t)g1.OH * g1.OW - 1) / ((int64_t)g1.OH * g1.OW);
             xpack = (size_t)nimg_max * desc->conv_cin * desc->in_h * desc->in_w * 2;
         } else if (desc->x_dtype == AQ_I8) {

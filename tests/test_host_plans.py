@@ -118,3 +118,21 @@ def _allocations(static):
 @pytest.mark.parametrize("static", [False, True])
 def test_first_forward_of_a_layer_allocates_nothing(child, static):
     assert child("_allocations", static) == [0, 0, 0, 0]
+
+
+# ---- device memory that no route reads is not held ----
+
+def _held(n, kw):
+    before = hd.live_bytes()
+    hd.Layer(max_n=n, **kw)
+    return hd.live_bytes() - before
+
+
+@pytest.mark.parametrize("n,kw,limit", [
+    (4096, dict(C_out=16, conv=(16, 3, 1, 1, 25, 25)), 8e6),      # 82 MB of input, never repacked for the dense product
+    (4096, dict(C_out=16, conv=(24, 3, 1, 1, 16, 16)), 8e6),      # 50 MB
+    (1, dict(C_out=1024, M=1, B=10, cb="f32", conv=(1024, 3, 1, 1, 25, 25)), 4e6),      # 19 MB of records
+    (1, dict(C_out=1024, M=1, B=10, g=9, conv=(1024, 3, 1, 1, 24, 24)), 4e6),
+])
+def test_device_memory_of_uneven_convolutions(child, n, kw, limit):
+    assert child("_held", n, kw) < limit
