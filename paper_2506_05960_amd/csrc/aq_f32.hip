@@ -32,6 +32,7 @@ namespace aq {
 constexpr int kF32Tile = 32;
 constexpr int kF32Steps = 4;       // steps of 8 k whose loads are in flight together
 constexpr int kF32Pitch = kF32Tile + 1;
+constexpr int64_t kF32GridX = 1 << 20;
 
 // MC > 0: g == 8 and M == MC, codes in chunks of 16 bytes and codebooks in LDS;
 // else one of
@@ -47,8 +48,10 @@ f32_fwd_kernel(Geom geo, const float* __restrict__ cb32, const CodeT* __restrict
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, q = lane >> 5;
-    const int64_t m0 = (int64_t)(blockIdx.x / (unsigned)tiles_n) * (kF32Tile * TM);
-    const int n0 = (int)(blockIdx.x % (unsigned)tiles_n) * kF32Tile;
+    const unsigned tile = blockIdx.y * gridDim.x + blockIdx.x;
+    const int64_t m0 = (int64_t)(tile / (unsigned)tiles_n) * (kF32Tile * TM);
+    const int n0 = (int)(tile % (unsigned)tiles_n) * kF32Tile;
+    if (m0 >= geo.tokens) return;              // past the last tile (the whole workgroup)
     const int g = geo.g, M = geo.M, K = geo.K;
     const int nk = 1 << geo.B;
 
@@ -221,12 +224,14 @@ static hipError_t f32_launch_cfg(const Geom& geo, const DeviceWeights& w, const 
     const int64_t tm = (geo.tokens + kF32Tile * TM - 1) / (kF32Tile * TM);
     const int tn = (geo.C_out + kF32Tile - 1) / kF32Tile;
     if (tm * tn >= (int64_t(1) << 31)) return hipErrorInvalidConfiguration;
+    // a launch holds fewer than 2^32 threads along x: more tiles go along y
+    const unsigned gx = (unsigned)std::min<int64_t>(tm * tn, kF32GridX), gy = (unsigned)((tm * tn + gx - 1) / gx);
     const size_t part = (size_t)NW * TM * kF32Tile * kF32Pitch * sizeof(float);
     const size_t lds = std::max(part, MC > 0 ? ((size_t)geo.M << geo.B) * 8 * sizeof(float) : size_t(0));
     const hipError_t e = ensure_dynamic_lds((const void*)kern, lds);
     if (e != hipSuccess) return e;
     const void* codes = MC > 0 ? static_cast<const void*>(w.codes_lut) : w.codes;
-    kern<<<(unsigned)(tm * tn), 64 * NW, lds, st>>>(geo, w.cb32, static_cast<const CodeT*>(codes), w.scales, X,
+    kern<<<dim3(gx, gy), 64 * NW, lds, st>>>(geo, w.cb32, static_cast<const CodeT*>(codes), w.scales, X,
                                                     x_scales, Y, y_dtype, tn);
     note_launch(st, "f32_fwd_kernel", {XT, 8 * (int)sizeof(CodeT), MC, NW, TM});
     return hipGetLastError();

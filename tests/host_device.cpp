@@ -28,6 +28,7 @@ std::map<void*, size_t> g_live;
 size_t g_live_bytes = 0;
 int64_t g_news = 0;
 Launch g_launch;
+int g_error = 0;          // what the next hipGetLastError reports
 struct Config {
     Dim grid, block;
     size_t lds;
@@ -50,7 +51,11 @@ void host_last_launch(uint64_t* out) {   // grid, block, dynamic LDS
 
 int hipGetDeviceCount(int* n) { *n = 1; return kOk; }
 int hipGetDevice(int* d) { *d = 0; return kOk; }
-int hipGetLastError() { return kOk; }
+int hipGetLastError() {
+    const int e = g_error;
+    g_error = kOk;
+    return e;
+}
 int hipDeviceSynchronize() { return kOk; }
 const char* hipGetErrorString(int e) {
     return e == kInvalidConfiguration ? "invalid configuration" : e == kOutOfMemory ? "out of memory" : "host device error";
@@ -112,7 +117,7 @@ int hipLaunchKernel(const void*, Dim grid, Dim block, void**, size_t lds, void*)
     // the limits of a launch: threads of a block, threads along x, blocks along y and z, LDS
     if (!grid.x || !grid.y || !grid.z || block.x * block.y * block.z > 1024 ||
         (uint64_t)grid.x * block.x >= (uint64_t(1) << 32) || grid.y > 65536 || grid.z > 65536 || lds > 160 * 1024)
-        return kInvalidConfiguration;
+        return g_error = kInvalidConfiguration;
     g_launch = Launch{{grid.x, grid.y, grid.z}, {block.x, block.y, block.z}, lds};
     return kOk;
 }

@@ -210,6 +210,25 @@ def test_f32_infinite_codeword():
     assert np.all(np.isposinf(y[:, 7])) and np.all(np.isfinite(np.delete(y, 7, axis=1)))
 
 
+def test_f32_more_tiles_than_one_grid_row():
+    """1050624 tiles: the last ones, in the grid's second row, and the first against the 64-bit product."""
+    import paper_2506_05960_amd as P
+    spec = _f32("s_grid", 65600, 8, 32800, M=1, B=8, y="f16")
+    rng = np.random.default_rng(7203)
+    inp = {"codebooks": rng.standard_normal((1, 256, 8)).astype(np.float32),
+           "codes": rng.integers(0, 256, (spec.C_out, 1, 1), dtype=np.uint8),
+           "scales": rng.uniform(0.5, 1.5, spec.C_out).astype(np.float32)}
+    x = torch.from_numpy(rng.standard_normal((spec.n, 8)).astype(np.float32)).cuda()
+    layer = P.AQLayer(spec, inp)
+    layer.set_path("decode")
+    y = layer.forward(x)
+    w = torch.from_numpy(inp["codebooks"][0][inp["codes"][:, 0, 0]] * inp["scales"][:, None]).cuda().double()
+    for rows in (slice(0, 40), slice(spec.n // 2, spec.n // 2 + 40), slice(spec.n - 80, spec.n)):
+        ref = x[rows].double() @ w.t()
+        assert torch.all((y[rows].double() - ref).abs() <= 2.0**-11 * ref.abs() + 2.0**-24 + 2e-6 * (x[rows].double().abs() @ w.abs().t()))
+    layer.close()
+
+
 def _glin(name, C_out, K, n, M=2, B=8):
     return LayerSpec(name=name, C_out=C_out, K=K, g=8, M=M, B=B, n=n)
 

@@ -136,3 +136,15 @@ def _held(n, kw):
 ])
 def test_device_memory_of_uneven_convolutions(child, n, kw, limit):
     assert child("_held", n, kw) < limit
+
+
+# ---- launches ----
+
+def _f32_large(n, C_out):
+    return hd.Layer(C_out, 8, M=1, B=4, max_n=n, x="f32", cb="f32", tile="f32").set(lut_max_tokens=-1).forward(n), hd.last_launch()
+
+
+def test_f32_launch_past_the_threads_of_one_dimension(child):
+    """33 million tiles of 256 threads: more than a launch holds along x."""
+    kernels, grid = child("_f32_large", 1 << 20, 1 << 16)
+    assert kernels == ["f32_fwd_kernel"] and grid[0] * grid[1] >= 1 << 25 and grid[0] * grid[3] < 2**32
