@@ -475,7 +475,8 @@ struct TileCand {
 constexpr double kFixedChunks = 3.0;
 constexpr double kFixedChunksUnderfilled = 12.0;
 constexpr double kSplitChunks = 1.0;
-constexpr double kLoop3Fixed = 3.2, kLoop3Publish = 0.7, kLoop3Split = 1.66;   // us, see fused_plan_tile
+// us, see fused_plan_tile
+constexpr double kLoop3Fixed = 3.2, kLoop3Publish = 0.8, kLoop3Split = 0.48, kLoop3SplitFull = 0.51;
 
 // Fewer than 256 tiles of 64 tokens x 64 channels: the layer cannot fill the chip.
 bool underfilled(const Geom& geo) {
@@ -637,10 +638,14 @@ bool fused_plan_tile(const Geom& geo, const aq::Options& opt, size_t part_cap, i
         if (narrow && !widen) tcost *= 1.15;             // bank conflicts on the A-fragment reads (measured)
         const bool under = underfilled(geo);
         // under-filled 3x3 layers decoding one or two codebooks in the loop: a tile's
-        // chunk time barely depends on its size, publishing and summing its K
-        // splits does; in us, fitted to forced tiles and splits of the 512-token
-        // U-Net layers (K = 8640: 64 x 96 with three splits 21.4, 64 x 64 with two
-        // 22.9; K = 17280: 64 x 96 with three 32.1, 128 x 64 with four 34.9)
+        // chunk time barely depends on its size; publishing and summing its K splits
+        // does, and grows with the share of the compute units that do it at once.  In
+        // us, fitted to forced tiles and splits (1 to 8) of 398 layers: M = 1 and 2,
+        // K = 1152 to 17280, 128 to 1536 outputs, 64 to 4096 tokens on images of 8 to 64
+        // pixels.  The choice is within 6 % of the best of them everywhere (M = 2: 64
+        // tokens, 1728 -> 192 three splits 10.1, one 11.1; 1024 tokens, 2304 -> 256 two
+        // splits 11.3, four 11.9; 512 tokens, 8640 -> 960 64 x 96 with three splits 21.4,
+        // 64 x 64 with two 22.9; 17280 -> 960 32.1, 128 x 64 with four 34.9).
         const bool in_loop3 = under && p->kind == 1 && p->dec == aq::FUSED_DEC_PK16 && p->mc <= 2;
         if (under && (p->dec == aq::FUSED_DEC_PK16 || p->dec == aq::FUSED_DEC_BF16)) tcost *= 1.0 + 32.0 * p->mc / t.bm;
         for (int S = 1; S <= aq::kMaxSplitK; ++S) {
@@ -655,9 +660,11 @@ bool fused_plan_tile(const Geom& geo, const aq::Options& opt, size_t part_cap, i
             double cost = tcost * cu_time((nwg * S + 255) / 256, occ, cpw,
                                           under ? kFixedChunksUnderfilled : kFixedChunks);
             if (in_loop3) {
-                const double area = (double)t.bm * t.bn / 4096.0;
-                cost = kLoop3Fixed + (t.bn == 96 ? 2.25 : t.bm == 128 ? 2.3 : 2.05) * (cpw - (S > 1 ? kSplitChunks : 0.0)) +
-                       (S > 1 ? kLoop3Publish + kLoop3Split * S * area : 0.0);
+                const double splits = S * ((double)t.bm * t.bn / 4096.0);    // in 64 x 64 tiles
+                const double load = std::min(1.0, (double)(nwg * S) / 256.0);
+                const double chunk = (t.bm == 128 ? 2.59 : t.bn == 96 ? 2.09 : 1.82) * (p->mc == 1 ? 0.75 : 1.0);
+                cost = kLoop3Fixed + chunk * std::ceil((double)p->nchunk / (4.0 * S)) +
+                       (S > 1 ? kLoop3Publish + (kLoop3Split + kLoop3SplitFull * load) * splits : 0.0);
                 if (narrow && !widen) cost *= 1.15;
             }
             // a forced split wins over the unsplit fallback of the same tile

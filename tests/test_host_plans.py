@@ -138,6 +138,28 @@ def test_device_memory_of_uneven_convolutions(child, n, kw, limit):
     assert child("_held", n, kw) < limit
 
 
+# ---- choices that were measured ----
+
+def _route(n, kw, options=None):
+    d = hd.Layer(max_n=n, **kw).set(**(options or {})).describe(n)
+    return [d.get(k) for k in ("route", "weights", "tile", "split_k")]
+
+
+@pytest.mark.parametrize("M,cin,C_out,side,n,tile,split", [
+    (2, 192, 192, 8, 1, "64x64", 3),       # 10.1 us, unsplit 11.1
+    (2, 192, 384, 16, 2, "64x64", 3),      # 10.1, 10.7
+    (1, 192, 192, 8, 4, "64x64", 3),       # 10.3, 10.5
+    (2, 192, 384, 32, 1, "64x64", 1),      # 11.0, three splits 15.8
+    (2, 256, 256, 8, 1, "64x64", 4),       # 10.5, two splits 11.2
+    (2, 256, 256, 32, 1, "64x64", 2),      # 11.3, four 11.9
+    (2, 960, 960, 8, 8, "64x96", 3),       # 21.4, 64 x 64 with two 22.9
+    (2, 1920, 960, 8, 8, "64x96", 3),      # 32.1, 128 x 64 with four 34.9
+])
+def test_splits_of_under_filled_in_loop_convolutions(child, M, cin, C_out, side, n, tile, split):
+    route = child("_route", n, dict(C_out=C_out, M=M, conv=(cin, 3, 1, 1, side, side)))
+    assert route == ["fused", "in-loop-lds-fp16", tile, str(split)]
+
+
 # ---- launches ----
 
 def _f32_large(n, C_out):
