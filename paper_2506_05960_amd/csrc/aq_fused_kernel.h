@@ -788,26 +788,17 @@ fused_fwd_kernel(Geom geo, FusedPlan plan, const void* __restrict__ cb, const ui
         }
         if (tid == 0) __hip_atomic_store(arrivals + tile_lin, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (task < TASKS) {
-        const int c8 = (task / (ROWS / 4)) * 8;
-        const int rq = task - (task / (ROWS / 4)) * (ROWS / 4);
-        // Columns are tokens (convolution: 8 consecutive tokens stay in one image
-        // plane when the plane size is a multiple of 8) or output channels
-        // (linear: 16-byte aligned when C_out is a multiple of 8).
-        int col0, ncols, rows_left;
-        bool aligned;
-        if constexpr (CONV) {
-            col0 = T0 + c8;
-            ncols = min(8, tokens - col0);
-            rows_left = geo.C_out - (N0 + 4 * rq);
-            aligned = plane % 8 == 0;
-        } else {
-            col0 = N0 + c8;
-            ncols = min(8, geo.C_out - col0);
-            rows_left = tokens - (T0 + 4 * rq);
-            aligned = geo.C_out % 8 == 0;
-        }
-        if (ncols == 8 && aligned) {
+    // Columns are tokens (convolution: 8 consecutive tokens stay in one image
+    // plane when the plane size is a multiple of 8) or output channels (linear:
+    // 16-byte aligned when C_out is a multiple of 8).  A tile's column octets are
+    // then whole or wholly past the end.
+    const bool aligned = CONV ? plane % 8 == 0 : geo.C_out % 8 == 0;
+    const int c8 = (task / (ROWS / 4)) * 8;
+    const int rq = task - (task / (ROWS / 4)) * (ROWS / 4);
+    if (aligned) {
+        const int col0 = (CONV ? T0 : N0) + c8;
+        const int rows_left = CONV ? geo.C_out - (N0 + 4 * rq) : tokens - (T0 + 4 * rq);
+        if (task < TASKS && col0 < (CONV ? tokens : geo.C_out)) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 if (e >= rows_left) break;
@@ -839,22 +830,40 @@ fused_fwd_kernel(Geom geo, FusedPlan plan, const void* __restrict__ cb, const ui
                     __builtin_amdgcn_raw_buffer_store_b128(h, yr, yi0 * 2, 0, 0);
                 }
             }
-        } else {
-            for (int e = 0; e < 4 && e < rows_left; ++e)
-                for (int c = 0; c < ncols; ++c) {
-                    int yi;
-                    float o;
-                    if constexpr (CONV) {
-                        const int tk = col0 + c, bb = tk / plane;
-                        yi = (bb * geo.C_out + N0 + 4 * rq + e) * plane + (tk - bb * plane);
-                        o = v[c][e] * esc[e];
-                    } else {
-                        yi = (T0 + 4 * rq + e) * geo.C_out + col0 + c;
-                        o = v[c][e] * esc[c] * (has_xs ? exs[e] : 1.0f);
-                    }
-                    if (y_dtype == AQ_F32) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o), yr, yi * 4, 0, 0);
-                    else __builtin_amdgcn_raw_buffer_store_b16(f32_to_f16(o), yr, yi * 2, 0, 0);
-                }
+        }
+    } else {
+        // Unaligned rows: the scaled tile goes through LDS, so that consecutive lanes
+        // store consecutive values (a thread's own 32 values lie in 4 rows, and a
+        // wave's stores of them in 64 lines).
+        constexpr int PITCH = COLS + 1;
+        float* ol = reinterpret_cast<float*>(red);
+        __syncthreads();                         // the partial tiles are read
+        if (task < TASKS) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int c = 0; c < 8; ++c)
+                    ol[(4 * rq + e) * PITCH + c8 + c] = CONV ? v[c][e] * esc[e] : v[c][e] * esc[c] * (has_xs ? exs[e] : 1.0f);
+        }
+        __syncthreads();
+        // (convolution tiles have 64 or 128 columns: a thread keeps its token)
+        static_assert(!CONV || 256 % COLS == 0, "columns per pass");
+        const int tk = T0 + tid % COLS, img = CONV ? tk / plane : 0;
+        for (int i = tid; i < ROWS * COLS; i += 256) {
+            const int row = i / COLS, col = i % COLS;
+            int yi;
+            if constexpr (CONV) {
+                const int co = N0 + row;
+                if (tk >= tokens || co >= geo.C_out) continue;
+                yi = (img * geo.C_out + co) * plane + (tk - img * plane);
+            } else {
+                const int t = T0 + row, co = N0 + col;
+                if (t >= tokens || co >= geo.C_out) continue;
+                yi = t * geo.C_out + co;
+            }
+            const float o = ol[row * PITCH + col];
+            if (y_dtype == AQ_F32) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o), yr, yi * 4, 0, 0);
+            else __builtin_amdgcn_raw_buffer_store_b16(f32_to_f16(o), yr, yi * 2, 0, 0);
         }
     }
 }

@@ -27,7 +27,8 @@ constexpr int kOk = 0, kInvalidValue = 1, kInvalidConfiguration = 9, kOutOfMemor
 std::map<void*, size_t> g_live;
 size_t g_live_bytes = 0;
 int64_t g_news = 0;
-Launch g_launch;
+Launch g_launch[64];         // the first ones since the last reset
+int64_t g_launches = 0;
 int g_error = 0;          // what the next hipGetLastError reports
 struct Config {
     Dim grid, block;
@@ -41,12 +42,15 @@ extern "C" {
 
 int64_t host_live_bytes() { return (int64_t)g_live_bytes; }
 int64_t host_news() { return g_news; }
-void host_last_launch(uint64_t* out) {   // grid, block, dynamic LDS
+int64_t host_launches() { return g_launches; }
+void host_reset_launches() { g_launches = 0; }
+void host_launch(int64_t i, uint64_t* out) {   // grid, block, dynamic LDS
+    const Launch& l = g_launch[i & 63];
     for (int k = 0; k < 3; ++k) {
-        out[k] = g_launch.grid[k];
-        out[3 + k] = g_launch.block[k];
+        out[k] = l.grid[k];
+        out[3 + k] = l.block[k];
     }
-    out[6] = g_launch.lds;
+    out[6] = l.lds;
 }
 
 int hipGetDeviceCount(int* n) { *n = 1; return kOk; }
@@ -118,7 +122,8 @@ int hipLaunchKernel(const void*, Dim grid, Dim block, void**, size_t lds, void*)
     if (!grid.x || !grid.y || !grid.z || block.x * block.y * block.z > 1024 ||
         (uint64_t)grid.x * block.x >= (uint64_t(1) << 32) || grid.y > 65536 || grid.z > 65536 || lds > 160 * 1024)
         return g_error = kInvalidConfiguration;
-    g_launch = Launch{{grid.x, grid.y, grid.z}, {block.x, block.y, block.z}, lds};
+    if (g_launches < 64) g_launch[g_launches] = Launch{{grid.x, grid.y, grid.z}, {block.x, block.y, block.z}, lds};
+    ++g_launches;
     return kOk;
 }
 

@@ -43,7 +43,7 @@ _host = None
 def bind(so: str) -> None:
     global _host
     _host = ctypes.CDLL(so, mode=ctypes.RTLD_GLOBAL)
-    for f in ("host_live_bytes", "host_news"):
+    for f in ("host_live_bytes", "host_news", "host_launches"):
         getattr(_host, f).restype = ctypes.c_int64
 
 
@@ -91,18 +91,23 @@ class Layer:
         return [k.split("<")[0] for k in self.aq.aq_layer_last_launches(self.handle)[1]]
 
     def grad(self, n, dtype="f16"):
+        """Kernels of a codebook gradient with their template arguments, or the status it is refused with."""
         try:
             self.aq.aq_layer_codebook_grad(self.handle, 4096, 4096, dtype, 4096, n, 0)
         except self.aq.AQError as e:
             return self.aq.STATUS_NAMES[e.status]
-        return [k.split("<")[0] for k in self.aq.aq_layer_last_launches(self.handle)[1]]
+        return self.aq.aq_layer_last_launches(self.handle)[1]
 
     def close(self):
         self.aq.aq_layer_destroy(self.handle)
 
 
-def last_launch():
-    """Grid, block and dynamic LDS bytes of the last launch."""
-    out = (ctypes.c_uint64 * 7)()
-    _host.host_last_launch(out)
-    return list(out)
+def launches(call):
+    """Result of ``call()``, and grid, block and dynamic LDS bytes of each kernel it launched."""
+    _host.host_reset_launches()
+    result, out = call(), []
+    for i in range(_host.host_launches()):
+        one = (ctypes.c_uint64 * 7)()
+        _host.host_launch(ctypes.c_int64(i), one)
+        out.append(list(one))
+    return result, out

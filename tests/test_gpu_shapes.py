@@ -157,6 +157,36 @@ def test_bf16_linear(spec, weights):
     layer.close()
 
 
+@pytest.mark.parametrize("tile,split,dt,y", [
+    ("64x96", 1, "f16", "f16"), ("64x64", 2, "f16", "f32"), ("32x128", 2, "f16", "f16"), ("32x64", 1, "f16", "f32"),
+    ("64x96", 2, "bf16", "f32"), ("32x128", 1, "bf16", "f16"),
+])
+def test_unaligned_output_rows(tile, split, dt, y):
+    """Outputs whose rows are no multiple of 16 bytes leave through LDS: the bits are those of the same channels in
+    a layer of whole rows, and nothing is written past the last one."""
+    import paper_2506_05960_amd as P
+    wide = LayerSpec(name="rows_136", C_out=136, K=840, g=8, M=2, B=8, n=77, codebook_dtype=dt, x_dtype=dt, y_dtype=y, tile_dtype=dt)
+    inp = generate(wide, 7111)
+    x = torch.from_numpy(inp["x"].view(np.int16)).cuda().view(torch.bfloat16) if dt == "bf16" else torch.from_numpy(inp["x"]).cuda()
+    outs = []
+    for C_out in (136, 131, 7):
+        spec = LayerSpec(**{**wide.__dict__, "name": f"rows_{C_out}", "C_out": C_out})
+        layer = P.AQLayer(spec, {**inp, "codes": inp["codes"][:C_out], "scales": inp["scales"][:C_out]})
+        layer.set_path("decode")
+        for k, v in {"weights": 1, "fused_tile": tile, "split_k": split}.items():
+            layer.set_option(k, v)
+        d = layer.describe(spec.n)
+        assert d["route"] == "fused" and d["tile"] == tile and (C_out == 7 or d["split_k"] == str(split))
+        buf = torch.full((spec.n * C_out + 64,), 9.0, dtype=torch.float16 if y == "f16" else torch.float32, device="cuda")
+        layer.forward(x, out=buf[:spec.n * C_out].view(spec.n, C_out))
+        assert bool((buf[spec.n * C_out:] == 9.0).all())
+        outs.append(buf[:spec.n * C_out].view(spec.n, C_out))
+        layer.close()
+    assert torch.equal(outs[1], outs[0][:, :131])
+    if split == 1:
+        assert torch.equal(outs[2], outs[0][:, :7])
+
+
 def _f32(name, n, K, C_out, g=8, M=2, B=8, x="f32", conv=None, y="f32"):
     return LayerSpec(name=name, C_out=C_out, K=K, g=g, M=M, B=B, n=n, codebook_dtype="f32", x_dtype=x, y_dtype=y,
                      tile_dtype="f32", conv=conv)

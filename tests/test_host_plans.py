@@ -163,7 +163,9 @@ def test_splits_of_under_filled_in_loop_convolutions(child, M, cin, C_out, side,
 # ---- launches ----
 
 def _f32_large(n, C_out):
-    return hd.Layer(C_out, 8, M=1, B=4, max_n=n, x="f32", cb="f32", tile="f32").set(lut_max_tokens=-1).forward(n), hd.last_launch()
+    layer = hd.Layer(C_out, 8, M=1, B=4, max_n=n, x="f32", cb="f32", tile="f32").set(lut_max_tokens=-1)
+    kernels, launches = hd.launches(lambda: layer.forward(n))
+    return kernels, launches[-1]
 
 
 def test_f32_launch_past_the_threads_of_one_dimension(child):
