@@ -744,13 +744,16 @@ bool gemm_plan_tile(const Geom& geo, const aq::Options& opt, aq::FusedPlan* p) {
     return found;
 }
 
-// A 3x3 layer of one or two codebooks whose weights are few: its tiles decode
-// them in the loop faster than a records launch does once (32768 tokens, M = 2:
-// 64 -> 64 10.0 against 13.1 us, 48 -> 96 8.0 against 11.7; 32 -> 192 the same,
-// 16 -> 160 16.6 against 12.0).
+// A 3x3 layer of one or two codebooks whose weights are few and whose in-loop
+// tiles (128 x 64, or 64 x 96 for more than 64 channels) run in one round: it
+// decodes in the loop faster than a records launch does once (32768 tokens, M = 2:
+// 64 -> 64 10.0 against 13.1 us, but 32 -> 96, two rounds, 14.3 against 12.4;
+// 65536 tokens 32 -> 64 18.1 against 14.2).  Very short reductions only with few
+// tokens (16 -> 32: 4096 tokens 6.6 and 8.6 us with M = 1, 32768 tokens 9.2 and 7.9).
 bool small_weights(const Geom& geo, const aq::FusedPlan& p) {
     return p.kind == 1 && p.dec == aq::FUSED_DEC_PK16 && p.mc <= 2 && geo.C_out <= 96 &&
-           (int64_t)geo.K * geo.C_out <= 50000;
+           (int64_t)geo.K * geo.C_out <= 50000 && geo.tokens <= 256 * (geo.C_out > 64 ? 64 : 128) &&
+           (geo.K >= 288 || geo.C_out > 32 || geo.tokens <= 16384);
 }
 
 // The product kernels index records and code records with 32-bit byte offsets,

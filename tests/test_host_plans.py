@@ -160,6 +160,20 @@ def test_splits_of_under_filled_in_loop_convolutions(child, M, cin, C_out, side,
     assert route == ["fused", "in-loop-lds-fp16", tile, str(split)]
 
 
+@pytest.mark.parametrize("M,cin,C_out,side,n,route", [
+    (2, 64, 64, 64, 8, "fused"),          # 10.7 us, by records 13.4: one round of in-loop tiles
+    (2, 32, 64, 64, 12, "rec-conv"),      # 13.1, in the loop 18.2
+    (1, 16, 96, 64, 64, "rec-conv"),      # 33.7, 88
+    (2, 32, 96, 64, 4, "fused"),
+    (2, 32, 96, 64, 8, "rec-conv"),       # 11.9, 14.4
+    (1, 16, 32, 32, 4, "fused"),          # 6.6, 8.6
+    (1, 16, 32, 64, 8, "rec-conv"),       # 7.9, 9.2
+])
+def test_convolutions_of_few_weights(child, M, cin, C_out, side, n, route):
+    got = child("_route", n, dict(C_out=C_out, M=M, conv=(cin, 3, 1, 1, side, side)))
+    assert got[:2] == [route, "in-loop-lds-fp16" if route == "fused" else "records"]
+
+
 # ---- launches ----
 
 def _f32_large(n, C_out):
