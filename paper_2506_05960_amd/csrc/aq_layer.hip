@@ -1034,11 +1034,12 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
         if (opt.rec_product == 3 && !ws_switch) {
             if (!r.uneven && (opt.fused_bm == 64 ? ok2 : ok1)) pick = opt.fused_bm == 64 ? &w2 : &w1;
         } else if (opt.rec_product == 0 && r.geo.OW >= 16 &&
-                   (geo.C_out > 64 || geo.K <= (fp.kind == 1 ? 576 : 512))) {
+                   (geo.C_out > 64 || geo.K <= (geo.tokens > 32768 ? (fp.kind == 1 ? 900 : 768) : fp.kind == 1 ? 576 : 512))) {
             // (C_out up to 64 leaves half of this kernel's tile empty, which only a
-            // short reduction repays; 8 x 64 x 64, M = 2: 3x3 576 -> 64 44.4 us here,
-            // 32.2 on the fused kernel, 1x1 576 -> 64 17.6 and 14.2, but 53 x 64 x 64
-            // 3x3 64 -> 64 42.0 and 50.0, 17 x 64 x 64 1x1 48 -> 32 9.1 and 17.5)
+            // short reduction repays, the more so past one round of its tiles; M = 2,
+            // here and on the fused kernel: 8 x 64 x 64 3x3 576 -> 64 44.4 and 32.2 us, 1x1 576
+            // -> 64 17.6 and 14.2; 32 x 64 x 64 3x3 80 -> 64 30.7 and 35.2, 192 -> 64 1.14 times
+            // longer, 1x1 576 -> 64 37.3 and 41.1, 960 -> 64 even)
             if (ok1 && w1.ntiles >= (fp.kind == 1 ? 192 : 256)) pick = &w1;
             else if (ok2 && w2.ntiles >= 256 && fp.nchunk >= 8) pick = &w2;
             else if (ok1 && fp.kind == 2 && geo.M >= 4 && w1.ntiles >= 128) pick = &w1;

@@ -174,6 +174,17 @@ def test_convolutions_of_few_weights(child, M, cin, C_out, side, n, route):
     assert got[:2] == [route, "in-loop-lds-fp16" if route == "fused" else "records"]
 
 
+@pytest.mark.parametrize("k,cin,C_out,n,route", [
+    (3, 80, 64, 32, "rec-conv"),          # 30.7 us, fused kernel 35.2
+    (3, 192, 64, 32, "fused"),            # rec-conv 1.14 times longer
+    (1, 576, 32, 16, "rec-conv"),         # 19.3, 23.2
+    (1, 960, 64, 16, "fused"),
+    (1, 576, 64, 8, "fused"),
+])
+def test_convolutions_to_few_channels(child, k, cin, C_out, n, route):
+    assert child("_route", n, dict(C_out=C_out, M=2, conv=(cin, k, 1, k // 2, 64, 64)))[0] == route
+
+
 # ---- launches ----
 
 def _f32_large(n, C_out):
