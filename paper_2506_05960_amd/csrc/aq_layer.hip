@@ -807,6 +807,14 @@ bool use_predecoded(const aq_layer* L, const Geom& geo) {
             // (bf16 codewords are summed in fp32 and rounded in the loop: records pay
             // off earlier; 2663 tokens x 2256 -> 832, 147 tiles: 27.9 against 38.8 us)
             if (p.dec == aq::FUSED_DEC_BF16) return tiles >= 128 && geo.tokens >= 1024;
+            // one codebook (decoded in the loop for a quarter of M = 4's gathers): past the
+            // in-loop tiles' first round while the records are few, and past two rounds
+            // (4096 tokens, records and in-loop: 192 -> 576 8.7 and 10.8 us, 952 -> 576 15.1
+            // and 16.2, 2304 -> 576 25.0 and 23.7; 1024 tokens 952 -> 2304 19.2 and 16.4;
+            // 1590 tokens 952 -> 3456 28.5 and 31.3), or where the fused kernel's output rows
+            // are unaligned (3000 tokens 2304 -> 700 26.0 and 29.9)
+            if (p.mc == 1 && p.dec == aq::FUSED_DEC_PK16)
+                return tiles >= 256 || (tiles > 128 && ((int64_t)geo.K * geo.C_out <= 1000000 || geo.C_out % 8 != 0));
             return tiles >= 192 && (geo.tokens >= 2048 || p.mc >= 4);
         }
         return p.mc >= 4 && geo.C_out >= 1152 && geo.tokens >= 2048;

@@ -185,6 +185,21 @@ def test_convolutions_to_few_channels(child, k, cin, C_out, n, route):
     assert child("_route", n, dict(C_out=C_out, M=2, conv=(cin, k, 1, k // 2, 64, 64)))[0] == route
 
 
+@pytest.mark.parametrize("n,K,C_out,route", [
+    (4096, 192, 576, "rec-linear"),       # 8.7 us, in the loop 10.8
+    (4096, 2304, 576, "fused"),           # 23.7, by records 25.0
+    (1024, 952, 2304, "fused"),           # 16.4, 19.2
+    (1024, 192, 2304, "rec-linear"),      # 9.4, 10.8
+    (1590, 952, 3456, "rec-linear"),      # 28.5, 31.3
+    (3000, 2304, 700, "rec-linear"),      # 26.0, 29.9: rows that are no multiple of 16 bytes
+    (1000, 2304, 700, "fused"),           # 12.6, 25.4
+])
+@pytest.mark.parametrize("x", ["f16", "i8"])
+def test_linear_layers_of_one_codebook(child, n, K, C_out, route, x):
+    got = child("_route", n, dict(C_out=C_out, K=K, M=1, x=x), {"lut_max_tokens": -1})
+    assert got[:2] == [route, "in-loop-lds-fp16" if route == "fused" else "records"]
+
+
 # ---- launches ----
 
 def _f32_large(n, C_out):
