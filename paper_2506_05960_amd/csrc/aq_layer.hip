@@ -942,6 +942,26 @@ bool few_route(const aq_layer* L, const Geom& geo) {
     return geo.tokens * geo.K * geo.C_out <= (geo.M == 4 ? int64_t(100) * 1000000 : int64_t(300) * 1000000);
 }
 
+// bf16 linear layers that the generic kernel runs faster than the fused one: short
+// reductions, where the fused kernel's prologue and epilogue are not repaid, above
+// all with unaligned output rows (C_out no multiple of 8) in many tiles.  Generic
+// and fused, us: 1 token 64 -> 1152, M = 1 4.0 and 4.5; 1000 tokens 64 -> 1152, M = 3
+// (a records launch) 8.4 and 9.4, 144 -> 1152 11.2 and 10.0; M = 1, B = 12 (records)
+// 3 tokens 88 -> 1152 4.3 and 6.7, 70 tokens 144 -> 4608 7.4 and 8.9; 361 tokens 144 ->
+// 3451, M = 1 8.8 and 10.2; 3561 tokens 64 -> 1007, M = 2 12.6 and 19.3; 9894 tokens
+// 640 -> 1007, M = 2 57.3 and 82.4.
+bool bf16_generic(const Geom& geo, const aq::FusedPlan& p) {
+    const int64_t wgs = ((geo.tokens + 63) / 64) * (int64_t)((geo.C_out + 95) / 96);   // 64 x 96 tiles
+    const bool odd8 = geo.C_out % 8 != 0, odd4 = geo.C_out % 4 != 0;   // (odd4: no wave-split linear kernel either)
+    if (geo.K <= 64 && ((geo.tokens <= 4 && (geo.M == 1 || odd8)) || (odd8 && wgs > 64))) return true;
+    // records only: a records launch for few codewords; one codebook's the generic kernel reads fastest
+    if (p.rec_only && geo.M > 1 && geo.K <= 96 && wgs <= 256) return true;
+    if (p.rec_only && geo.M == 1 && ((geo.K <= 300 && geo.tokens <= 4) || (geo.K <= 160 && wgs <= 256 && geo.C_out > 128)))
+        return true;
+    if (odd4 && geo.K < 200 && wgs > 128) return true;
+    return odd4 && !p.rec_only && wgs > 256 && geo.K < std::min<int64_t>(1024, 150 * ((wgs + 255) / 256));
+}
+
 Route plan_route(const aq_layer* L, const Geom& geo) {
     Route r{};
     const aq_layer_desc& d = L->desc;
@@ -979,6 +999,8 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
     // formats without one (g = 9: refused)
     const bool rec_fit = L->fused_ok && records_fit(geo, L->fplan);
     if (L->fused_ok && !(L->fplan.rec_only ? rec_fit : code_records_fit(geo, L->fplan))) fits31 = false;
+    const bool unforced = opt.weights == 0 && opt.rec_product == 0 && opt.fused_bm == 0 && opt.split_k == 0;
+    if (L->fused_ok && fp.tile == AQ_BF16 && unforced && bf16_generic(geo, L->fplan)) fits31 = false;
     if (rec_fit && use_predecoded(L, geo)) {
         // pre-decoded mode: operands decoded once per forward, then read with plain loads
         fp.dec = aq::FUSED_DEC_REC;

@@ -200,6 +200,24 @@ def test_linear_layers_of_one_codebook(child, n, K, C_out, route, x):
     assert got[:2] == [route, "in-loop-lds-fp16" if route == "fused" else "records"]
 
 
+@pytest.mark.parametrize("n,K,C_out,M,B,route", [
+    (1, 64, 1152, 1, 8, "generic"),       # 4.0 us, fused 4.5
+    (40, 64, 1152, 1, 8, "fused"),
+    (1000, 64, 1152, 3, 8, "generic"),    # 8.4, 9.4
+    (1000, 144, 1152, 3, 8, "fused"),     # 10.0, generic 11.2
+    (3, 88, 1152, 1, 12, "generic"),      # 4.3, 6.7
+    (70, 144, 4608, 1, 12, "generic"),    # 7.4, 8.9
+    (361, 144, 3451, 1, 8, "generic"),    # 8.8, 10.2
+    (3561, 64, 1007, 2, 8, "generic"),    # 12.6, 19.3
+    (9894, 640, 1007, 2, 8, "generic"),   # 57.3, 82.4
+    (1000, 640, 1007, 2, 8, "fused"),
+    (1000, 2304, 576, 2, 8, "fused"),     # 15.8, 56
+])
+def test_bf16_linear_layers(child, n, K, C_out, M, B, route):
+    kw = dict(C_out=C_out, K=K, M=M, B=B, x="bf16", cb="bf16", tile="bf16", y="f32")
+    assert child("_route", n, kw, {"lut_max_tokens": -1})[0] == route
+
+
 # ---- launches ----
 
 def _f32_large(n, C_out):
