@@ -906,7 +906,8 @@ bool uneven_generic(const Geom& geo, const Geom& kgeo, int cb_dtype) {
     if (geo.g != 8 || cb_dtype != AQ_F16) return true;
     // 1x1 on planes of an odd pixel count with few channels: one launch of the
     // generic kernel is faster (2 x 15 x 15, 64 -> 64: 11.7 against 14.3 us)
-    return geo.kh == 1 && kgeo.W % 2 != 0 && geo.K <= 128;
+    // or with one to two groups per channel (2 x 50 x 50, 16 -> 256: 10.2 and 11.0)
+    return geo.kh == 1 && (geo.K <= 16 || (kgeo.W % 2 != 0 && geo.K <= 128));
 }
 
 // Whether any forward of a layer may take the fused or record kernels (`geo` of any n).
@@ -1001,7 +1002,15 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
     if (L->fused_ok && !(L->fplan.rec_only ? rec_fit : code_records_fit(geo, L->fplan))) fits31 = false;
     const bool unforced = opt.weights == 0 && opt.rec_product == 0 && opt.fused_bm == 0 && opt.split_k == 0;
     if (L->fused_ok && fp.tile == AQ_BF16 && unforced && bf16_generic(geo, L->fplan)) fits31 = false;
-    if (rec_fit && use_predecoded(L, geo)) {
+    // convolutions that do not tile, in more 64 x 64 tiles than one round:
+    const bool rounds = r.uneven && ((geo.tokens + 63) / 64) * (int64_t)((geo.C_out + 63) / 64) > 256;
+    //  * 3x3 on 8 channels fills half of a chunk: the generic kernel (22500 tokens, M = 2,
+    //    8 -> 64 15.0 us, fused 18.3)
+    if (rounds && unforced && geo.kh == 3 && geo.K <= 72) fits31 = false;
+    //  * 1x1 with M = 4: records rather than four gathers per group and tile (22500
+    //    tokens, 64 -> 256 25.4 and 39.2 us, 128 -> 512 42.4 and 70.3)
+    const bool rec_rounds = rounds && unforced && geo.kh == 1 && geo.M >= 4;
+    if (rec_fit && (use_predecoded(L, geo) || rec_rounds)) {
         // pre-decoded mode: operands decoded once per forward, then read with plain loads
         fp.dec = aq::FUSED_DEC_REC;
         fp.mc = 1;

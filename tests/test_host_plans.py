@@ -218,6 +218,19 @@ def test_bf16_linear_layers(child, n, K, C_out, M, B, route):
     assert child("_route", n, kw, {"lut_max_tokens": -1})[0] == route
 
 
+@pytest.mark.parametrize("n,cin,C_out,k,M,side,route,weights", [
+    (2, 16, 256, 1, 1, 50, "generic", None),             # 10.2 us, fused 11.0
+    (2, 48, 320, 1, 1, 50, "fused", "records"),
+    (9, 8, 64, 3, 2, 50, "generic", None),               # 15.0, 18.3
+    (2, 8, 64, 3, 2, 50, "fused", "records"),
+    (9, 64, 256, 1, 4, 50, "fused", "records"),          # 25.4, in the loop 39.2
+    (1, 64, 256, 1, 4, 50, "fused", "in-loop-lds-fp16"),
+])
+def test_short_reductions_of_uneven_convolutions(child, n, cin, C_out, k, M, side, route, weights):
+    got = child("_route", n, dict(C_out=C_out, M=M, conv=(cin, k, 1, k // 2, side, side)))
+    assert got[:2] == [route, weights]
+
+
 # ---- launches ----
 
 def _f32_large(n, C_out):
