@@ -1048,25 +1048,38 @@ static bool grad_dma_ok(const Geom& geo, const Options& opt) {
 // Token splits of a gradient over nchunk 64-token chunks.  Register-staged
 // kernels: about four workgroups per CU.  Direct-to-LDS kernels: the least of
 //     chunks per split x chunk time x rounds of workgroups
-//   + partial gradients written and read back at about 4 TB/s (+ 3 us for
-//     the sum's launch),
-// with the chunk times (us) and the workgroups a CU runs at full rate measured
-// on U-Net shapes (one to sixteen splits each): 405 tokens x 1224 -> 1336 takes
-// 24 us with one split, 32 with the three of the first rule.
+//   + partial gradients written and read back (+ the sum's launch),
+// with the chunk times (us) and the workgroups a CU holds measured (one to
+// sixteen splits each, U-Net shapes and 64 to 4608 channels).  The 64 x 64 linear
+// tile runs three to a CU, a chunk taking 0.46, 0.70 or 0.90 us with one, two or
+// three there: 405 tokens x 1224 -> 1336 takes 24 us with one split, 32 with three;
+// 7495 tokens 400 -> 3800 (420 tiles) 91, 93, 80, 84 us with one to four.
 static int grad_splits(const GradPlan& gp, const Geom& geo, int64_t nchunk) {
     const int64_t tiles = (int64_t)gp.tiles_m * gp.tiles_n;
     const int64_t slice = (int64_t)geo.C_out * geo.K * 4;
     const int64_t cap = std::min<int64_t>({16, nchunk, std::max<int64_t>(1, (int64_t(32) << 20) / slice)});
     if (!gp.dma) return (int)std::min<int64_t>(cap, std::max<int64_t>(1, (960 + tiles - 1) / tiles));
     const bool wide = !geo.conv && gp.bm == kWideM, one = wide || gp.halves == 2;   // one workgroup per CU
-    const double chunk_us = wide ? 0.75 : geo.conv ? 0.6 : 0.5;
-    const double slots = one ? 256.0 : geo.conv ? 280.0 : 640.0;
+    const double chunk_us = wide ? 0.75 : 0.6;
+    const double slots = one ? 256.0 : 280.0;
+    const auto small_tiles = [&](int64_t wgs) {        // a chunk of `wgs` 64 x 64 linear tiles, in rounds of 768
+        const int64_t rest = wgs % 768;
+        return 0.90 * (double)(wgs / 768) + (rest == 0 ? 0.0 : rest <= 256 ? 0.46 : rest <= 512 ? 0.70 : 0.90);
+    };
     int best = 1;
     double best_us = 0;
     for (int S = 1; S <= cap; ++S) {
-        const double rounds = std::max(1.0, (double)(tiles * S) / slots);
-        const double us = (double)((nchunk + S - 1) / S) * chunk_us * (one ? std::ceil(rounds) : rounds) +
-                          (S > 1 ? 3.0 + (double)(2 * S * slice) / 4.0e6 : (double)slice / 4.0e6);
+        const int64_t cps = (nchunk + S - 1) / S;
+        double us;
+        if (!wide && !geo.conv) {
+            const int64_t Se = (nchunk + cps - 1) / cps;   // splits that hold a chunk
+            us = (double)cps * small_tiles(tiles * Se) +
+                 (Se > 1 ? 2.9 + (double)(2 * Se * slice) / 3.6e6 : (double)slice / 3.6e6);
+        } else {
+            const double rounds = std::max(1.0, (double)(tiles * S) / slots);
+            us = (double)cps * chunk_us * (one ? std::ceil(rounds) : rounds) +
+                 (S > 1 ? 3.0 + (double)(2 * S * slice) / 4.0e6 : (double)slice / 4.0e6);
+        }
         if (S == 1 || us < best_us) {
             best = S;
             best_us = us;
@@ -1106,8 +1119,11 @@ GradPlan grad_plan_create(const Geom& geo, int64_t max_tokens, const Options& op
         gp.bn = 64;
         gp.tiles_m = (geo.C_out + gp.bm - 1) / gp.bm;
         gp.tiles_n = (npairs + gp.bn - 1) / gp.bn;
-        // few tiles: eight waves on each, with half the token splits
-        if (gp.bm == 64 && gp.tiles_m * (int64_t)gp.tiles_n < 256) gp.halves = 2;
+        // few tiles: eight waves on each, with half the token splits (1x1 layers until their
+        // chunks fill the chip for long: 2 x 64 x 64, 360 -> 696 31.3 us, four waves 33.6;
+        // 9 images 78.9 and 71.8)
+        const int64_t tiles = gp.tiles_m * (int64_t)gp.tiles_n;
+        if (gp.bm == 64 && tiles < 256 && (geo.kh == 3 || tiles * nchunk <= 24000)) gp.halves = 2;
     } else {
         const int shapes[3][2] = {{128, 128}, {64, 128}, {64, 64}};
         int pick = 2;

@@ -231,6 +231,35 @@ def test_short_reductions_of_uneven_convolutions(child, n, cin, C_out, k, M, sid
     assert got[:2] == [route, weights]
 
 
+def _grad(n, kw):
+    layer = hd.Layer(max_n=n, **kw)
+    kernels, launches = hd.launches(lambda: layer.grad(n, "f16"))
+    product = [i for i, k in enumerate(kernels) if k.startswith("wgrad")][0]
+    return kernels[product], launches[product - len(kernels)][0]
+
+
+@pytest.mark.parametrize("n,K,C_out,splits", [
+    (7495, 400, 3800, 3),       # 80 us; one split 91, two 93
+    (300, 400, 3800, 1),        # 22.9, three 31.5
+    (16384, 200, 4608, 8),      # 102, three 119
+    (5432, 320, 320, 10),       # 19.6, sixteen 21.0
+])
+def test_token_splits_of_linear_gradients(child, n, K, C_out, splits):
+    kernel, blocks = child("_grad", n, dict(C_out=C_out, K=K))
+    tiles = -(-K // 64) * -(-C_out // 64)
+    assert kernel.startswith("wgrad_linear_dma_kernel") and blocks == -(-tiles * splits // 8) * 8
+
+
+@pytest.mark.parametrize("n,k,cin,C_out,halves", [
+    (9, 1, 360, 696, 1),        # 71.8 us, eight waves 78.9
+    (2, 1, 360, 696, 2),        # 31.3, four waves 33.6
+    (2, 3, 144, 856, 2),
+])
+def test_waves_of_convolution_gradients(child, n, k, cin, C_out, halves):
+    kernel, _ = child("_grad", n, dict(C_out=C_out, conv=(cin, k, 1, k // 2, 64, 64)))
+    assert kernel.endswith(f"64, {halves}>")
+
+
 # ---- launches ----
 
 def _f32_large(n, C_out):
