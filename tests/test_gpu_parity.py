@@ -372,14 +372,14 @@ def test_wave_split_conv_matches_oracle(spec, wk):
     check_against_oracle(spec, inp, sampled_outputs(spec, y1, tok, ch), tok, ch, "decode", TOL[spec.tile_dtype])
 
 
-def test_wave_split_conv_staging_and_fallback():
-    """Input rows staged once per image block or kh rows per output row give identical outputs; shapes the
-    kernel does not take (output rows that do not tile 128 tokens) keep the fused kernel."""
+def test_wave_split_conv_widths_and_fallback():
+    """Tiles of 128 and 192 channels give identical outputs, within the oracle's bound; shapes the kernel is not forced
+    on (output rows that do not tile 128 tokens) keep the fused or the generic kernel."""
     spec = WSPLIT[0]
     inp = generate(spec, 61)
-    a = _run(spec, inp, "decode", opts={"weights": 2, "record_product": 3})
-    b = _run(spec, inp, "decode", opts={"weights": 2, "record_product": 3, "stage_rows": 1})
+    a, b = (_run(spec, inp, "decode", opts={"weights": 2, "record_product": 3, "fused_tile": t}) for t in ("128x128", "128x192"))
     assert np.array_equal(a, b)
+    assert O.rel_err_inf(a, O.forward(spec, inp)) <= 2e-3
     import paper_2506_05960_amd as P
     for odd in (LayerSpec(name="ws_no_6x6", C_out=64, K=16 * 9, g=8, M=2, B=8, n=2, conv=ConvGeom(16, 3, 3, 1, 1, 6, 6)),
                 LayerSpec(name="ws_no_12", C_out=64, K=16 * 9, g=8, M=2, B=8, n=2, conv=ConvGeom(16, 3, 3, 1, 1, 8, 12))):
@@ -606,16 +606,31 @@ def test_predecoded_formats(spec):
 
 
 @pytest.mark.parametrize("spec", [f for f in FUSED + KAQ if f.conv is not None], ids=lambda s: s.name)
-def test_fused_conv_row_staging(spec):
-    """Input rows staged once per image block fill the fragments exactly as kh rows per output row do."""
+def test_fused_conv_tiles_stage_the_same_rows(spec):
+    """Tiles of other sizes start in other rows and images and stage other runs of input rows; the terms of an output
+    and their order are the same, so the outputs are identical."""
+    import paper_2506_05960_amd as P
     inp = generate(spec, 78)
-    for rec in ("0", "1"):
-        w = 2 if rec == "1" else 1
-        y_once = _run(spec, inp, "decode", opts={"weights": w})
-        y_each = _run(spec, inp, "decode", opts={"weights": w, "stage_rows": 1})
-        _say(f"row staging {spec.name} rec={rec} identical={np.array_equal(y_once, y_each)}")
-        assert np.array_equal(y_once, y_each)
-    assert O.rel_err_inf(y_once, O.forward(spec, inp)) <= 2e-3
+    ref = O.forward(spec, inp)
+    for weights in (1, 2):
+        layer = P.AQLayer(spec, inp)
+        layer.set_option("weights", weights)
+        layer.set_option("record_product", 1)
+        layer.set_option("split_k", 1)
+        layer.set_path("decode")
+        x = _dev(inp["x"], spec.x_dtype)
+        ys = {}
+        for tile in ("64x64", "64x96", "128x64"):
+            layer.set_option("fused_tile", tile)
+            d = layer.describe(spec.n)
+            if d["route"] == "fused" and d["tile"] == tile:
+                ys[tile] = layer.forward(x).float().cpu().numpy().astype(np.float64)
+        layer.close()
+        first = next(iter(ys.values()))
+        _say(f"row staging {spec.name} weights={weights} tiles={list(ys)}")
+        # (128 x 64 is built for 3x3 layers; the rows of a strided tile fit the 64 x 64 one alone)
+        assert len(ys) >= (2 if spec.conv.stride == 1 else 1) and all(np.array_equal(first, y) for y in ys.values())
+        assert O.rel_err_inf(first, ref) <= 2e-3
 
 
 def test_kaq_codebook_doubling_is_exact():
