@@ -22,7 +22,7 @@ CASES = [
     # (spec, options, smaller n for the second call)
     (LayerSpec(name="st_tiny_f32", C_out=256, K=256, g=8, M=2, B=8, n=64, codebook_dtype="f32", x_dtype="f32",
                y_dtype="f32", tile_dtype="f32", codebook_std=0.1), {}, 17),
-    (LayerSpec(name="st_lut", C_out=300, K=4096, g=8, M=2, B=8, n=40), {"lut_max_tokens": 64}, 3),
+    (LayerSpec(name="st_lut", C_out=300, K=4096, g=8, M=2, B=8, n=40), {"lut_max_tokens": 64}, 5),
     (LayerSpec(name="st_lut_one", C_out=300, K=4096, g=8, M=4, B=8, n=40),
      {"lut_max_tokens": 64, "table_one_launch": 1}, 5),
     (LayerSpec(name="st_conv_inloop", C_out=192, K=192 * 9, g=8, M=2, B=8, n=2, conv=ConvGeom(192, 3, 3, 1, 1, 32, 32)),
@@ -35,6 +35,8 @@ CASES = [
     (LayerSpec(name="st_dense", C_out=200, K=32 * 9, g=8, M=2, B=8, n=3, conv=ConvGeom(32, 3, 3, 1, 1, 24, 16)),
      {"weights": 2, "record_product": 2}, 1),
     (LayerSpec(name="st_kaq", C_out=96, K=32 * 9, g=9, M=2, B=8, n=2, conv=ConvGeom(32, 3, 3, 1, 1, 16, 16)), {}, 1),
+    # four tokens and fewer: the few-token kernel, which needs no scratch
+    (LayerSpec(name="st_few", C_out=300, K=4096, g=8, M=2, B=8, n=4), {}, 3),
     # the wave-split convolution kernel: one wave per reduction (3x3), two waves per reduction (1x1)
     (LayerSpec(name="st_ws_conv3", C_out=192, K=64 * 9, g=8, M=2, B=8, n=3, conv=ConvGeom(64, 3, 3, 1, 1, 16, 16)),
      {"weights": 2, "record_product": 3}, 1),
