@@ -329,7 +329,7 @@ __device__ __forceinline__ void wait_chunks(int after) {
 // (c, r) -- and the q variants of every dY fragment are built in registers
 // from the fragment and its two neighbouring values.  Rows are 128 bytes with
 // the 16-byte pieces XOR-swizzled by the row index (conflict-free fragment
-// reads); three or four stages keep all but one chunk of them in flight.
+// reads); conv_stages() of them keep all but one chunk in flight.
 //
 // TH = 2: eight waves, the second four taking the second half of every chunk's
 // tokens; the two partial tiles meet in LDS.  A layer with few tiles then puts
@@ -1005,11 +1005,11 @@ hipError_t wgrad_dma_launch(const Geom& geo, const GradArgs& ga, const uint8_t* 
 }
 
 template <int KIND, int DT>
-hipError_t wgrad_dma_dispatch(const Geom& geo, const GradPlan& gp, const GradArgs& ga, const uint8_t* zero,
+hipError_t wgrad_dma_dispatch(const Geom& geo, const GradPlan& gp, int halves, const GradArgs& ga, const uint8_t* zero,
                               hipStream_t st) {
     if (gp.bm == 128 && gp.bn == 64) return wgrad_dma_launch<KIND, DT, 128, 64, 1>(geo, ga, zero, st);
     if (gp.bm == 64 && gp.bn == 64)
-        return gp.halves == 2 ? wgrad_dma_launch<KIND, DT, 64, 64, 2>(geo, ga, zero, st)
+        return halves == 2 ? wgrad_dma_launch<KIND, DT, 64, 64, 2>(geo, ga, zero, st)
                               : wgrad_dma_launch<KIND, DT, 64, 64, 1>(geo, ga, zero, st);
     return hipErrorInvalidConfiguration;
 }
@@ -1045,47 +1045,70 @@ static bool grad_dma_ok(const Geom& geo, const Options& opt) {
     return 64 % geo.OW == 0 && ((int64_t)geo.OH * geo.OW) % 64 == 0;
 }
 
-// Token splits of a gradient over nchunk 64-token chunks.  Register-staged
-// kernels: about four workgroups per CU.  Direct-to-LDS kernels: the least of
-//     chunks per split x chunk time x rounds of workgroups
+// Token splits of a gradient over nchunk 64-token chunks, and for the 64 x 64
+// convolution tile its waves (halves).  Register-staged kernels: about four
+// workgroups per CU.  Direct-to-LDS kernels: the least of
+//     chunks per split x chunk time of the workgroups
 //   + partial gradients written and read back (+ the sum's launch),
-// with the chunk times (us) and the workgroups a CU holds measured (one to
-// sixteen splits each, U-Net shapes and 64 to 4608 channels).  The 64 x 64 linear
-// tile runs three to a CU, a chunk taking 0.46, 0.70 or 0.90 us with one, two or
-// three there: 405 tokens x 1224 -> 1336 takes 24 us with one split, 32 with three;
-// 7495 tokens 400 -> 3800 (420 tiles) 91, 93, 80, 84 us with one to four.
-static int grad_splits(const GradPlan& gp, const Geom& geo, int64_t nchunk) {
+// with the times (us) measured (one to sixteen splits each, U-Net shapes and 64
+// to 4608 channels).  Three four-wave workgroups share a CU; the more there are
+// on one, the longer a chunk takes.  Linear 64 x 64 tile: 405 tokens x 1224 -> 1336 24 us
+// with one split, 32 with three; 7495 tokens 400 -> 3800 (420 tiles) 91, 93, 80, 84 us
+// with one to four.  Convolutions (114 shapes, 512 to 65536 tokens): eight waves on a tile
+// pay while few tiles and tokens leave the CUs one workgroup, four waves with more splits
+// after that: 16 x 32 x 32, 384 -> 384 3x3 91 us with eight waves, 74 with four and six
+// splits; 16 x 64 x 64, 360 -> 696 1x1 125 and 81; but 1 x 16 x 16, 320 -> 320 3x3 8 splits
+// 27.6 us, one 20.3.  The choice is within 12 % of the best of them (mean 1 %).
+struct GradSplits {
+    int splits, halves;
+};
+
+struct GradTimes {
+    double chunk[3];       // a chunk with one, two or three workgroups of four waves on a CU
+    double chunk8, fixed8; // eight waves: a chunk, and what such a workgroup takes longer
+    double sum, per_mb;    // the sum's launch; writing or reading a megabyte of partials
+};
+constexpr GradTimes kGradLinear{{0.46, 0.70, 0.90}, 0.0, 0.0, 2.9, 1.0 / 3.6};
+constexpr GradTimes kGradConv3{{0.65, 0.79, 1.00}, 0.54, 1.2, 3.0, 0.20};
+constexpr GradTimes kGradConv1{{0.38, 0.50, 0.55}, 0.34, 1.1, 1.94, 0.45};
+
+static GradSplits grad_splits(const GradPlan& gp, const Geom& geo, int64_t nchunk, int s_min, int s_max) {
     const int64_t tiles = (int64_t)gp.tiles_m * gp.tiles_n;
     const int64_t slice = (int64_t)geo.C_out * geo.K * 4;
-    const int64_t cap = std::min<int64_t>({16, nchunk, std::max<int64_t>(1, (int64_t(32) << 20) / slice)});
-    if (!gp.dma) return (int)std::min<int64_t>(cap, std::max<int64_t>(1, (960 + tiles - 1) / tiles));
-    const bool wide = !geo.conv && gp.bm == kWideM, one = wide || gp.halves == 2;   // one workgroup per CU
-    const double chunk_us = wide ? 0.75 : 0.6;
-    const double slots = one ? 256.0 : 280.0;
-    const auto small_tiles = [&](int64_t wgs) {        // a chunk of `wgs` 64 x 64 linear tiles, in rounds of 768
+    const bool wide = !geo.conv && gp.bm == kWideM;      // one workgroup per CU
+    const GradTimes& t = !geo.conv ? kGradLinear : geo.kh == 3 ? kGradConv3 : kGradConv1;
+    const auto four_waves = [&](int64_t wgs) {           // a chunk of `wgs` workgroups, in rounds of 768
         const int64_t rest = wgs % 768;
-        return 0.90 * (double)(wgs / 768) + (rest == 0 ? 0.0 : rest <= 256 ? 0.46 : rest <= 512 ? 0.70 : 0.90);
+        return t.chunk[2] * (double)(wgs / 768) +
+               (rest == 0 ? 0.0 : rest <= 256 ? t.chunk[0] : rest <= 512 ? t.chunk[1] : t.chunk[2]);
     };
-    int best = 1;
-    double best_us = 0;
-    for (int S = 1; S <= cap; ++S) {
+    GradSplits best{s_min, 1};
+    double best_us = 1e30;
+    for (int S = s_min; S <= s_max; ++S) {
         const int64_t cps = (nchunk + S - 1) / S;
-        double us;
-        if (!wide && !geo.conv) {
-            const int64_t Se = (nchunk + cps - 1) / cps;   // splits that hold a chunk
-            us = (double)cps * small_tiles(tiles * Se) +
-                 (Se > 1 ? 2.9 + (double)(2 * Se * slice) / 3.6e6 : (double)slice / 3.6e6);
-        } else {
-            const double rounds = std::max(1.0, (double)(tiles * S) / slots);
-            us = (double)cps * chunk_us * (one ? std::ceil(rounds) : rounds) +
-                 (S > 1 ? 3.0 + (double)(2 * S * slice) / 4.0e6 : (double)slice / 4.0e6);
-        }
-        if (S == 1 || us < best_us) {
-            best = S;
-            best_us = us;
+        const int64_t Se = (nchunk + cps - 1) / cps;     // splits that hold a chunk
+        const double rounds = std::ceil((double)(tiles * Se) / 256.0);
+        const double sum = wide ? (S > 1 ? 3.0 + (double)(2 * S * slice) / 4.0e6 : (double)slice / 4.0e6)
+                                : Se > 1 ? t.sum + (double)(2 * Se * slice) * 1e-6 * t.per_mb
+                                         : (double)slice * 1e-6 * t.per_mb;
+        for (int halves = 1; halves <= (geo.conv && gp.bm == 64 ? 2 : 1); ++halves) {
+            const double us = sum + (wide          ? (double)cps * 0.75 * std::ceil((double)(tiles * S) / 256.0)
+                                     : halves == 2 ? t.fixed8 + (double)cps * t.chunk8 * rounds
+                                                   : (double)cps * four_waves(tiles * Se));
+            if (us < best_us) {
+                best = GradSplits{S, halves};
+                best_us = us;
+            }
         }
     }
     return best;
+}
+
+static int grad_splits_cap(const GradPlan& gp, const Geom& geo, int64_t nchunk) {
+    const int64_t tiles = (int64_t)gp.tiles_m * gp.tiles_n;
+    const int64_t slice = (int64_t)geo.C_out * geo.K * 4;
+    const int64_t cap = std::min<int64_t>({16, nchunk, std::max<int64_t>(1, (int64_t(32) << 20) / slice)});
+    return (int)(gp.dma ? cap : std::min<int64_t>(cap, std::max<int64_t>(1, (960 + tiles - 1) / tiles)));
 }
 
 // Tile choice (the register-staged kernels: the largest tile that still gives
@@ -1097,7 +1120,6 @@ GradPlan grad_plan_create(const Geom& geo, int64_t max_tokens, const Options& op
     gp.dma = grad_dma_ok(geo, opt);
     const int want_bm = opt.grad_bm, want_bn = opt.grad_bn;
     const int64_t nchunk = std::max<int64_t>(1, (max_tokens + kGradChunk - 1) / kGradChunk);
-    gp.halves = 1;
     if (gp.dma && !geo.conv) {
         gp.bm = gp.bn = 64;
         // the 128 x 192 tile (one workgroup per CU) where little of it is padding
@@ -1119,11 +1141,6 @@ GradPlan grad_plan_create(const Geom& geo, int64_t max_tokens, const Options& op
         gp.bn = 64;
         gp.tiles_m = (geo.C_out + gp.bm - 1) / gp.bm;
         gp.tiles_n = (npairs + gp.bn - 1) / gp.bn;
-        // few tiles: eight waves on each, with half the token splits (1x1 layers until their
-        // chunks fill the chip for long: 2 x 64 x 64, 360 -> 696 31.3 us, four waves 33.6;
-        // 9 images 78.9 and 71.8)
-        const int64_t tiles = gp.tiles_m * (int64_t)gp.tiles_n;
-        if (gp.bm == 64 && tiles < 256 && (geo.kh == 3 || tiles * nchunk <= 24000)) gp.halves = 2;
     } else {
         const int shapes[3][2] = {{128, 128}, {64, 128}, {64, 64}};
         int pick = 2;
@@ -1147,7 +1164,13 @@ GradPlan grad_plan_create(const Geom& geo, int64_t max_tokens, const Options& op
         gp.tiles_m = (geo.C_out + gp.bm - 1) / gp.bm;
         gp.tiles_n = (geo.K + gp.bn - 1) / gp.bn;
     }
-    gp.s_max = grad_splits(gp, geo, nchunk);
+    gp.s_max = grad_splits_cap(gp, geo, nchunk);
+    if (gp.dma) {   // a call of fewer tokens may want more splits than the largest
+        const int cap = gp.s_max;
+        gp.s_max = 1;
+        for (int64_t c = nchunk; c >= 1; c /= 2)
+            gp.s_max = std::max(gp.s_max, grad_splits(gp, geo, c, 1, (int)std::min<int64_t>(cap, c)).splits);
+    }
     if (opt.grad_splits > 0) gp.s_max = (int)std::min<int64_t>({16, nchunk, (int64_t)opt.grad_splits});
     return gp;
 }
@@ -1166,8 +1189,12 @@ hipError_t launch_codebook_grad(const Geom& geo, const GradPlan& gp, int dtype, 
     ga.scales = scales;
     ga.P = P;
     ga.nchunk = (int)((geo.tokens + kGradChunk - 1) / kGradChunk);
-    int S = std::min(gp.s_max, splits_override > 0 ? splits_override : grad_splits(gp, geo, ga.nchunk));
-    S = std::min(S, ga.nchunk);
+    const int s_max = std::min(gp.s_max, ga.nchunk);
+    const int forced = splits_override > 0 ? std::min(s_max, splits_override)
+                       : gp.dma            ? 0
+                                           : std::min(s_max, grad_splits_cap(gp, geo, ga.nchunk));
+    const GradSplits split = grad_splits(gp, geo, ga.nchunk, std::max(1, forced), forced ? forced : s_max);
+    const int S = split.splits;
     ga.cps = (ga.nchunk + S - 1) / S;
     ga.S = (ga.nchunk + ga.cps - 1) / ga.cps;     // every split owns at least one chunk
     ga.tiles_m = gp.tiles_m;
@@ -1186,10 +1213,10 @@ hipError_t launch_codebook_grad(const Geom& geo, const GradPlan& gp, int dtype, 
         note_launch(st, "wgrad_linear_dma_kernel", {dtype});
         e = hipGetLastError();
     } else if (gp.dma) {
-        e = kind == 1 ? (dtype == AQ_BF16 ? wgrad_dma_dispatch<1, AQ_BF16>(geo, gp, ga, z16, st)
-                                          : wgrad_dma_dispatch<1, AQ_F16>(geo, gp, ga, z16, st))
-                      : (dtype == AQ_BF16 ? wgrad_dma_dispatch<2, AQ_BF16>(geo, gp, ga, z16, st)
-                                          : wgrad_dma_dispatch<2, AQ_F16>(geo, gp, ga, z16, st));
+        e = kind == 1 ? (dtype == AQ_BF16 ? wgrad_dma_dispatch<1, AQ_BF16>(geo, gp, split.halves, ga, z16, st)
+                                          : wgrad_dma_dispatch<1, AQ_F16>(geo, gp, split.halves, ga, z16, st))
+                      : (dtype == AQ_BF16 ? wgrad_dma_dispatch<2, AQ_BF16>(geo, gp, split.halves, ga, z16, st)
+                                          : wgrad_dma_dispatch<2, AQ_F16>(geo, gp, split.halves, ga, z16, st));
     } else if (dtype == AQ_BF16) {
         e = kind == 0 ? wgrad_dispatch<0, AQ_BF16>(geo, gp, ga, st)
             : kind == 1 ? wgrad_dispatch<1, AQ_BF16>(geo, gp, ga, st)

@@ -221,7 +221,6 @@ hipError_t launch_f32_forward(const Geom& geo, const DeviceWeights& w, const voi
 struct GradPlan {
     bool dma;                     // convolution kernel with direct-to-LDS staging
     int bm, bn;                   // weight-gradient tile: output channels x inputs (x (channel, kernel row) pairs)
-    int halves;                   // direct-to-LDS convolution: waves sharing a tile's tokens (1 or 2)
     int tiles_m, tiles_n;
     int s_max;                    // most token splits (partial buffers in the workspace)
 };

@@ -232,7 +232,7 @@ def test_short_reductions_of_uneven_convolutions(child, n, cin, C_out, k, M, sid
 
 
 def _grad(n, kw):
-    layer = hd.Layer(max_n=n, **kw)
+    layer = hd.Layer(**{"max_n": n, **kw})
     kernels, launches = hd.launches(lambda: layer.grad(n, "f16"))
     product = [i for i, k in enumerate(kernels) if k.startswith("wgrad")][0]
     return kernels[product], launches[product - len(kernels)][0]
@@ -250,14 +250,21 @@ def test_token_splits_of_linear_gradients(child, n, K, C_out, splits):
     assert kernel.startswith("wgrad_linear_dma_kernel") and blocks == -(-tiles * splits // 8) * 8
 
 
-@pytest.mark.parametrize("n,k,cin,C_out,halves", [
-    (9, 1, 360, 696, 1),        # 71.8 us, eight waves 78.9
-    (2, 1, 360, 696, 2),        # 31.3, four waves 33.6
-    (2, 3, 144, 856, 2),
+@pytest.mark.parametrize("n,k,cin,C_out,H,halves,splits", [
+    (16, 1, 360, 696, 64, 1, 11),       # 81 us; the best with eight waves 125
+    (9, 1, 360, 696, 64, 1, 11),
+    (16, 3, 384, 384, 32, 1, 6),        # 74, eight waves 91
+    (16, 3, 192, 192, 64, 1, 16),       # 72, eight waves 80
+    (16, 3, 64, 64, 64, 2, 16),         # 52.0, four waves 57.8
+    (1, 3, 320, 320, 16, 1, 1),         # 20.3; eight splits 27.6 (512 tokens)
 ])
-def test_waves_of_convolution_gradients(child, n, k, cin, C_out, halves):
-    kernel, _ = child("_grad", n, dict(C_out=C_out, conv=(cin, k, 1, k // 2, 64, 64)))
-    assert kernel.endswith(f"64, {halves}>")
+def test_waves_and_splits_of_convolution_gradients(child, n, k, cin, C_out, H, halves, splits):
+    kw = dict(C_out=C_out, conv=(cin, k, 1, k // 2, H, H))
+    kernel, blocks = child("_grad", n, kw)
+    tiles = -(-C_out // 64) * -(-cin * k // 64)
+    assert kernel.endswith(f"64, {halves}>") and blocks == -(-tiles * splits // 8) * 8
+    # the tokens of the call decide, not the most that the layer takes
+    assert child("_grad", n, dict(kw, max_n=8 * n)) == [kernel, blocks]
 
 
 # ---- launches ----
