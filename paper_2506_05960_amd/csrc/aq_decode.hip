@@ -330,17 +330,16 @@ operand_records_f16_kernel(const u32x4* __restrict__ cb, const uint32_t* __restr
 // Records of a 3x3 chunk in the kernel-aware format (g = 9: one group per
 // input channel's 3x3 filter) from fp16 codebooks padded to 16 values per row:
 // a codeword is one 16-byte and one 4-byte read, of a copy in LDS where codes
-// are 8 bits wide (1152 -> 576, M = 2: 9.6 -> 8.1 us), and the M codewords of a group are summed in fp16 in
+// are 8 bits wide and workgroups many (1152 -> 576, M = 2: 9.6 -> 8.1 us), and the M codewords of a group are summed in fp16 in
 // ascending m (the same IEEE fp16 sums as operand_records_kernel).  A record
 // (chunk c, position s, channel n, lane half q) holds tap s of the 8 input
 // channels 16c + 8q + e; two threads share it, each decoding 4 channels and
 // writing its 8-byte half.
-template <typename CodeT, int MC>
+template <typename CodeT, int MC, bool LDS>
 __device__ __forceinline__ void records_g9_f16_body(const uint8_t* __restrict__ cbp, const CodeT* __restrict__ codes,
                                                     uint8_t* __restrict__ rec, int nchunk, int C_out, int Gn, int B,
                                                     uint32_t idx,        // (chunk, channel, half, quarter)
-                                                    u32x4* cb_lds) {     // 8-bit codes: 2 MC << B pieces
-    constexpr bool LDS = sizeof(CodeT) == 1;
+                                                    u32x4* cb_lds) {     // LDS: 2 MC << B pieces
     const bool live = idx < (uint32_t)nchunk * (uint32_t)C_out * 4u;
     const uint32_t rid = live ? idx >> 1 : 0u;
     const int hq = (int)(idx & 1u);
@@ -405,12 +404,12 @@ __device__ __forceinline__ void records_g9_f16_body(const uint8_t* __restrict__ 
     }
 }
 
-template <typename CodeT, int MC>
+template <typename CodeT, int MC, bool LDS>
 __global__ void __launch_bounds__(256)
 operand_records_g9_f16_kernel(const uint8_t* __restrict__ cbp, const CodeT* __restrict__ codes,
                               uint8_t* __restrict__ rec, int nchunk, int C_out, int Gn, int B) {
-    __shared__ u32x4 cb_lds[sizeof(CodeT) == 1 ? 2 * MC * 256 : 1];
-    records_g9_f16_body<CodeT, MC>(cbp, codes, rec, nchunk, C_out, Gn, B, blockIdx.x * 256u + threadIdx.x, cb_lds);
+    __shared__ u32x4 cb_lds[LDS ? 2 * MC * 256 : 1];
+    records_g9_f16_body<CodeT, MC, LDS>(cbp, codes, rec, nchunk, C_out, Gn, B, blockIdx.x * 256u + threadIdx.x, cb_lds);
 }
 
 // Batched forms: one launch decodes the records of several layers that share
@@ -442,7 +441,7 @@ __global__ void __launch_bounds__(256) operand_records_g9_f16_batch_kernel(const
     const int l = record_job_of(b, blockIdx.x);
     const RecordJob& j = b.job[l];
     __shared__ u32x4 cb_lds[sizeof(CodeT) == 1 ? 2 * MC * 256 : 1];
-    records_g9_f16_body<CodeT, MC>(static_cast<const uint8_t*>(j.cb), static_cast<const CodeT*>(j.codes),
+    records_g9_f16_body<CodeT, MC, sizeof(CodeT) == 1>(static_cast<const uint8_t*>(j.cb), static_cast<const CodeT*>(j.codes),
                                    static_cast<uint8_t*>(j.rec), j.nchunk, j.C_out, j.G, j.B,
                                    (blockIdx.x - b.start[l]) * 256u + threadIdx.x, cb_lds);
 }
@@ -515,9 +514,22 @@ static hipError_t records_dispatch(const Geom& geo, const FusedPlan& plan, const
         const uint8_t* cbp = static_cast<const uint8_t*>(w.cb9);
         const dim3 grid9((unsigned)((2 * n + 255) / 256));   // two threads per record
         uint8_t* r8 = static_cast<uint8_t*>(rec);
-#define AQ_REC9(MC)                                                                                       \
-    operand_records_g9_f16_kernel<CodeT, MC><<<grid9, block, 0, st>>>(cbp, codes, r8, plan.nchunk, geo.C_out, \
-                                                                      geo.G, geo.B)
+        // the copy pays with more than a workgroup per CU, as above (below 64 workgroups 0.1 to 0.2 us
+        // longer with M = 2, 0.2 to 0.6 with M = 4)
+        const bool lds = grid9.x >= 256;
+#define AQ_REC9(MC)                                                                                             \
+    do {                                                                                                        \
+        if constexpr (sizeof(CodeT) == 1) {                                                                     \
+            if (lds) {                                                                                          \
+                operand_records_g9_f16_kernel<CodeT, MC, true><<<grid9, block, 0, st>>>(cbp, codes, r8,         \
+                                                                                        plan.nchunk, geo.C_out, \
+                                                                                        geo.G, geo.B);          \
+                break;                                                                                          \
+            }                                                                                                   \
+        }                                                                                                       \
+        operand_records_g9_f16_kernel<CodeT, MC, false><<<grid9, block, 0, st>>>(cbp, codes, r8, plan.nchunk,   \
+                                                                                 geo.C_out, geo.G, geo.B);      \
+    } while (0)
         if (geo.M == 1) AQ_REC9(1);
         else if (geo.M == 2) AQ_REC9(2);
         else AQ_REC9(4);
