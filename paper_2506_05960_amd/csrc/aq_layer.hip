@@ -963,6 +963,33 @@ bool bf16_generic(const Geom& geo, const aq::FusedPlan& p) {
     return odd4 && !p.rec_only && wgs > 256 && geo.K < std::min<int64_t>(1024, 150 * ((wgs + 255) / 256));
 }
 
+// Convolutions that do not tile (1x1: planes of an odd pixel count), in more than one round of
+// 64 x 64 tiles: the generic kernel where its estimate is not clearly the longer one.  Both in us, in rounds of 256 workgroups,
+// fitted to 126 layers with one of the tiles on a compute unit (K = 72 to 632; the fused kernel's
+// within 5 % for 1x1 and 14 % for 3x3, the generic one's mostly within 15 %) and 40 with two.  Fused
+// and generic, M = 1: 3x3 on 61 x 71, 25986 tokens 16 -> 400 108 and 59, 24 -> 290 84 and 52, 46683
+// tokens 64 -> 209 (M = 2) 121 and 130; 1x1 on 29 x 39, 53157 tokens 136 -> 832 (M = 2) 359 and 202, 13 x
+// 33, 10725 tokens 400 -> 304 (M = 2) 46 and 68.
+bool uneven_rounds_generic(const Geom& geo, const Geom& kgeo, const aq::FusedPlan& p) {
+    if (p.wsplit || p.splitk > 1 || p.ntiles <= 256 || (geo.kh == 1 && kgeo.W % 2 == 0)) return false;
+    // one chunk for four waves, one codebook (22960 tokens on 7 x 41, 16 -> 720 101 and 83)
+    if (p.bm == 128 && geo.kh == 3 && geo.M == 1 && geo.K <= 144) return true;
+    if (p.bm != 64 || p.bn != 64) return false;
+    const auto tiles = [&](int64_t bm, int64_t bn) { return ((geo.tokens + bm - 1) / bm) * ((geo.C_out + bn - 1) / bn); };
+    const auto rounds = [](int64_t n) { return (double)((n + 255) / 256); };
+    const bool k3 = geo.kh == 3, two = p.lds_bytes <= kLdsBytes / 2;
+    const double K = geo.K, m4 = geo.M >= 4;
+    const double round = k3 ? (two ? 5.5 + 0.0035 * K : 7.0 + 0.0043 * K) : (two ? 4.0 + 0.0085 * K : 7.0 + 0.0092 * K);
+    const double fused = rounds(p.ntiles) * round + (k3 ? 6.8 - 0.0087 * K : 4.1) +
+                         (geo.M == 1 || geo.M == 2 || geo.M == 4 ? 0.0 : 8.0);   // records value by value
+    const int64_t t128 = tiles(128, 128), t64 = tiles(128, 64);
+    double generic = t128 >= 256 ? rounds(t128) * (7.6 + (0.0505 + 0.0176 * m4 - 0.0137 * k3) * K) + 8.0 + 0.0595 * K
+                     : t64 >= 256  ? rounds(t64) * (5.2 + (0.0508 + 0.0114 * m4 - 0.0113 * k3) * K) + 2.6 + 0.0254 * K
+                                   : 7.7 + (0.069 + 0.0356 * m4 - 0.0098 * k3) * K;
+    if (geo.B > 8 && geo.M == 1) generic *= 0.85;     // one codebook, read as it is from the L2
+    return generic < 1.08 * fused;
+}
+
 Route plan_route(const aq_layer* L, const Geom& geo) {
     Route r{};
     const aq_layer_desc& d = L->desc;
@@ -1114,6 +1141,7 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
         fp.cb_bytes = 0;
         planned = fused_plan_tile(r.geo, opt, L->part_bytes, d.x_dtype, &fp);
     }
+    if (planned && r.uneven && unforced && opt.generic != 1 && uneven_rounds_generic(geo, r.geo, fp)) planned = false;
     if (planned) {
         order(fp);
         fp.tile_div = fp.nmajor ? (int)((geo.tokens + fp.bm - 1) / fp.bm) : (geo.C_out + fp.bn - 1) / fp.bn;

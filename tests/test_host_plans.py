@@ -231,6 +231,21 @@ def test_short_reductions_of_uneven_convolutions(child, n, cin, C_out, k, M, sid
     assert got[:2] == [route, weights]
 
 
+@pytest.mark.parametrize("n,k,cin,C_out,H,W,M,B,route", [
+    (6, 3, 16, 400, 61, 71, 1, 8, "generic"),        # 59 us, fused 108
+    (37, 3, 24, 290, 11, 65, 1, 8, "generic"),       # 52, 84
+    (117, 3, 24, 638, 7, 69, 4, 8, "generic"),       # 226, 316
+    (80, 3, 16, 720, 7, 41, 1, 12, "generic"),       # 83, 101: two tiles on a compute unit
+    (63, 3, 64, 209, 13, 57, 2, 8, "fused"),         # 121, generic 130
+    (47, 1, 136, 832, 29, 39, 2, 8, "generic"),      # 202, 359
+    (13, 1, 272, 272, 61, 29, 1, 12, "generic"),     # 70, 84
+    (25, 1, 400, 304, 13, 33, 2, 8, "fused"),        # 46, 68
+    (1, 1, 152, 360, 13, 33, 2, 8, "fused"),         # one round
+])
+def test_uneven_convolutions_in_many_tiles(child, n, k, cin, C_out, H, W, M, B, route):
+    assert child("_route", n, dict(C_out=C_out, M=M, B=B, conv=(cin, k, 1, k // 2, H, W)))[0] == route
+
+
 def _grad(n, kw):
     layer = hd.Layer(**{"max_n": n, **kw})
     kernels, launches = hd.launches(lambda: layer.grad(n, "f16"))
