@@ -768,6 +768,26 @@ bool code_records_fit(const Geom& geo, const aq::FusedPlan& p) {
     return (int64_t)p.nchunk * geo.C_out * 2 * p.rec_bytes < kOffsetLimit;
 }
 
+// The static array of the allocation-free forward.
+constexpr size_t kScratchBytes = size_t(64) << 20;             // per GPU
+constexpr size_t kScratchCounterBytes = size_t(256) << 10;     // arrival counters first (table, then K split)
+constexpr size_t kScratchLutCounters = 0;
+constexpr size_t kScratchSplitCounters = size_t(128) << 10;
+constexpr int kScratchMaxDevices = 64;
+
+size_t align256(size_t b) { return (b + 255) / 256 * 256; }
+
+// Scratch of a fused-kernel or record-product plan within the static array's data area.
+size_t plan_scratch(const Geom& geo, const aq::FusedPlan& p) {
+    return (p.dec == aq::FUSED_DEC_REC ? align256(aq::operand_record_bytes(geo, p)) : 0) +
+           (p.splitk > 1 ? align256((size_t)p.splitk * p.ntiles * p.bm * p.bn * 4) : 0);
+}
+
+// The static array holds a layer's records.
+bool static_holds_records(const Geom& geo, const aq::FusedPlan& p) {
+    return align256(aq::operand_record_bytes(geo, p)) <= kScratchBytes - kScratchCounterBytes;
+}
+
 // Pre-decoded mode (operands decoded once per forward into records the main
 // loop reads with plain 16-byte loads) instead of decoding inside the main
 // loop: chosen for codebooks too large for LDS (their codeword reads from L2
@@ -794,6 +814,10 @@ bool use_predecoded(const aq_layer* L, const Geom& geo) {
         // M = 2 once the reduction is long for the token count (conv64, 8192
         // tokens x K = 1728, stays in-loop: 13.5 vs 15.1 us)
         if (p.mc >= 4 && geo.tokens >= 512) return true;
+        // M = 1 past two rounds of 64 x 96 tiles, whose width then takes the 64 x 64 tile (records and
+        // in-loop: 16896 tokens 864 -> 112 19.0 and 23.1 us, 22784 tokens 432 -> 120 15.0 and 17.1,
+        // 20736 tokens 1584 -> 112 22.7 and 27.9; one round, 19968 tokens 432 -> 88 14.8 and 12.8)
+        if (p.mc == 1 && geo.K >= 288 && token_tiles * ((geo.C_out + 95) / 96) > 512 && static_holds_records(geo, p)) return true;
         return tm >= 32768 || (geo.K >= 3456 && geo.tokens >= 8192) || (geo.K >= 5000 && geo.tokens >= 2048) ||
                geo.K >= 13000;
     }
@@ -861,21 +885,6 @@ bool wsplit_plan(const Geom& geo, const aq::Options& opt, int wk, aq::FusedPlan*
     q.inv_ntiles = 1.0f / (float)nt;
     *p = q;
     return true;
-}
-
-// The static array of the allocation-free forward.
-constexpr size_t kScratchBytes = size_t(64) << 20;             // per GPU
-constexpr size_t kScratchCounterBytes = size_t(256) << 10;     // arrival counters first (table, then K split)
-constexpr size_t kScratchLutCounters = 0;
-constexpr size_t kScratchSplitCounters = size_t(128) << 10;
-constexpr int kScratchMaxDevices = 64;
-
-size_t align256(size_t b) { return (b + 255) / 256 * 256; }
-
-// Scratch of a fused-kernel or record-product plan within the static array's data area.
-size_t plan_scratch(const Geom& geo, const aq::FusedPlan& p) {
-    return (p.dec == aq::FUSED_DEC_REC ? align256(aq::operand_record_bytes(geo, p)) : 0) +
-           (p.splitk > 1 ? align256((size_t)p.splitk * p.ntiles * p.bm * p.bn * 4) : 0);
 }
 
 // The records alone fit the static array, the partial tiles beside them do not.

@@ -246,6 +246,16 @@ def test_uneven_convolutions_in_many_tiles(child, n, k, cin, C_out, H, W, M, B, 
     assert child("_route", n, dict(C_out=C_out, M=M, B=B, conv=(cin, k, 1, k // 2, H, W)))[0] == route
 
 
+@pytest.mark.parametrize("n,cin,C_out,side,weights", [
+    (324, 176, 112, 8, "records"),               # 22.7 us, in the loop 27.9
+    (89, 48, 120, 16, "records"),                # 15.0, 17.1
+    (78, 48, 88, 16, "in-loop-lds-fp16"),        # 12.8, 14.8: one round of 64 x 96 tiles
+    (89, 16, 120, 16, "in-loop-lds-fp16"),
+])
+def test_convolutions_of_one_codebook(child, n, cin, C_out, side, weights):
+    assert child("_route", n, dict(C_out=C_out, M=1, conv=(cin, 3, 1, 1, side, side)))[:2] == ["fused", weights]
+
+
 def _grad(n, kw):
     layer = hd.Layer(**{"max_n": n, **kw})
     kernels, launches = hd.launches(lambda: layer.grad(n, "f16"))
