@@ -957,7 +957,8 @@ bool few_route(const aq_layer* L, const Geom& geo) {
 // all with unaligned output rows (C_out no multiple of 8) in many tiles.  Generic
 // and fused, us: 1 token 64 -> 1152, M = 1 4.0 and 4.5; 1000 tokens 64 -> 1152, M = 3
 // (a records launch) 8.4 and 9.4, 144 -> 1152 11.2 and 10.0; M = 1, B = 12 (records)
-// 3 tokens 88 -> 1152 4.3 and 6.7, 70 tokens 144 -> 4608 7.4 and 8.9; 361 tokens 144 ->
+// 3 tokens 88 -> 1152 4.3 and 6.7, 304 -> 1030 7.2 and 9.0, 1025 tokens 192 -> 109 7.8 and
+// 8.8, 70 tokens 144 -> 4608 7.4 and 8.9; M = 3 1 token 144 -> 1472 6.8 and 8.3; 361 tokens 144 ->
 // 3451, M = 1 8.8 and 10.2; 3561 tokens 64 -> 1007, M = 2 12.6 and 19.3; 9894 tokens
 // 640 -> 1007, M = 2 57.3 and 82.4.
 bool bf16_generic(const Geom& geo, const aq::FusedPlan& p) {
@@ -966,7 +967,10 @@ bool bf16_generic(const Geom& geo, const aq::FusedPlan& p) {
     if (geo.K <= 64 && ((geo.tokens <= 4 && (geo.M == 1 || odd8)) || (odd8 && wgs > 64))) return true;
     // records only: a records launch for few codewords; one codebook's the generic kernel reads fastest
     if (p.rec_only && geo.M > 1 && geo.K <= 96 && wgs <= 256) return true;
-    if (p.rec_only && geo.M == 1 && ((geo.K <= 300 && geo.tokens <= 4) || (geo.K <= 160 && wgs <= 256 && geo.C_out > 128)))
+    if (p.rec_only && geo.M > 1 && (geo.B <= 8 ? geo.K <= 168 && geo.tokens <= 16 : geo.K <= 128 && geo.tokens <= 4)) return true;
+    if (p.rec_only && geo.M == 1 &&
+        ((geo.K <= 448 && geo.tokens <= 16) || (geo.K <= 330 && geo.tokens <= 36) || (geo.K <= 240 && wgs <= 128) ||
+         (geo.K <= 160 && wgs <= 256 && geo.C_out > 128)))
         return true;
     if (odd4 && geo.K < 200 && wgs > 128) return true;
     return odd4 && !p.rec_only && wgs > 256 && geo.K < std::min<int64_t>(1024, 150 * ((wgs + 255) / 256));

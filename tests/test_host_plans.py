@@ -207,6 +207,11 @@ def test_linear_layers_of_one_codebook(child, n, K, C_out, route, x):
     (1000, 144, 1152, 3, 8, "fused"),     # 10.0, generic 11.2
     (3, 88, 1152, 1, 12, "generic"),      # 4.3, 6.7
     (70, 144, 4608, 1, 12, "generic"),    # 7.4, 8.9
+    (4, 304, 1030, 1, 12, "generic"),     # 7.2, 9.0
+    (1025, 192, 109, 1, 12, "generic"),   # 7.8, 8.8
+    (633, 280, 64, 1, 12, "fused"),       # 8.4, 9.0
+    (1, 144, 1472, 3, 4, "generic"),      # 6.8, 8.6
+    (2, 240, 630, 3, 4, "fused"),         # 8.4, 9.8
     (361, 144, 3451, 1, 8, "generic"),    # 8.8, 10.2
     (3561, 64, 1007, 2, 8, "generic"),    # 12.6, 19.3
     (9894, 640, 1007, 2, 8, "generic"),   # 57.3, 82.4
