@@ -841,6 +841,14 @@ bool use_predecoded(const aq_layer* L, const Geom& geo) {
                 return tiles >= 256 || (tiles > 128 && ((int64_t)geo.K * geo.C_out <= 1000000 || geo.C_out % 8 != 0));
             return tiles >= 192 && (geo.tokens >= 2048 || p.mc >= 4);
         }
+        if (p.dec == aq::FUSED_DEC_BF16) {
+            // bf16 rows the wave-split product does not take (C_out % 4 != 0), by 64 x 96 tiles: records
+            // past one round with M = 4 and past four with M = 2 (records and in-loop: 11162 tokens
+            // 672 -> 197, M = 4 20 and 42 us, 1784 tokens 2312 -> 4017, M = 4 99 and 236, 6976 tokens 1144 ->
+            // 1415, M = 2 61 and 104; 417 tokens 400 -> 3339, M = 4, one round 18.6 and 14.6)
+            const int64_t wgs = token_tiles * ((geo.C_out + 95) / 96);
+            return (p.mc == 4 && wgs > 256) || (p.mc == 2 && wgs >= 1024);
+        }
         return p.mc >= 4 && geo.C_out >= 1152 && geo.tokens >= 2048;
     }
     return p.mc >= 4 && geo.tokens >= 32768;
@@ -972,8 +980,8 @@ bool bf16_generic(const Geom& geo, const aq::FusedPlan& p) {
         ((geo.K <= 448 && geo.tokens <= 16) || (geo.K <= 330 && geo.tokens <= 36) || (geo.K <= 240 && wgs <= 128) ||
          (geo.K <= 160 && wgs <= 256 && geo.C_out > 128)))
         return true;
-    if (odd4 && geo.K < 200 && wgs > 128) return true;
-    return odd4 && !p.rec_only && wgs > 256 && geo.K < std::min<int64_t>(1024, 150 * ((wgs + 255) / 256));
+    if (odd4 && geo.K <= 200 && wgs > 128) return true;
+    return odd4 && !p.rec_only && wgs > 256 && geo.K < std::min<int64_t>(1024, 160 * ((wgs + 255) / 256));
 }
 
 // Convolutions that do not tile (1x1: planes of an odd pixel count), in more than one round of
@@ -1149,6 +1157,18 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
         planned = fused_plan_tile(r.geo, opt, L->part_bytes, d.x_dtype, &fp);
     if (!planned && r.uneven && fits31 && rec_fit && opt.generic != 1 && fp.dec != aq::FUSED_DEC_REC && opt.weights != 1) {
         // long output rows stage more pixels than the in-loop tiles hold
+        fp.dec = aq::FUSED_DEC_REC;
+        fp.mc = 1;
+        fp.cb_bytes = 0;
+        planned = fused_plan_tile(r.geo, opt, L->part_bytes, d.x_dtype, &fp);
+    }
+    if (planned && unforced && rec_fit && fp.kind == 0 && (fp.dec == aq::FUSED_DEC_PK16 || fp.dec == aq::FUSED_DEC_BF16) && fp.mc == 1 &&
+        geo.C_out % 4 != 0 && fp.bn == 96 && fp.ntiles >= 704 && geo.K * 5 <= fp.ntiles * 6 &&
+        static_holds_records(geo, fp)) {
+        // one codebook, rows the wave-split product does not take, in many 64 x 96 tiles: records
+        // (and in-loop: 6270 tokens 144 -> 1891 38 and 63 us, 6738 tokens 704 -> 1526 45 and 66, 6893
+        // tokens 1616 -> 1386 74 and 89; 1260 tokens 2712 -> 4234 85 and 68; bf16 4325 tokens 1144 -> 2433
+        // 75 and 90)
         fp.dec = aq::FUSED_DEC_REC;
         fp.mc = 1;
         fp.cb_bytes = 0;

@@ -261,6 +261,23 @@ def test_convolutions_of_one_codebook(child, n, cin, C_out, side, weights):
     assert child("_route", n, dict(C_out=C_out, M=1, conv=(cin, 3, 1, 1, side, side)))[:2] == ["fused", weights]
 
 
+@pytest.mark.parametrize("n,K,C_out,M,dt,route,weights", [
+    (6270, 144, 1891, 1, "f16", "fused", "records"),           # 38 us, in the loop 63
+    (6893, 1616, 1386, 1, "f16", "fused", "records"),          # 74, 89
+    (1260, 2712, 4234, 1, "f16", "fused", "in-loop-lds-fp16"),   # 68, 85
+    (1250, 152, 806, 1, "f16", "fused", "in-loop-lds-fp16"),     # one round
+    (4325, 1144, 2433, 1, "bf16", "fused", "records"),         # 75, 90
+    (11162, 672, 197, 4, "bf16", "fused", "records"),          # 20, 42
+    (417, 400, 3339, 4, "bf16", "fused", "in-loop-lds-bf16"),  # 14.6, 18.6
+    (6976, 1144, 1415, 2, "bf16", "fused", "records"),         # 61, 104
+    (1174, 728, 4279, 2, "bf16", "fused", "in-loop-lds-bf16"),   # 35, 39
+    (1088, 312, 2603, 1, "bf16", "generic", None),             # 17.5, 20.8
+])
+def test_linear_layers_of_odd_output_rows(child, n, K, C_out, M, dt, route, weights):
+    kw = dict(C_out=C_out, K=K, M=M, x=dt, cb=dt, tile=dt, y="f32" if dt == "bf16" else "f16")
+    assert child("_route", n, kw, {"lut_max_tokens": -1})[:2] == [route, weights]
+
+
 def _grad(n, kw):
     layer = hd.Layer(**{"max_n": n, **kw})
     kernels, launches = hd.launches(lambda: layer.grad(n, "f16"))
