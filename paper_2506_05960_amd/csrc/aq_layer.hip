@@ -977,7 +977,8 @@ bool bf16_generic(const Geom& geo, const aq::FusedPlan& p) {
     if (p.rec_only && geo.M > 1 && geo.K <= 96 && wgs <= 256) return true;
     if (p.rec_only && geo.M > 1 && (geo.B <= 8 ? geo.K <= 168 && geo.tokens <= 16 : geo.K <= 128 && geo.tokens <= 4)) return true;
     if (p.rec_only && geo.M == 1 &&
-        ((geo.K <= 448 && geo.tokens <= 16) || (geo.K <= 330 && geo.tokens <= 36) || (geo.K <= 240 && wgs <= 128) ||
+        ((geo.K <= 448 && geo.tokens <= 16) || (geo.K <= 330 && geo.tokens <= 36) ||
+         (geo.K <= 240 && wgs <= 128 && (geo.K > 64 || geo.C_out > 128 || geo.tokens <= 64)) ||
          (geo.K <= 160 && wgs <= 256 && geo.C_out > 128)))
         return true;
     if (odd4 && geo.K <= 200 && wgs > 128) return true;
