@@ -843,11 +843,12 @@ bool use_predecoded(const aq_layer* L, const Geom& geo) {
         }
         if (p.dec == aq::FUSED_DEC_BF16) {
             // bf16 rows the wave-split product does not take (C_out % 4 != 0), by 64 x 96 tiles: records
-            // past one round with M = 4 and past four with M = 2 (records and in-loop: 11162 tokens
+            // past one round with M = 4, past four (K to 640: not quite two) with M = 2 (records and in-loop: 11162 tokens
             // 672 -> 197, M = 4 20 and 42 us, 1784 tokens 2312 -> 4017, M = 4 99 and 236, 6976 tokens 1144 ->
-            // 1415, M = 2 61 and 104; 417 tokens 400 -> 3339, M = 4, one round 18.6 and 14.6)
+            // 1415, M = 2 61 and 104, 6386 tokens 344 -> 438 16.4 and 21.6, 1094 tokens 488 -> 1389 14.8 and
+            // 13.2; 417 tokens 400 -> 3339, M = 4, one round 18.6 and 14.6)
             const int64_t wgs = token_tiles * ((geo.C_out + 95) / 96);
-            return (p.mc == 4 && wgs > 256) || (p.mc == 2 && wgs >= 1024);
+            return (p.mc == 4 && wgs > 256) || (p.mc == 2 && (wgs >= 1024 || (wgs >= 448 && geo.K <= 640)));
         }
         return p.mc >= 4 && geo.C_out >= 1152 && geo.tokens >= 2048;
     }
@@ -1135,13 +1136,12 @@ Route plan_route(const aq_layer* L, const Geom& geo) {
                    geo.K <= 12000) {
             // 3x3 on rows under 16 tokens: from 192 tiles of 128 x 128, up to where the
             // fragment reads' conflicts even it out
-            // (8 x 8 images, records included: 64 x 960 -> 960, B = 16 82.6 against the
-            // fused kernel's 89.1 us, 128 x 512 -> 512 46.4 and 53.2, 64 x 256 -> 1024
-            // 26.6 and 35.2, 32 x 960 -> 960 with 128 tiles 61.8 and 46.7; 64 x 1920 ->
-            // 960, K = 17280, 145.5 and 144.9; widths that do not tile: 32 x 12 x 12,
-            // 960 -> 960 107 and 95).  192-channel tiles where they need fewer rounds of
-            // the 256 units per channel (512 x 4 x 4, 512 -> 768: 60.3 against 76.3 us
-            // at one round against two; 64 x 8 x 8, 960 -> 960 89.8 and 76.3 at one each)
+            // (8 x 8 images, records included, this kernel and the fused one: 64 x 960 -> 960, B = 16
+            // 77.8 and 81.8 us, 128 x 512 -> 512 44.0 and 51.2, 64 x 256 -> 1024 25.6 and 31.7, 32 x 960 ->
+            // 960 with 128 tiles 60.0 and 45.1; 64 x 1920 -> 960, K = 17280, 138 and 136; widths that
+            // do not tile: 32 x 12 x 12, 960 -> 960 107 and 95).  192-channel tiles where they need
+            // fewer rounds of the 256 units per channel (512 x 4 x 4, 512 -> 768: 59.9 against 72.1 us
+            // at one round against two; 64 x 8 x 8, 960 -> 960, B = 16 82.6 and 77.8 at one each)
             aq::FusedPlan w128 = rp;
             if (wsplit_plan(r.geo, opt, 1, &w128, 128) && w128.ntiles >= 192) {
                 const bool wide = ok1 && w1.bn == 192 && (w1.ntiles + 255) / 256 * 3 < (w128.ntiles + 255) / 256 * 2;

@@ -270,6 +270,8 @@ def test_convolutions_of_one_codebook(child, n, cin, C_out, side, weights):
     (11162, 672, 197, 4, "bf16", "fused", "records"),          # 20, 42
     (417, 400, 3339, 4, "bf16", "fused", "in-loop-lds-bf16"),  # 14.6, 18.6
     (6976, 1144, 1415, 2, "bf16", "fused", "records"),         # 61, 104
+    (6386, 344, 438, 2, "bf16", "fused", "records"),           # 16.4, 21.6
+    (1094, 488, 1389, 2, "bf16", "fused", "in-loop-lds-bf16"),   # 13.2, 14.8
     (1174, 728, 4279, 2, "bf16", "fused", "in-loop-lds-bf16"),   # 35, 39
     (1088, 312, 2603, 1, "bf16", "generic", None),             # 17.5, 20.8
 ])
