@@ -22,7 +22,7 @@
 //
 // Measured, M = 2: 64 tokens x 256 -> 256 5.9 us (52.8 with the 64 x 64 vector-ALU
 // tiles this replaces, which decoded 16 k at a time between barriers); 256 x
-// 512 -> 512 8.6 us (101); 1000 x 704 -> 704 22.8 us (131), 43 TFLOP/s.
+// 512 -> 512 7.5 us (101); 1000 x 704 -> 704 22.8 us (131), 43 TFLOP/s.
 #include <algorithm>
 
 #include "aq_device.h"
