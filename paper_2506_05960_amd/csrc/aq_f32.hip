@@ -77,12 +77,52 @@ f32_fwd_kernel(Geom geo, const float* __restrict__ cb32, const CodeT* __restrict
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[a][r] = 0.0f;
 
-    auto load_x = [&](const int64_t t, int k) -> floatx4 {   // k .. k + 3 (past K: the last ones again)
-        if (xvec) return *reinterpret_cast<const floatx4*>(static_cast<const float*>(X) + t * K + min(k, K - 4));
-        floatx4 v;
+    // a convolution's token: its image and the input position of kernel tap (0, 0)
+    int64_t img[TM];
+    int ih0[TM], iw0[TM];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = x_elem<XT>(geo, X, t, min(k + e, K - 1));
-        return v;
+    for (int a = 0; a < TM; ++a) {
+        img[a] = 0;
+        ih0[a] = iw0[a] = 0;
+        if (geo.conv) {
+            const int64_t plane = (int64_t)geo.OH * geo.OW, b = tok[a] / plane;
+            const int p = (int)(tok[a] - b * plane), oh = p / geo.OW;
+            img[a] = b * geo.cin * (int64_t)geo.H * geo.W;
+            ih0[a] = oh * geo.stride - geo.pad;
+            iw0[a] = (p - oh * geo.OW) * geo.stride - geo.pad;
+        }
+    }
+    const int khw = geo.kh * geo.kw;
+    auto load_x = [&](auto& xv, int u, int k) {   // k .. k + 3 of every token (past K: the last ones again)
+        if (geo.conv) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int ke = min(k + e, K - 1);
+                int c = ke, r = 0, s = 0;
+                if (khw != 1) {
+                    c = ke / khw;
+                    r = (ke - c * khw) / geo.kw;
+                    s = ke - c * khw - r * geo.kw;
+                }
+#pragma unroll
+                for (int a = 0; a < TM; ++a) {
+                    const int ih = ih0[a] + r, iw = iw0[a] + s;
+                    const bool in = ih >= 0 && ih < geo.H && iw >= 0 && iw < geo.W;
+                    const float v = load_as_f32<XT>(X, in ? img[a] + ((int64_t)c * geo.H + ih) * geo.W + iw : 0);
+                    xv[a][u][e] = in ? v : 0.0f;
+                }
+            }
+            return;
+        }
+#pragma unroll
+        for (int a = 0; a < TM; ++a) {
+            if (xvec) {
+                xv[a][u] = *reinterpret_cast<const floatx4*>(static_cast<const float*>(X) + tok[a] * K + min(k, K - 4));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) xv[a][u][e] = load_as_f32<XT>(X, tok[a] * K + min(k + e, K - 1));
+            }
+        }
     };
     if constexpr (MC > 0) {
         constexpr int JC = 16 / MC;                  // groups (steps) per chunk
@@ -99,11 +139,10 @@ f32_fwd_kernel(Geom geo, const float* __restrict__ cb32, const CodeT* __restrict
             if (c + 1 < c_end) cw = cchunk[(int64_t)(c + 1) * geo.C_out];
 #pragma unroll
             for (int h = 0; h < JC / U; ++h) {
+                if (c * JC + h * U >= geo.G) break;   // a last chunk that ends before its second half
                 floatx4 xv[TM][U], wv[U];
 #pragma unroll
-                for (int a = 0; a < TM; ++a)
-#pragma unroll
-                    for (int u = 0; u < U; ++u) xv[a][u] = load_x(tok[a], 8 * (c * JC + h * U + u) + 4 * q);
+                for (int u = 0; u < U; ++u) load_x(xv, u, 8 * (c * JC + h * U + u) + 4 * q);
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
 #pragma unroll
@@ -138,9 +177,7 @@ f32_fwd_kernel(Geom geo, const float* __restrict__ cb32, const CodeT* __restrict
             // in range) and become zeros before the products
             floatx4 xv[TM][kF32Steps], wv[kF32Steps];
 #pragma unroll
-            for (int a = 0; a < TM; ++a)
-#pragma unroll
-                for (int u = 0; u < kF32Steps; ++u) xv[a][u] = load_x(tok[a], 8 * (s0 + u) + 4 * q);
+            for (int u = 0; u < kF32Steps; ++u) load_x(xv, u, 8 * (s0 + u) + 4 * q);
             if constexpr (MC == kF32G8) {
                 const CodeT* cp[kF32Steps];
 #pragma unroll

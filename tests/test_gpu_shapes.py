@@ -203,6 +203,8 @@ F32 = [
     _f32("s_i8", 50, 64, 40, x="i8", y="f16"),
     _f32("s_bf16", 50, 64, 40, x="bf16"),
     _f32("s_conv", 2, 12 * 9, 36, g=4, conv=ConvGeom(12, 3, 3, 2, 1, 9, 7)),
+    _f32("s_conv_m1", 3, 24 * 9, 70, M=1, conv=ConvGeom(24, 3, 3, 1, 1, 9, 11)),     # a chunk that ends in its first half
+    _f32("s_conv1_s2", 3, 40, 36, M=4, conv=ConvGeom(40, 1, 1, 2, 0, 11, 7)),
 ]
 
 
