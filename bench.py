@@ -146,7 +146,7 @@ def _graph_time_us(torch, fn, reps: int, trials: int = 5) -> float:
 
 
 PRODUCT_KERNELS = ("fused_fwd_kernel", "rec_conv_kernel", "rec_linear_kernel", "rec_gemm_kernel", "mfma_fwd_kernel",
-                   "f32_fwd_kernel", "lut_fwd_kernel")
+                   "f32_fwd_kernel", "f32_tile_kernel", "lut_fwd_kernel")
 
 
 def launch_times(torch, items, replays: int = 5, graph_reps: int = 10):

@@ -254,6 +254,80 @@ f32_fwd_kernel(Geom geo, const float* __restrict__ cb32, const CodeT* __restrict
     }
 }
 
+// Short reductions in many tiles (f32_tile_better): 64 x 64 tiles on the vector ALUs, 16 k of activations and
+// of decoded weights at a time staged in LDS, 4 x 4 outputs a thread.  Bound by the staging's
+// index arithmetic and loads; no prologue or partial tiles, which at K = 8 take three times its time.
+constexpr int kF32BM = 64, kF32BN = 64, kF32BK = 16;
+
+template <int XT, typename CodeT>
+__global__ void __launch_bounds__(256)
+f32_tile_kernel(Geom geo, const float* __restrict__ cb32, const CodeT* __restrict__ codes,
+               const float* __restrict__ scales, const void* __restrict__ X, const float* __restrict__ x_scales,
+               void* __restrict__ Y, int y_dtype) {
+    __shared__ float xs[kF32BK][kF32BM + 4];
+    __shared__ float wsh[kF32BK][kF32BN + 4];
+    const int tid = threadIdx.x;
+    const int tx = tid & 15, ty = tid >> 4;
+    const int64_t m0 = (int64_t)blockIdx.x * kF32BM;
+    const int n0 = blockIdx.y * kF32BN;
+    const int g = geo.g, M = geo.M;
+    const int64_t nk = (int64_t)1 << geo.B;
+    float acc[4][4] = {};
+
+    for (int k0 = 0; k0 < geo.K; k0 += kF32BK) {
+        // 64 x 16 activations and 64 x 16 decoded weights, 4 of each per thread
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int e = tid + q * 256;
+            const int row = e & 63;
+            const int kk = e >> 6;
+            const int k = k0 + kk;
+            const int64_t tok = m0 + row;
+            xs[kk][row] = (tok < geo.tokens && k < geo.K) ? x_elem<XT>(geo, X, tok, k) : 0.0f;
+            const int co = n0 + row;
+            float w = 0.0f;
+            if (co < geo.C_out && k < geo.K) {
+                const int j = k / g;
+                const int t = k - j * g;
+                const CodeT* bp = codes + ((int64_t)co * geo.G + j) * M;
+                w = cb32[(int64_t)bp[0] * g + t];
+                for (int m = 1; m < M; ++m) w = __fadd_rn(w, cb32[((int64_t)m * nk + bp[m]) * g + t]);
+            }
+            wsh[kk][row] = w;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int kk = 0; kk < kF32BK; ++kk) {
+            float a[4], b[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                a[i] = xs[kk][ty * 4 + i];
+                b[i] = wsh[kk][tx * 4 + i];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) acc[i][jj] = fmaf(a[i], b[jj], acc[i][jj]);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t tok = m0 + ty * 4 + i;
+        if (tok >= geo.tokens) continue;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+            const int co = n0 + tx * 4 + jj;
+            if (co >= geo.C_out) continue;
+            float v = acc[i][jj] * scales[co];
+            if (x_scales) v *= x_scales[tok];
+            const int64_t yi = y_index(geo, tok, co);
+            if (y_dtype == AQ_F32) static_cast<float*>(Y)[yi] = v;
+            else static_cast<uint16_t*>(Y)[yi] = f32_to_f16(v);
+        }
+    }
+}
+
 template <int XT, typename CodeT, int MC, int NW, int TM>
 static hipError_t f32_launch_cfg(const Geom& geo, const DeviceWeights& w, const void* X, const float* x_scales,
                                  void* Y, int y_dtype, hipStream_t st) {
@@ -286,9 +360,44 @@ static hipError_t f32_launch_mode(const Geom& geo, const DeviceWeights& w, const
     return f32_launch_cfg<XT, CodeT, MC, 16, 1>(geo, w, X, x_scales, Y, y_dtype, st);
 }
 
+// Short reductions in many 64 x 64 tiles: the tile kernel.  A chunk of codes covers 128 / M k, so
+// a short K leaves waves of the other kernel without one, and its workgroups copy the codebooks and
+// add their partial tiles for little work; group sizes other than 8 read their codewords there value by value.
+// The limits are where both are even, from some 2000 layers (tile kernel and the other, us: 16511
+// tokens 8 -> 3172, M = 2 107 and 353; 5393 tokens 72 -> 1097, M = 1 38 and 64; 4554 tokens 24 -> 338, M = 2
+// 12.0 and 16.4; 1808 tokens 120 -> 1422, M = 1 32.5 and 33.0; 1x1 17712 tokens 280 -> 666, M = 1 272 and 312;
+// g = 12, M = 4 9727 tokens 144 -> 252 71 and 108).
+template <int XT>
+static bool f32_tile_better(const Geom& geo, const DeviceWeights& w) {
+    const int64_t tiles = ((geo.tokens + kF32BM - 1) / kF32BM) * ((geo.C_out + kF32BN - 1) / kF32BN);
+    if (tiles < 128 || geo.tokens >= (int64_t(1) << 29)) return false;   // (more rows than its grid takes)
+    const bool chunks = XT == AQ_F32 && w.codes_lut && geo.B <= 8;       // the other kernel's chunked codes, g = 8
+    const int size = tiles < 200 ? 0 : tiles < 256 ? 1 : tiles < 300 ? 2 : tiles < 800 ? 3 : 4;
+    // longest K by tiles, from 128, 200, 256, 300 and 800 up
+    static constexpr int m1[5] = {16, 16, 16, 136, 192}, m1_conv[5] = {72, 72, 100, 160, 400};
+    static constexpr int m2[5] = {16, 16, 16, 40, 72}, m2_conv[5] = {16, 24, 72, 104, 192};
+    static constexpr int m4[5] = {0, 0, 0, 16, 16}, m4_conv[5] = {0, 0, 0, 40, 40};
+    static constexpr int any[5] = {16, 33, 33, 48, 72}, any_m1[5] = {16, 16, 16, 33, 152};
+    static constexpr int groups_m1[5] = {0, 48, 48, 150, 300}, groups_m2[5] = {0, 48, 48, 300, 350}, groups[5] = {0, 48, 48, 200, 400};
+    const int* limit = geo.g != 8               ? (geo.M == 1 ? groups_m1 : geo.M == 2 ? groups_m2 : groups)
+                       : chunks && geo.M == 1   ? (geo.conv ? m1_conv : m1)
+                       : chunks && geo.M == 2   ? (geo.conv ? m2_conv : m2)
+                       : chunks && geo.M == 4   ? (geo.conv ? m4_conv : m4)
+                       : geo.M == 1             ? any_m1
+                                                : any;
+    return geo.K <= limit[size] || (!geo.conv && geo.g == 8 && geo.M == 3 && geo.K <= 33);
+}
+
 template <int XT, typename CodeT>
 static hipError_t f32_launch_x(const Geom& geo, const DeviceWeights& w, const void* X, const float* x_scales, void* Y,
                                int y_dtype, hipStream_t st) {
+    if (f32_tile_better<XT>(geo, w)) {
+        const dim3 grid((unsigned)((geo.tokens + kF32BM - 1) / kF32BM), (unsigned)((geo.C_out + kF32BN - 1) / kF32BN));
+        f32_tile_kernel<XT, CodeT><<<grid, 256, 0, st>>>(geo, w.cb32, static_cast<const CodeT*>(w.codes), w.scales, X,
+                                                         x_scales, Y, y_dtype);
+        note_launch(st, "f32_tile_kernel", {XT, 8 * (int)sizeof(CodeT)});
+        return hipGetLastError();
+    }
     if (geo.g != 8) return f32_launch_mode<XT, CodeT, kF32AnyG>(geo, w, X, x_scales, Y, y_dtype, st);
     if constexpr (sizeof(CodeT) == 1 && XT == AQ_F32) {
         // chunks of 16 code bytes per channel (the table path's code layout for these M:

@@ -205,6 +205,13 @@ F32 = [
     _f32("s_conv", 2, 12 * 9, 36, g=4, conv=ConvGeom(12, 3, 3, 2, 1, 9, 7)),
     _f32("s_conv_m1", 3, 24 * 9, 70, M=1, conv=ConvGeom(24, 3, 3, 1, 1, 9, 11)),     # a chunk that ends in its first half
     _f32("s_conv1_s2", 3, 40, 36, M=4, conv=ConvGeom(40, 1, 1, 2, 0, 11, 7)),
+    # short reductions in many tiles: the tile kernel, partial tiles on both edges
+    _f32("t_k8", 1001, 8, 715),
+    _f32("t_k24", 1280, 24, 1025, M=1, y="f16"),
+    _f32("t_g3", 1290, 27, 1030, g=3, B=5),
+    _f32("t_i8", 1300, 40, 970, M=3, x="i8"),
+    _f32("t_conv", 3, 8 * 9, 460, M=1, conv=ConvGeom(8, 3, 3, 1, 1, 25, 33)),
+    _f32("t_conv1", 5, 32, 300, M=2, B=10, conv=ConvGeom(32, 1, 1, 2, 0, 51, 49)),
 ]
 
 
@@ -245,16 +252,17 @@ def test_f32_infinite_codeword():
 def test_f32_more_tiles_than_one_grid_row():
     """1050624 tiles: the last ones, in the grid's second row, and the first against the 64-bit product."""
     import paper_2506_05960_amd as P
-    spec = _f32("s_grid", 65600, 8, 32800, M=1, B=8, y="f16")
+    spec = _f32("s_grid", 65600, 200, 32800, M=1, B=8, y="f16")
     rng = np.random.default_rng(7203)
     inp = {"codebooks": rng.standard_normal((1, 256, 8)).astype(np.float32),
-           "codes": rng.integers(0, 256, (spec.C_out, 1, 1), dtype=np.uint8),
+           "codes": rng.integers(0, 256, (spec.C_out, 25, 1), dtype=np.uint8),
            "scales": rng.uniform(0.5, 1.5, spec.C_out).astype(np.float32)}
-    x = torch.from_numpy(rng.standard_normal((spec.n, 8)).astype(np.float32)).cuda()
+    x = torch.from_numpy(rng.standard_normal((spec.n, spec.K)).astype(np.float32)).cuda()
     layer = P.AQLayer(spec, inp)
     layer.set_path("decode")
     y = layer.forward(x)
-    w = torch.from_numpy(inp["codebooks"][0][inp["codes"][:, 0, 0]] * inp["scales"][:, None]).cuda().double()
+    assert layer.last_launches()[1][0].startswith("f32_fwd_kernel")
+    w = torch.from_numpy(inp["codebooks"][0][inp["codes"][:, :, 0]].reshape(spec.C_out, spec.K) * inp["scales"][:, None]).cuda().double()
     for rows in (slice(0, 40), slice(spec.n // 2, spec.n // 2 + 40), slice(spec.n - 80, spec.n)):
         ref = x[rows].double() @ w.t()
         assert torch.all((y[rows].double() - ref).abs() <= 2.0**-11 * ref.abs() + 2.0**-24 + 2e-6 * (x[rows].double().abs() @ w.abs().t()))

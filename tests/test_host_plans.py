@@ -316,10 +316,28 @@ def test_waves_and_splits_of_convolution_gradients(child, n, k, cin, C_out, H, h
     assert child("_grad", n, dict(kw, max_n=8 * n)) == [kernel, blocks]
 
 
+@pytest.mark.parametrize("n,K,C_out,conv,M,g,x,kernel", [
+    (16511, 8, 3172, None, 2, 8, "f32", "f32_tile_kernel"),      # 107 us, matrix cores 353
+    (5393, 72, 1097, None, 1, 8, "f32", "f32_tile_kernel"),      # 38, 64
+    (4554, 24, 338, None, 2, 8, "f32", "f32_tile_kernel"),       # 12.0, 16.4
+    (5711, 256, 611, None, 1, 8, "f32", "f32_fwd_kernel"),
+    (5000, 40, 600, None, 4, 8, "f32", "f32_fwd_kernel"),
+    (914, 48, 3844, None, 4, 4, "f32", "f32_tile_kernel"),       # 35, 53
+    (1332, 144, 694, None, 4, 16, "f32", "f32_fwd_kernel"),      # 43.6, tiles 48.5
+    (3, 0, 675, (64, 1, 1, 0, 40, 49), 2, 8, "f32", "f32_tile_kernel"),
+    (3, 0, 675, (64, 1, 1, 0, 40, 49), 4, 8, "f32", "f32_fwd_kernel"),
+    (64, 256, 256, None, 2, 8, "f32", "f32_fwd_kernel"),
+    (512, 24, 512, None, 2, 8, "f32", "f32_fwd_kernel"),
+])
+def test_fp32_layers(child, n, K, C_out, conv, M, g, x, kernel):
+    kw = dict(C_out=C_out, M=M, g=g, x=x, cb="f32", tile="f32", y="f32", conv=conv)
+    assert child("_conv_limit", n, {}, dict(kw, K=K)) == [kernel]
+
+
 # ---- launches ----
 
 def _f32_large(n, C_out):
-    layer = hd.Layer(C_out, 8, M=1, B=4, max_n=n, x="f32", cb="f32", tile="f32").set(lut_max_tokens=-1)
+    layer = hd.Layer(C_out, 200, M=1, B=4, max_n=n, x="f32", cb="f32", tile="f32").set(lut_max_tokens=-1)
     kernels, launches = hd.launches(lambda: layer.forward(n))
     return kernels, launches[-1]
 
