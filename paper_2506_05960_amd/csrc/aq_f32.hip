@@ -370,7 +370,7 @@ static hipError_t f32_launch_mode(const Geom& geo, const DeviceWeights& w, const
 template <int XT>
 static bool f32_tile_better(const Geom& geo, const DeviceWeights& w) {
     const int64_t tiles = ((geo.tokens + kF32BM - 1) / kF32BM) * ((geo.C_out + kF32BN - 1) / kF32BN);
-    if (tiles < 128 || geo.tokens >= (int64_t(1) << 29)) return false;   // (more rows than its grid takes)
+    if (tiles < 128 || geo.tokens >= (int64_t(1) << 29) || geo.C_out > (1 << 21)) return false;   // (more than its grid takes)
     const bool chunks = XT == AQ_F32 && w.codes_lut && geo.B <= 8;       // the other kernel's chunked codes, g = 8
     const int size = tiles < 200 ? 0 : tiles < 256 ? 1 : tiles < 300 ? 2 : tiles < 800 ? 3 : 4;
     // longest K by tiles, from 128, 200, 256, 300 and 800 up
