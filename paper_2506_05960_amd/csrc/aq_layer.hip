@@ -986,7 +986,7 @@ bool bf16_generic(const Geom& geo, const aq::FusedPlan& p) {
     return odd4 && !p.rec_only && wgs > 256 && geo.K < std::min<int64_t>(1024, 160 * ((wgs + 255) / 256));
 }
 
-// Convolutions that do not tile (1x1: planes of an odd pixel count), in more than one round of
+// Convolutions that do not tile (1x1 with stride 1: planes of an odd pixel count), in more than one round of
 // 64 x 64 tiles: the generic kernel where its estimate is not clearly the longer one.  Both in us, in rounds of 256 workgroups,
 // fitted to 126 layers with one of the tiles on a compute unit (K = 72 to 632; the fused kernel's
 // within 5 % for 1x1 and 14 % for 3x3, the generic one's mostly within 15 %) and 40 with two.  Fused
@@ -994,7 +994,12 @@ bool bf16_generic(const Geom& geo, const aq::FusedPlan& p) {
 // tokens 64 -> 209 (M = 2) 121 and 130; 1x1 on 29 x 39, 53157 tokens 136 -> 832 (M = 2) 359 and 202, 13 x
 // 33, 10725 tokens 400 -> 304 (M = 2) 46 and 68.
 bool uneven_rounds_generic(const Geom& geo, const Geom& kgeo, const aq::FusedPlan& p) {
-    if (p.wsplit || p.splitk > 1 || p.ntiles <= 256 || (geo.kh == 1 && kgeo.W % 2 == 0)) return false;
+    // 1x1 of three groups per channel (four with 16-bit codes), one codebook, in up to two rounds: one
+    // launch (3348 tokens 24 -> 512 10.3 and 11.0, 1656 tokens 32 -> 40, B = 16 8.7 and 9.5; 2880 tokens
+    // 24 -> 784, 585 tiles 16.0 and 13.6), and four codebooks in more (31842 tokens 24 -> 393 44 and 51)
+    if (!p.wsplit && geo.kh == 1 && geo.M == 1 && geo.K <= (geo.B > 8 ? 32 : 24) && p.ntiles <= 512) return true;
+    if (!p.wsplit && geo.kh == 1 && geo.M == 4 && geo.K <= 24 && p.ntiles > 512) return true;
+    if (p.wsplit || p.splitk > 1 || p.ntiles <= 256 || (geo.kh == 1 && geo.stride == 1 && kgeo.W % 2 == 0)) return false;
     // one chunk for four waves, one codebook (22960 tokens on 7 x 41, 16 -> 720 101 and 83)
     if (p.bm == 128 && geo.kh == 3 && geo.M == 1 && geo.K <= 144) return true;
     if (p.bm != 64 || p.bn != 64) return false;
@@ -1009,8 +1014,9 @@ bool uneven_rounds_generic(const Geom& geo, const Geom& kgeo, const aq::FusedPla
     double generic = t128 >= 256 ? rounds(t128) * (7.6 + (0.0505 + 0.0176 * m4 - 0.0137 * k3) * K) + 8.0 + 0.0595 * K
                      : t64 >= 256  ? rounds(t64) * (5.2 + (0.0508 + 0.0114 * m4 - 0.0113 * k3) * K) + 2.6 + 0.0254 * K
                                    : 7.7 + (0.069 + 0.0356 * m4 - 0.0098 * k3) * K;
-    if (geo.B > 8 && geo.M == 1) generic *= 0.85;     // one codebook, read as it is from the L2
-    return generic < 1.08 * fused;
+    if (geo.B > 8 && geo.M == 1 && t128 >= 256) generic *= 0.85;     // one codebook, read as it is from the L2
+    // (1x1 with a stride: few of the fitted layers, so only where it is clearly the shorter one)
+    return generic < (!k3 && geo.stride > 1 ? 0.9 : 1.08) * fused;
 }
 
 Route plan_route(const aq_layer* L, const Geom& geo) {

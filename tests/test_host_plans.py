@@ -246,9 +246,21 @@ def test_short_reductions_of_uneven_convolutions(child, n, cin, C_out, k, M, sid
     (13, 1, 272, 272, 61, 29, 1, 12, "generic"),     # 70, 84
     (25, 1, 400, 304, 13, 33, 2, 8, "fused"),        # 46, 68
     (1, 1, 152, 360, 13, 33, 2, 8, "fused"),         # one round
+    (1, 1, 24, 512, 62, 54, 1, 8, "generic"),        # 10.3, 11.0
+    (1, 1, 24, 784, 48, 60, 1, 16, "fused"),         # 13.6, 16.0
+    (1, 1, 40, 512, 62, 54, 1, 8, "fused"),
 ])
 def test_uneven_convolutions_in_many_tiles(child, n, k, cin, C_out, H, W, M, B, route):
     assert child("_route", n, dict(C_out=C_out, M=M, B=B, conv=(cin, k, 1, k // 2, H, W)))[0] == route
+
+
+@pytest.mark.parametrize("n,cin,C_out,H,W,M,B,route", [
+    (932, 192, 143, 33, 7, 1, 8, "generic"),         # 80 us, fused 110
+    (126, 160, 288, 59, 16, 1, 16, "generic"),       # 53, 72
+    (71, 104, 468, 9, 32, 1, 16, "fused"),           # 24, 32
+])
+def test_strided_uneven_convolutions_in_many_tiles(child, n, cin, C_out, H, W, M, B, route):
+    assert child("_route", n, dict(C_out=C_out, M=M, B=B, conv=(cin, 1, 2, 0, H, W)))[0] == route
 
 
 @pytest.mark.parametrize("n,cin,C_out,side,weights", [
