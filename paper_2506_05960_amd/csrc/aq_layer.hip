@@ -957,7 +957,15 @@ bool few_route(const aq_layer* L, const Geom& geo) {
         if (geo.M >= 2 && geo.tokens > 2 && geo.C_out > 8192) return false;
         if (geo.M == 4 ? geo.tokens * geo.K > 4608 : geo.tokens * geo.K > 35000 || geo.K > 14000) return false;
     }
-    if (geo.M == 4 && geo.K > 16000 && geo.C_out > 2048) return false;
+    if (geo.M == 4 && geo.K > (geo.tokens == 2 ? 12000 : 16000) && geo.C_out > 2048) return false;
+    // Three and four tokens with M = 4 read four times the X per codeword: the second round over
+    // 2048 rows pays up to K = 4096 only, a first one over 1024 rows up to 11300 (3 tokens, this kernel
+    // and the others: 13392 -> 2160 26.2 and 16.2, 5520 -> 2224 13.3 and 11.6, 3680 -> 2456 10.2 and 10.3,
+    // 14184 -> 1152 16.8 and 15.4, 9016 -> 1640 12.1 and 13.3, 16456 -> 520 12.8 and 15.3).  With M = 2 and over
+    // 4096 rows it is the longer one just below the K from which the table path is the other (4 tokens
+    // 4040 -> 4288 11.3 and 10.1, 5528 -> 3952 10.0 and 17.0)
+    if (geo.M == 4 && geo.tokens >= 3 && ((geo.C_out > 2048 && geo.K > 4096) || (geo.C_out > 1024 && geo.K > 11300))) return false;
+    if (geo.M == 2 && geo.tokens >= 3 && geo.C_out > 4096 && geo.K > 3400 && geo.K < 4096) return false;
     return geo.tokens * geo.K * geo.C_out <= (geo.M == 4 ? int64_t(100) * 1000000 : int64_t(300) * 1000000);
 }
 

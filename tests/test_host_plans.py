@@ -292,6 +292,23 @@ def test_linear_layers_of_odd_output_rows(child, n, K, C_out, M, dt, route, weig
     assert child("_route", n, kw, {"lut_max_tokens": -1})[:2] == [route, weights]
 
 
+@pytest.mark.parametrize("n,K,C_out,M,route", [
+    (3, 13392, 2160, 4, "fused"),         # 16.2 us, few-token kernel 26.2
+    (4, 4176, 2720, 4, "fused"),          # 11.3, 11.9
+    (4, 3912, 2224, 4, "few-token"),      # 10.3, 10.9
+    (4, 14184, 1152, 4, "fused"),         # 15.4, 16.8
+    (4, 10896, 432, 4, "few-token"),      # 9.9, 13.5
+    (4, 17208, 464, 4, "few-token"),      # 13.1, 16.0
+    (2, 12400, 2320, 4, "fused"),         # 16.3, 17.1
+    (2, 10096, 4048, 4, "few-token"),     # 14.8, 16.9
+    (4, 4040, 4288, 2, "fused"),          # 10.1, 11.3
+    (4, 5528, 3952, 2, "few-token"),      # 10.0, 17.0
+])
+@pytest.mark.parametrize("x", ["f16", "i8"])
+def test_few_token_layers(child, n, K, C_out, M, route, x):
+    assert child("_route", n, dict(C_out=C_out, K=K, M=M, x=x))[0] == route
+
+
 def _grad(n, kw):
     layer = hd.Layer(**{"max_n": n, **kw})
     kernels, launches = hd.launches(lambda: layer.grad(n, "f16"))
