@@ -745,14 +745,16 @@ bool gemm_plan_tile(const Geom& geo, const aq::Options& opt, aq::FusedPlan* p) {
 }
 
 // A 3x3 layer of one or two codebooks whose weights are few and whose in-loop
-// tiles (128 x 64, or 64 x 96 for more than 64 channels) run in one round: it
-// decodes in the loop faster than a records launch does once (32768 tokens, M = 2:
-// 64 -> 64 10.0 against 13.1 us, but 32 -> 96, two rounds, 14.3 against 12.4;
-// 65536 tokens 32 -> 64 18.1 against 14.2).  Very short reductions only with few
-// tokens (16 -> 32: 4096 tokens 6.6 and 8.6 us with M = 1, 32768 tokens 9.2 and 7.9).
+// tiles (128 x 64, or 64 x 96 for more than 64 channels) run in one round (with a
+// stride, which leaves 64 x 64, in not much more): it decodes in the loop faster than
+// a records launch does once (32768 tokens, M = 2: 64 -> 64 10.0 against 13.1 us, but
+// 32 -> 96, two rounds, 14.3 against 12.4; 65536 tokens 32 -> 64 18.1 against 14.2;
+// stride 2, 32 -> 32 20480 tokens 13.5 against 15.5, 32768 13.9 against 10.5).  Very
+// short reductions only with few tokens (16 -> 32: 4096 tokens 6.6 and 8.6 us with
+// M = 1, 32768 tokens 9.2 and 7.9).
 bool small_weights(const Geom& geo, const aq::FusedPlan& p) {
     return p.kind == 1 && p.dec == aq::FUSED_DEC_PK16 && p.mc <= 2 && geo.C_out <= 96 &&
-           (int64_t)geo.K * geo.C_out <= 50000 && geo.tokens <= 256 * (geo.C_out > 64 ? 64 : 128) &&
+           (int64_t)geo.K * geo.C_out <= 50000 && geo.tokens <= 256 * (geo.stride > 1 ? 88 : geo.C_out > 64 ? 64 : 128) &&
            (geo.K >= 288 || geo.C_out > 32 || geo.tokens <= 16384);
 }
 
