@@ -375,7 +375,7 @@ static bool f32_tile_better(const Geom& geo, const DeviceWeights& w) {
     const int size = tiles < 200 ? 0 : tiles < 256 ? 1 : tiles < 300 ? 2 : tiles < 800 ? 3 : 4;
     // longest K by tiles, from 128, 200, 256, 300 and 800 up
     static constexpr int m1[5] = {16, 16, 16, 136, 192}, m1_conv[5] = {72, 72, 100, 160, 400};
-    static constexpr int m2[5] = {16, 16, 16, 40, 72}, m2_conv[5] = {16, 24, 72, 104, 192};
+    static constexpr int m2[5] = {16, 16, 16, 40, 88}, m2_conv[5] = {16, 24, 72, 104, 192};
     static constexpr int m4[5] = {0, 0, 0, 16, 16}, m4_conv[5] = {0, 0, 0, 40, 40};
     static constexpr int any[5] = {16, 33, 33, 48, 72}, any_m1[5] = {16, 16, 16, 33, 152};
     static constexpr int groups_m1[5] = {0, 48, 48, 150, 300}, groups_m2[5] = {0, 48, 48, 300, 350}, groups[5] = {0, 48, 48, 200, 400};

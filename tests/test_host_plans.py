@@ -357,6 +357,7 @@ def test_waves_and_splits_of_convolution_gradients(child, n, k, cin, C_out, H, h
     (4554, 24, 338, None, 2, 8, "f32", "f32_tile_kernel"),       # 12.0, 16.4
     (5711, 256, 611, None, 1, 8, "f32", "f32_fwd_kernel"),
     (5000, 40, 600, None, 4, 8, "f32", "f32_fwd_kernel"),
+    (2639, 80, 2198, None, 2, 8, "f32", "f32_tile_kernel"),      # 50, 58
     (914, 48, 3844, None, 4, 4, "f32", "f32_tile_kernel"),       # 35, 53
     (1332, 144, 694, None, 4, 16, "f32", "f32_fwd_kernel"),      # 43.6, tiles 48.5
     (3, 0, 675, (64, 1, 1, 0, 40, 49), 2, 8, "f32", "f32_tile_kernel"),
